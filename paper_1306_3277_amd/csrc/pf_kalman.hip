@@ -1,15 +1,17 @@
 // The windkessel model's Kalman filter (Sec. 3.1.1, Alg. 1 reduced to one
 // dimension: every Cholesky factor is a square root), batched over filters,
-// one lane per filter, in FP64:
+// in FP64.  Runs over many intervals come in two forms, one wave per filter
+// with the intervals spread over its lanes (kf_wave) and one lane per filter:
 //   k_kf_run          whole runs over t = 1..T (the exact likelihood)
 //   k_kf_proposal     SMC over the parameters with attached Kalman filters:
 //                     each proposal's filter over t_{0:i-1}
 //   k_kf_advance      every attached filter over t_{i-1:i}
 //   k_smc2_accept_kf  the Metropolis-Hastings decision with those filters
 //   k_kf_pmmh         marginal Metropolis-Hastings chains on (R, C, Z,
-//                     sigma^2) with the exact likelihood, a chain per lane
+//                     sigma^2) with the exact likelihood
 #include <math.h>
 
+#include "pf_device.hpp"
 #include "pf_kalman.hpp"
 
 namespace pfk {
@@ -34,6 +36,226 @@ __device__ __forceinline__ double kf_interval(const double* th, const KfArgs& A,
   return e;
 }
 
+// ---------------------------------------------------------------- a filter over a wave's lanes
+// A run of T intervals by one wave, KF_L consecutive intervals per lane and
+// 64 KF_L per pass.  The lane-per-filter form is a chain of T (2 K + a
+// logarithm and two divisions) dependent steps, about 0.74 us per interval
+// with the scalar loads of the flow on its path, while a batch of hundreds of
+// filters fills a few lanes of a few CUs.  The chain breaks into parts that
+// do not depend on each other or compose associatively:
+//   - K predictions are m <- a^K m + c g_t, V <- a^{2K} V + C2, with
+//     g_t = sum_s a^{K-1-s} q_{tK+s} depending on the flow alone and C2 the
+//     same for every interval;
+//   - prediction and correction take the variance to V' = R P / (P + R),
+//     P = a^{2K} V + C2: a fractional-linear map with the same matrix
+//     [[R a^{2K}, R C2], [a^{2K}, C2 + R]] at every interval, so a lane's
+//     first variance is a power of that matrix applied to the pass's first
+//     (powers by squaring; the entries are non-negative, so nothing cancels
+//     and each squaring perturbs the map by an ulp of its entries);
+//   - given the gains the mean's maps m' = alpha m + beta compose by a wave
+//     scan.
+// The logarithms and divisions then run in all lanes at once.  512 chains
+// over T = 100, K = 10: 4.5 us an iteration against 74 (two waves per SIMD,
+// still latency: two intervals per lane interleave); 512 likelihoods: 57 us a
+// call, most of it the copies of the results, against 147.  Against 80-bit
+// arithmetic its likelihoods are within 1.2e-15 relative where the chain's
+// are within 3.6e-15 (T = 300, K = 20: 3.6e-15 and 2.5e-15).  Which form
+// runs: kf_wave_form.
+constexpr int KF_L = 2;
+
+// Flow and observations in memory, or staged in LDS with the substeps as
+// rows (lanes read consecutive entries).
+struct KfSeriesMem {
+  const double *qp, *yp;
+  int K;
+  __device__ __forceinline__ double q(int t, int s) const { return qp[(int64_t)t * K + s]; }
+  __device__ __forceinline__ double q_end(int t) const { return qp[(int64_t)(t + 1) * K]; }
+  __device__ __forceinline__ double y(int t) const { return yp[t]; }
+};
+struct KfSeriesLds {
+  const double *qp, *yp;
+  int ld;  // T + 1
+  __device__ __forceinline__ double q(int t, int s) const { return qp[s * ld + t]; }
+  __device__ __forceinline__ double q_end(int t) const { return qp[t + 1]; }
+  __device__ __forceinline__ double y(int t) const { return yp[t]; }
+};
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// inclusive scan of the affine maps (a, b): lane l gets the composition of
+// lanes 0..l's, first lane applied first
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void affine_step(double& a, double& b) {
+  const double pa = dpp_move<CTRL, ROWS>(a, 1.0), pb = dpp_move<CTRL, ROWS>(b, 0.0);
+  b = __builtin_fma(a, pb, b);
+  a = a * pa;
+}
+__device__ __forceinline__ void wave_affine_scan(double& a, double& b) {
+  affine_step<0x111, 0xf>(a, b);
+  affine_step<0x112, 0xf>(a, b);
+  affine_step<0x114, 0xf>(a, b);
+  affine_step<0x118, 0xf>(a, b);
+  affine_step<0x142, 0xa>(a, b);
+  affine_step<0x143, 0xc>(a, b);
+}
+
+// The log-likelihood of T intervals from N(m, V), every lane of the wave
+// active; th uniform.  ell (or null) receives the T increments; m and V
+// become the filtered mean and variance.  The result is the same in every
+// lane.
+template <class Series>
+__device__ __forceinline__ double kf_wave(const double* th, int K, int T, double R,
+                                          const Series& Q, double& m, double& V,
+                                          double* __restrict__ ell) {
+  const double a = th[0], c = th[1], Z = th[2], sp = th[3];
+  const int lane = threadIdx.x & (WAVE - 1);
+  // a^K as a sum of two doubles, and C2 with a^2 as one: the same rounding
+  // error at every interval would add up where the substeps' own cancel
+  double aK = 1.0, aKl = 0.0, C2 = 0.0;
+  const double a2 = a * a, a2l = __builtin_fma(a, a, -a2), sp2 = sp * sp;
+  for (int s = 0; s < K; ++s) {
+    const double p = aK * a;
+    aKl = __builtin_fma(aKl, a, __builtin_fma(aK, a, -p));
+    aK = p;
+    C2 = __builtin_fma(a2, C2, __builtin_fma(a2l, C2, sp2));
+  }
+  const double A2 = __builtin_fma(aK, aK, 2.0 * aK * aKl);
+  // P[j]: the variance map of KF_L 2^j intervals, scaled by powers of two so
+  // that nothing overflows
+  const bool stable = __builtin_fabs(a) <= 1.0;
+  double P[6][4];
+  {
+    double M[4] = {R * A2, R * C2, A2, C2 + R};
+    const int e0 = -__builtin_amdgcn_frexp_exp((M[0] + M[1]) + (M[2] + M[3]));
+#pragma unroll
+    for (int p = 0; p < 4; ++p) M[p] = __builtin_ldexp(M[p], e0);
+    auto square = [](const double(&x)[4], double(&r)[4]) {
+      const double p0 = __builtin_fma(x[0], x[0], x[1] * x[2]);
+      const double p1 = x[1] * (x[0] + x[3]);
+      const double p2 = x[2] * (x[0] + x[3]);
+      const double p3 = __builtin_fma(x[3], x[3], x[1] * x[2]);
+      const int e = -__builtin_amdgcn_frexp_exp((p0 + p1) + (p2 + p3));
+      r[0] = __builtin_ldexp(p0, e);
+      r[1] = __builtin_ldexp(p1, e);
+      r[2] = __builtin_ldexp(p2, e);
+      r[3] = __builtin_ldexp(p3, e);
+    };
+    static_assert(KF_L == 2, "the first power is one squaring");
+    square(M, P[0]);
+#pragma unroll
+    for (int j = 1; j < 6; ++j) square(P[j - 1], P[j]);
+  }
+  double tot = 0.0;
+  for (int t0 = 0; t0 < T; t0 += WAVE * KF_L) {
+    const int tl = t0 + lane * KF_L;  // this lane's first interval
+    double g[KF_L], b[KF_L];
+#pragma unroll
+    for (int e = 0; e < KF_L; ++e) {
+      const int t = min(tl + e, T - 1);
+      g[e] = 0.0;
+      b[e] = Q.y(t) - Z * Q.q_end(t);
+    }
+#pragma unroll 4
+    for (int s = 0; s < K; ++s)
+#pragma unroll
+      for (int e = 0; e < KF_L; ++e)
+        g[e] = __builtin_fma(a, g[e], Q.q(min(tl + e, T - 1), s));
+    // the variance at the lane's first interval
+    double vx = V, vy = 1.0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const double nx = __builtin_fma(P[j][0], vx, P[j][1] * vy);
+      const double ny = __builtin_fma(P[j][2], vx, P[j][3] * vy);
+      const bool on = (lane >> j) & 1;
+      vx = on ? nx : vx;
+      vy = on ? ny : vy;
+    }
+    double Vl = vx / vy;
+    // no circuit's a = exp(-h/(RC)) exceeds 1; for one that is given all the
+    // same the powers' entries may spread beyond the exponent range: step by
+    // step
+    if (!stable) {
+      Vl = V;
+      for (int n = 0; n < lane * KF_L; ++n) {
+        const double Pv = __builtin_fma(A2, Vl, C2);
+        Vl = R * (Pv / (Pv + R));
+      }
+    }
+    double S[KF_L], iS[KF_L], Kg[KF_L];
+    double al = 1.0, be = 0.0;
+#pragma unroll
+    for (int e = 0; e < KF_L; ++e) {
+      const bool in = tl + e < T;
+      const double Pv = __builtin_fma(A2, Vl, C2);
+      S[e] = Pv + R;
+      iS[e] = 1.0 / S[e];
+      Kg[e] = Pv * iS[e];
+      const double rest = R * iS[e];  // 1 - Kg
+      Vl = in ? R * Kg[e] : Vl;
+      g[e] = c * g[e];
+      const double ae = __builtin_fma(aK, rest, aKl * rest), bb = __builtin_fma(rest, g[e], Kg[e] * b[e]);
+      be = in ? __builtin_fma(ae, be, bb) : be;
+      al = in ? ae * al : al;
+    }
+    wave_affine_scan(al, be);
+    const double mi = __builtin_fma(al, m, be);  // the mean after the lane's intervals
+    double ml = wave_prev(mi, m);
+    double part = 0.0;
+#pragma unroll
+    for (int e = 0; e < KF_L; ++e) {
+      const bool in = tl + e < T;
+      const double mp = __builtin_fma(aK, ml, __builtin_fma(aKl, ml, g[e]));
+      const double v = b[e] - mp;
+      const double le = -0.5 * (log(2.0 * 3.14159265358979323846 * S[e]) + v * v * iS[e]);
+      ml = in ? __builtin_fma(Kg[e], v, mp) : ml;
+      part += in ? le : 0.0;
+      if (ell && in) ell[tl + e] = le;
+    }
+    tot = tot + wave_sum(part);
+    const int last = min(WAVE - 1, (T - 1 - t0) / KF_L);  // the pass's last lane with intervals
+    m = lane_value(ml, last);
+    V = lane_value(Vl, last);
+  }
+  return tot;
+}
+
+__global__ __launch_bounds__(WAVE) void k_kf_run_wave(KfArgs A, const double* __restrict__ theta,
+                                                      double* __restrict__ ll,
+                                                      double* __restrict__ ell) {
+  const int b = blockIdx.x;
+  double th[6];
+#pragma unroll
+  for (int p = 0; p < 6; ++p) th[p] = theta[(int64_t)b * 8 + p];
+  double m = th[4], V = th[5] * th[5];
+  const double tot = kf_wave(th, A.K, A.T, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V,
+                             ell + (int64_t)b * A.T);
+  if (threadIdx.x == 0) ll[b] = tot;
+}
+
+// The proposals' filters (k_kf_proposal), a wave each; i >= 2.
+__global__ __launch_bounds__(WAVE) void k_kf_proposal_wave(KfArgs A, Smc2Args S,
+                                                           const double* __restrict__ prop_dev,
+                                                           double* __restrict__ prop_l,
+                                                           double* __restrict__ prop_mV, int i) {
+  const int j = blockIdx.x;
+  if (!S.inside[j]) return;
+  double th[6];
+#pragma unroll
+  for (int p = 0; p < 6; ++p) th[p] = prop_dev[(int64_t)j * 8 + p];
+  double m = th[4], V = th[5] * th[5];
+  const double tot = kf_wave(th, A.K, i - 1, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V, nullptr);
+  if (threadIdx.x == 0) {
+    prop_l[j] = tot;
+    prop_mV[2 * j] = m;
+    prop_mV[2 * j + 1] = V;
+  }
+}
+
+// ---------------------------------------------------------------- a filter per lane
 __global__ void k_kf_run(KfArgs A, const double* __restrict__ theta, double* __restrict__ ll,
                          double* __restrict__ ell) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
@@ -141,6 +363,123 @@ __device__ __forceinline__ double kf_loglik(const KfArgs& A, const double* th) {
   return tot;
 }
 
+// One chain per wave through every iteration (k_kf_pmmh's steps and order of
+// operations).  Lane l works on parameter l mod 4, so the proposals'
+// distribution functions, logarithms and inverses of the four parameters are
+// evaluated at once; the current state's terms are kept from one iteration to
+// the next and follow an acceptance only.  The likelihood is kf_wave, with the
+// series staged in LDS when it fits.
+template <bool LDS>
+__global__ __launch_bounds__(WAVE) void k_kf_pmmh_wave(KfArgs A, pf_wk_mh H, double h,
+                                                       int32_t iters,
+                                                       const double* __restrict__ theta0,
+                                                       const double* __restrict__ prop,
+                                                       const double* __restrict__ alpha,
+                                                       double* __restrict__ theta_trace,
+                                                       double* __restrict__ ll_trace,
+                                                       int32_t* __restrict__ accepts,
+                                                       double* __restrict__ ll0) {
+  extern __shared__ double series[];
+  const int c = blockIdx.x, lane = threadIdx.x, k = lane & 3;
+  const int T = A.T, K = A.K;
+  if constexpr (LDS) {  // rows of T + 1: q_{tK+s} at [s][t], then y
+    for (int n = lane; n <= T * K; n += WAVE) {
+      const int t = n / K;
+      series[(n - t * K) * (T + 1) + t] = A.q[n];
+    }
+    double* ys = series + (int64_t)K * (T + 1);
+    for (int t = lane; t < T; t += WAVE) ys[t] = A.obs[t];
+    __syncthreads();
+  }
+  auto loglik = [&](const double* th) -> double {
+    double m = th[4], V = th[5] * th[5];
+    if constexpr (LDS)
+      return kf_wave(th, K, T, A.R, KfSeriesLds{series, series + (int64_t)K * (T + 1), T + 1}, m,
+                     V, nullptr);
+    else
+      return kf_wave(th, K, T, A.R, KfSeriesMem{A.q, A.obs, K}, m, V, nullptr);
+  };
+  // the sum over the parameters in their order
+  auto sum4 = [&](double v) -> double {
+    double r = 0.0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) r += lane_value(v, p);
+    return r;
+  };
+  auto params = [&](double v, double* th) {
+    double w[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) w[p] = lane_value(v, p);
+    wk_params(H, h, w, th);
+  };
+  auto prior_term = [&](double v) -> double {
+    const double lv = log(v);
+    if (k == 3) return -(H.ig_shape + 1.0) * lv - H.ig_scale / v;
+    const double sh = k == 0 ? H.prior_shape[0] : k == 1 ? H.prior_shape[1] : H.prior_shape[2];
+    const double sc = k == 0 ? H.prior_scale[0] : k == 1 ? H.prior_scale[1] : H.prior_scale[2];
+    return (sh - 1.0) * lv - v / sc;
+  };
+  // this lane's proposal sd (0: fixed); sigma^2 moves by its factor
+  const double sd = k == 0 ? H.step_sd[0] : k == 1 ? H.step_sd[1] : k == 2 ? H.step_sd[2] : 0.0;
+  const bool gauss = sd > 0.0, ig = k == 3 && H.ig_prop_factor > 0.0;
+  double th[8];
+  double x = theta0[(int64_t)c * 4 + k];
+  params(x, th);
+  double ll = loglik(th);
+  double lp = sum4(prior_term(x));
+  if (ll0 && lane == 0) ll0[c] = ll;
+  // Phi(-x/sd) and ln Phi(x/sd) of the current state
+  double p0 = gauss ? ncdf(-x / sd) : 0.0;
+  double lcx = gauss ? log(ncdf(x / sd)) : 0.0;
+  int32_t acc = 0;
+  double un = iters > 0 ? prop[(int64_t)c * 4 + k] : 0.5;
+  double an = iters > 0 ? alpha[c] : 1.0;
+  for (int32_t i = 0; i < iters; ++i) {
+    const int64_t row = (int64_t)i * A.B + c;
+    const double u = un, al = an;
+    if (i + 1 < iters) {  // the next iteration's numbers, on their way meanwhile
+      un = prop[(row + A.B) * 4 + k];
+      an = alpha[row + A.B];
+    }
+    double y = x, lq = 0.0, lcy = lcx;
+    bool ok = true;
+    if (gauss) {
+      const double pu = u <= 0.5 ? p0 + u * (1.0 - p0) : (1.0 - u) * (1.0 - p0);
+      const double zi = normcdfinv(pu);
+      const double z = u <= 0.5 ? zi : -zi;
+      y = x + sd * z;
+      ok = y > 0.0 && isfinite(y);
+      if (ok) {
+        lcy = log(ncdf(y / sd));
+        lq = lcx - lcy;
+      }
+    } else if (ig) {
+      y = H.ig_prop_factor * x / u;
+      ok = y > 0.0 && isfinite(y);
+      if (ok) {
+        const double r = y / x;
+        lq = (2.0 * H.ig_prop_shape + 1.0) * log(r) - H.ig_prop_factor * (r - 1.0 / r);
+      }
+    }
+    if (__ballot(!ok) == 0) {
+      params(y, th);
+      const double llp = loglik(th);
+      const double lpp = sum4(prior_term(y));
+      if (log(al) <= (llp - ll) + ((lpp - lp) + sum4(lq))) {
+        x = y;
+        ll = llp;
+        lp = lpp;
+        ++acc;
+        lcx = lcy;
+        if (gauss) p0 = ncdf(-x / sd);
+      }
+    }
+    if (lane < 4) theta_trace[row * 4 + k] = x;
+    if (lane == 0) ll_trace[row] = ll;
+  }
+  if (lane == 0) accepts[c] = acc;
+}
+
 // One chain per lane through every iteration (Alg. 3): truncated-Gaussian
 // proposals of R, C, Z by inversion on the accurate tail, the
 // Inverse-Gamma proposal of sigma^2 from the given Gamma variate, support
@@ -214,9 +553,32 @@ __global__ void __launch_bounds__(64) k_kf_pmmh(KfArgs A, pf_wk_mh H, double h, 
 
 static inline unsigned kf_blocks(int n) { return (unsigned)((n + 255) / 256); }
 
+// Which form runs B filters over T intervals of K substeps.  The
+// lane-per-filter form is bound by its chain: whatever B (up to 32,768 at
+// least) a chain iteration takes about 11 us for the proposals and 0.32 +
+// 0.033 K us per interval (K = 10: 13.0 us at T = 3, 23.4 at T = 20, 75 at
+// T = 100, 221 at T = 300; T = 100: 46 at K = 1, 109 at K = 20).  The
+// wave-per-filter form is bound by issue once its waves fill the SIMDs: per
+// chain and iteration about 2.4 ns, plus 1.5 + 0.08 K ns per pass of 128
+// intervals (T = 100, K = 10: 6.1 us at 512 chains, 41 at 8,192, 78 at
+// 16,384, 152 at 32,768; T = 300: 250 at 32,768).  A plain likelihood run has
+// no proposals, in either form.  The cheaper estimate wins: at T = 100 and
+// K = 10 the wave form up to 16,500 chains.
+static inline bool kf_wave_form(int B, int T, int K, bool chains) {
+  const double passes = (double)((T + WAVE * KF_L - 1) / (WAVE * KF_L));
+  const double wave_ns = B * ((chains ? 2.4 : 0.6) + passes * (1.5 + 0.08 * K));
+  const double lane_ns = (chains ? 11e3 : 0.0) + T * (320.0 + 33.0 * K);
+  return wave_ns <= lane_ns;
+}
+// LDS the chains' series may take (a block is one wave; 160 KB per CU)
+constexpr size_t KF_LDS_MAX = 64 * 1024;
+
 hipError_t launch_kf_run(const KfArgs& A, const double* theta, double* ll, double* ell,
                          hipStream_t s) {
-  hipLaunchKernelGGL(k_kf_run, kf_blocks(A.B), 256, 0, s, A, theta, ll, ell);
+  if (kf_wave_form(A.B, A.T, A.K, false))
+    hipLaunchKernelGGL(k_kf_run_wave, (unsigned)A.B, WAVE, 0, s, A, theta, ll, ell);
+  else
+    hipLaunchKernelGGL(k_kf_run, kf_blocks(A.B), 256, 0, s, A, theta, ll, ell);
   return hipGetLastError();
 }
 
@@ -227,8 +589,12 @@ hipError_t launch_kf_init(const Smc2Args& S, hipStream_t s) {
 
 hipError_t launch_kf_proposal(const KfArgs& A, const Smc2Args& S, const double* prop_dev,
                               double* prop_l, double* prop_mV, int i, hipStream_t s) {
-  hipLaunchKernelGGL(k_kf_proposal, kf_blocks(S.B), 256, 0, s, A, S, prop_dev, prop_l, prop_mV,
-                     i);
+  if (i >= 2 && kf_wave_form(S.B, i - 1, A.K, false))
+    hipLaunchKernelGGL(k_kf_proposal_wave, (unsigned)S.B, WAVE, 0, s, A, S, prop_dev, prop_l,
+                       prop_mV, i);
+  else
+    hipLaunchKernelGGL(k_kf_proposal, kf_blocks(S.B), 256, 0, s, A, S, prop_dev, prop_l, prop_mV,
+                       i);
   return hipGetLastError();
 }
 
@@ -244,8 +610,17 @@ hipError_t launch_kf_pmmh(const KfArgs& A, const pf_wk_mh& H, double h, int32_t 
                           const double* theta0, const double* prop, const double* alpha,
                           double* theta_trace, double* ll_trace, int32_t* accepts, double* ll0,
                           hipStream_t s) {
-  hipLaunchKernelGGL(k_kf_pmmh, (unsigned)((A.B + 63) / 64), 64, 0, s, A, H, h, iters, theta0,
-                     prop, alpha, theta_trace, ll_trace, accepts, ll0);
+  const size_t lds = 8 * ((size_t)A.K * ((size_t)A.T + 1) + (size_t)A.T);
+  const bool wave = kf_wave_form(A.B, A.T, A.K, true);
+  if (wave && lds <= KF_LDS_MAX)
+    hipLaunchKernelGGL(k_kf_pmmh_wave<true>, (unsigned)A.B, WAVE, lds, s, A, H, h, iters, theta0,
+                       prop, alpha, theta_trace, ll_trace, accepts, ll0);
+  else if (wave)
+    hipLaunchKernelGGL(k_kf_pmmh_wave<false>, (unsigned)A.B, WAVE, 0, s, A, H, h, iters, theta0,
+                       prop, alpha, theta_trace, ll_trace, accepts, ll0);
+  else
+    hipLaunchKernelGGL(k_kf_pmmh, (unsigned)((A.B + 63) / 64), 64, 0, s, A, H, h, iters, theta0,
+                       prop, alpha, theta_trace, ll_trace, accepts, ll0);
   return hipGetLastError();
 }
 
