@@ -228,7 +228,8 @@ typedef struct pf_wk_mh {
 
 /* B independent chains, one per filter slot of the windkessel handle h (its
  * flow series, observations, observation sd and h; its particles are
- * untouched), all iterations of a chain in one lane of one kernel on the
+ * untouched), all iterations of a chain in one wave (for very many chains,
+ * one lane) of one kernel on the
  * handle's stream (asynchronous).  The random numbers are inputs, device
  * arrays (FP64, 8-byte aligned, not overlapping the outputs):
  *   theta0 [B][4]       initial (R, C, Z, sigma^2), each > 0;

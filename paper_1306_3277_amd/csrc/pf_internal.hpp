@@ -140,6 +140,8 @@ constexpr int K4_NT = 256;  // tile-gather threads
 constexpr int K4_PER = 1;   // outputs per tile-gather lane
 constexpr int K4_TILE = K4_NT * K4_PER;  // outputs per tile (one owner each)
 static_assert(K4_TILE == K1_NT, "a propagation block names the ancestors of one tile");
+// particles a single workgroup steps or resamples on its own
+constexpr int SMALL_MAXN = 4096;
 constexpr int BATCH_NT = 256;
 constexpr int BATCH_MAXN = 8192;
 
@@ -156,7 +158,8 @@ hipError_t launch_propagate(int model, int d, int prec, void* xa, void* xb, void
 hipError_t launch_set_amode(FilterState* fs, int n, int32_t v, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_combine(const double* part, double* boff, const PlainArgs& a, hipStream_t s);
-hipError_t launch_lw_partials(const double* lw, double* part, const PlainArgs& a, hipStream_t s);
+hipError_t launch_lw_partials(const double* lw, double* part, int32_t* marks, double u,
+                              const PlainArgs& a, hipStream_t s);
 hipError_t launch_tile_anc(int32_t* marks, const int32_t* owner, const int32_t* jc, int32_t* anc,
                            const PlainArgs& a, hipStream_t s);
 hipError_t launch_scan_mark(const double* lw, const double* part, const double* boff,
@@ -181,6 +184,11 @@ hipError_t launch_multinomial_anc(const double* wcum, const int32_t* jc, int32_t
                                   const PlainArgs& a, hipStream_t s);
 hipError_t launch_simulate(int model, int d, double* out, const PlainArgs& a, double obs_sd,
                            hipStream_t s);
+// ---- small filters, one workgroup each (pf_small.hip) ----
+// The stateless resampler for n <= SMALL_MAXN weights in one launch; the
+// plain kernels' bits.
+hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* anc, double* stats,
+                                   hipStream_t s);
 // ---- batched (pf_batched.hip) ----
 hipError_t launch_batched_init(int model, int d, int prec, void* x, int32_t* anc,
                                const BatchArgs& a, hipStream_t s);

@@ -556,25 +556,36 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
   }
 }
 
-// Block partials (max, sum, sum of squares of exp(lw - max)) of caller-given
-// FP64 log-weights, the reduction K1 ends with; block 0 publishes the
-// interval index as K1 does.
+// The stateless resampler's first kernel: block partials (max, sum, sum of
+// squares of exp(lw - max)) of caller-given FP64 log-weights, the reduction
+// K1 ends with; each block also clears its marks, and block 0 starts the
+// scalars that the scan reads (u, interval 1).  Launch-bound calls: three
+// launches for the clearing and the scalars took as long as this kernel (5.7
+// us of 10^6 weights' 34, more than half of the kernel time of a small set's).
 __global__ __launch_bounds__(K1_NT) void k_lw_partials(const double* __restrict__ lw,
-                                                       double* __restrict__ part, PlainArgs A) {
+                                                       double* __restrict__ part,
+                                                       int32_t* __restrict__ marks, double u,
+                                                       PlainArgs A) {
   __shared__ double red[K1_NT / WAVE];
   const int64_t j = (int64_t)blockIdx.x * K1_NT + threadIdx.x;
-  const double l = j < A.N ? lw[A.off + j] : -INFINITY;
+  const double l = j < A.N ? lw[j] : -INFINITY;
+  if (j < A.N) marks[j] = -1;
   const double lc = (l == l) ? l : -INFINITY;  // a NaN log-weight counts as zero weight
   const double m = block_max<K1_NT>(lc, red);
   const double e = (m > -INFINITY && m < INFINITY) ? exp_nonpos(lc - m) : 0.0;
   const double s1 = block_sum<K1_NT>(e, red);
   const double s2 = block_sum<K1_NT>(e * e, red);
   if (threadIdx.x == 0) {
-    double* p = part + 3 * (A.boff0 + blockIdx.x);
+    double* p = part + 3 * (int64_t)blockIdx.x;
     p[0] = m;
     p[1] = s1;
     p[2] = s2;
-    if (blockIdx.x == 0) A.fs->tk = A.fs->t + 1;
+    if (blockIdx.x == 0) {
+      FilterState f = {};
+      f.u = u;
+      f.tk = 1;
+      *A.fs = f;
+    }
   }
 }
 
@@ -1106,8 +1117,9 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_lw_partials(const double* lw, double* part, const PlainArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_lw_partials, nblocks(a.N, K1_NT), K1_NT, 0, s, lw, part, a);
+hipError_t launch_lw_partials(const double* lw, double* part, int32_t* marks, double u,
+                              const PlainArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_lw_partials, nblocks(a.N, K1_NT), K1_NT, 0, s, lw, part, marks, u, a);
   return hipGetLastError();
 }
 
