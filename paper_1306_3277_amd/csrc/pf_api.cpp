@@ -59,8 +59,11 @@ struct Layout {
   int64_t nblk_total = 0;
   // byte offsets into the workspace
   size_t x_cur, x_tmp, lw, marks, anc, part, boff, owner, jc, fs, ell, ess, theta, obs, obs_pos,
-      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, total;
+      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, nz, rec, total;
   int32_t n_chunks = 0;
+  // plain windkessel filters small enough for one workgroup each: the
+  // intervals whose random numbers the workspace holds at a time (0: none)
+  int32_t small_n = 0;
 };
 
 pf_status validate(const pf_config* c) {
@@ -184,6 +187,28 @@ Layout make_layout(const pf_config* c) {
   L.kf_ll = take(8 * (size_t)c->B);
   L.kf_ell = take(8 * (size_t)c->B * c->T);
   L.wcum = take(c->layout == PF_LAYOUT_PLAIN ? 8 * (size_t)L.n_total : 8);
+  // Runs of windkessel filters of up to SMALL_MAXN particles draw their random
+// numbers ahead (K values per particle and interval, whole 256-particle
+  // blocks of the largest filter's number for each): as many intervals at a time
+  // as 64 MiB hold, at least one, in at most 256 MiB.  Measured against the
+  // multi-kernel path's graphs, us per interval, FP64 at K = 1, 10 and 20:
+  // 4.6, 5.5, 7.4 against 11.3, 14.3, 18.6 for 1,024 particles; 5.8, 7.3, 9.5
+  // against 11.2, 15.0, 18.9 for 2,048; 10.6, 13.5, 16.7 against 11.2, 14.8,
+  // 18.7 for 4,096 (FP32 9.1, 11.1, 13.1 against 11.0, 12.4, 13.8): there one
+  // CU's bandwidth for the numbers and its registers run out.  Several
+  // filters run side by side where the other path takes them in turn.
+  if (c->layout == PF_LAYOUT_PLAIN && c->model == PF_MODEL_WK && c->K <= pfk::SMALL_MAXK &&
+      c->B <= 65535 &&
+      *std::max_element(c->n_particles, c->n_particles + c->B) <= pfk::SMALL_MAXN) {
+    const int64_t nb = *std::max_element(L.nblk.begin(), L.nblk.end());
+    const size_t one = sx * (size_t)c->K * (size_t)(nb * pfk::K1_NT) * (size_t)c->B;
+    if (one <= ((size_t)256 << 20)) {
+      const size_t most = std::max<size_t>(1, ((size_t)64 << 20) / one);
+      L.small_n = (int32_t)std::min<size_t>({most, (size_t)c->T, (size_t)1024});
+      L.nz = take(one * (size_t)L.small_n);
+      L.rec = take(8 * (size_t)c->B * (size_t)L.small_n * ((size_t)c->K + 3));
+    }
+  }
   L.total = p;
   return L;
 }
@@ -215,6 +240,7 @@ struct pf_handle {
   uint32_t iter = 0;
   bool resampled_once = false;
   bool stepped_once = false;
+  bool marks_pending = false;  // plain layout: the pending ancestors may be marks
   std::vector<int64_t> np;
   std::vector<double> theta_host;  // [B][n_theta]
   // batched layout tuning: workgroup size of the per-filter collective, and
@@ -430,6 +456,7 @@ pf_status do_init(pf_handle* H, hipStream_t s) {
   if (st) return st;
   H->t = 0;
   H->phase = 0;
+  H->marks_pending = false;
   return PF_OK;
 }
 
@@ -531,6 +558,7 @@ pf_status enqueue_batched(pf_handle* H, hipStream_t s, int n) {
 pf_status enqueue_step(pf_handle* H, hipStream_t s) {
   const pf_config& c = H->cfg;
   if (c.layout == PF_LAYOUT_BATCHED) return enqueue_batched(H, s, 1);
+  H->marks_pending = true;
   for (int b = 0; b < c.B; ++b) {
     PlainArgs a = plain_args(H, b);
     hipEvent_t e0{};
@@ -632,6 +660,27 @@ pf_status enqueue_resample(pf_handle* H, hipStream_t s, const double* u) {
       HIP_TRY(pfk::launch_record_plain(c.precision, H->ws + H->L.x_cur, H->ws + H->L.x_tmp,
                                        H->at<int32_t>(H->L.anc), hist_args(H), a.off, a.N, a.fs,
                                        s));
+  }
+  return PF_OK;
+}
+
+// n intervals of the plain layout's small windkessel filters, each filter in
+// one workgroup.
+pf_status enqueue_small(pf_handle* H, hipStream_t s, int n) {
+  const pf_config& c = H->cfg;
+  if (H->marks_pending)
+    for (int b = 0; b < c.B; ++b)
+      if (pf_status st = plain_anc_out(H, b, s)) return st;
+  H->marks_pending = false;
+  const PlainArgs a = plain_args(H, 0);
+  const int max_n = (int)*std::max_element(H->np.begin(), H->np.end());
+  for (int left = n; left > 0;) {
+    const int m = std::min(left, (int)H->L.small_n);
+    HIP_TRY(pfk::launch_small_run(c.precision, c.B, max_n, H->ws + H->L.x_cur,
+                                  H->ws + H->L.x_tmp, H->at<double>(H->L.lw),
+                                  H->at<int32_t>(H->L.anc), a, H->at<int64_t>(H->L.b_off),
+                                  H->ws + H->L.nz, H->at<double>(H->L.rec), m, s));
+    left -= m;
   }
   return PF_OK;
 }
@@ -1070,6 +1119,11 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
   if (H->t + n_steps > H->cfg.T)
     return fail(PF_E_STATE, "%d steps from t = %d exceed T = %d", n_steps, H->t, H->cfg.T);
   if (n_steps == 0) return PF_OK;
+  if (H->L.small_n > 0 && !H->hist) {
+    if ((st = enqueue_small(H, H->stream, n_steps))) return st;
+    H->t += n_steps;
+    return PF_OK;
+  }
   hipStream_t ls;
   if ((st = launch_stream(H, &ls))) return st;
   if (H->eager_replay && H->cfg.layout == PF_LAYOUT_BATCHED) {
@@ -1078,6 +1132,7 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
     return PF_OK;
   }
   if ((st = ensure_graphs(H))) return st;
+  if (H->cfg.layout == PF_LAYOUT_PLAIN) H->marks_pending = true;
   const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
   const int G = batched ? H->groups : 1;
   // group g's graphs go on its own stream (the caller's with one group)

@@ -142,6 +142,7 @@ constexpr int K4_TILE = K4_NT * K4_PER;  // outputs per tile (one owner each)
 static_assert(K4_TILE == K1_NT, "a propagation block names the ancestors of one tile");
 // particles a single workgroup steps or resamples on its own
 constexpr int SMALL_MAXN = 4096;
+constexpr int SMALL_MAXK = 253;  // substeps per interval such a run takes
 constexpr int BATCH_NT = 256;
 constexpr int BATCH_MAXN = 8192;
 
@@ -189,6 +190,15 @@ hipError_t launch_simulate(int model, int d, double* out, const PlainArgs& a, do
 // plain kernels' bits.
 hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* anc, double* stats,
                                    hipStream_t s);
+// n intervals of B windkessel filters of at most max_n <= SMALL_MAXN
+// particles (a: the first filter's arguments; off: [B + 1] first particles),
+// a workgroup each, after a launch that draws their random numbers into nz
+// (n K B ceil(max_n / 256) 256 values in the state's precision) and rec (B n (K + 3)
+// doubles).  The ancestors pending must not be marks; they are the array
+// afterwards.  Refused on a capturing stream.
+hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, double* lw,
+                            int32_t* anc, const PlainArgs& a, const int64_t* off, void* nz,
+                            double* rec, int n, hipStream_t s);
 // ---- batched (pf_batched.hip) ----
 hipError_t launch_batched_init(int model, int d, int prec, void* x, int32_t* anc,
                                const BatchArgs& a, hipStream_t s);

@@ -59,7 +59,9 @@ __device__ __forceinline__ double lane_val(double v, int lane) {
 // past N are ignored): likelihood sums, the resampling decision and, for
 // every output of the rows, its ancestor.  `between` runs after the first
 // barrier, while the arithmetic hides what it starts.
-template <int NQ, class Between>
+// SYS: systematic resampling (any scheme otherwise: a kernel with all of
+// them spends most of its registers on their constants).
+template <int NQ, bool SYS, class Between>
 __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const double (&l)[ROWS],
                                                      int N, double u, const ResampleArgs& rs,
                                                      Key key, int32_t t, uint32_t b,
@@ -75,14 +77,14 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
     const int j = base + r * WAVE;
     lc[r] = (j < N && l[r] == l[r]) ? l[r] : -INFINITY;
     m = fmax(m, lc[r]);
-    X.lw[j] = l[r];
+    X.lw[j] = lc[r];  // a NaN is a weight of 0 to every scheme
   }
   m = wave_max(m);
   {
-    const bool fin = m > -INFINITY && m < INFINITY;
+    // (without a finite maximum lc - m is -inf or NaN and the weight 0)
     double e[ROWS], s1 = 0.0, s2 = 0.0;
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) e[r] = fin ? exp_nonpos(lc[r] - m) : 0.0;
+    for (int r = 0; r < ROWS; ++r) e[r] = exp_nonpos(lc[r] - m);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) s1 += wave_sum(e[r]);
 #pragma unroll
@@ -125,35 +127,31 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
   const double ess = o.pos ? (S * S) / o.S2 : 0.0;
   o.carry = o.pos && !(ess < rs.ess_frac * (double)N);
   const bool draws = o.pos && !o.carry;
-  const bool marked = rs.scheme == RS_SYSTEMATIC || rs.scheme == RS_STRATIFIED;
+  const bool marked = SYS || rs.scheme == RS_SYSTEMATIC || rs.scheme == RS_STRATIFIED;
   if (!draws) {  // every particle is its own offspring
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) anc[r] = base + r * WAVE;
     __syncthreads();  // the next collective's stores come after these reads
     return o;
   }
-  if (rs.scheme == RS_METROPOLIS || rs.scheme == RS_REJECTION) {
+  if (!SYS && (rs.scheme == RS_METROPOLIS || rs.scheme == RS_REJECTION)) {
 #pragma unroll 1
     for (int r = 0; r < ROWS; ++r) {
       const int k = base + r * WAVE;
       int j = k;
       if (k < N && rs.scheme == RS_METROPOLIS) {
-        auto read = [&](int i) -> double {
-          const double x = X.lw[i];
-          return x == x ? x : -INFINITY;
-        };
-        double lj = read(j);
+        double lj = X.lw[j];
         for (int s = 1; s <= rs.steps; s += 2) {
           const uint4 q = metro_draw(key, t, b, iter, k, s);
           int jp = metro_index(q.x, N);
-          double lp = read(jp);
+          double lp = X.lw[jp];
           if (ln_f64(u01_f64(q.y)) <= lp - lj) {
             j = jp;
             lj = lp;
           }
           if (s + 1 <= rs.steps) {
             jp = metro_index(q.z, N);
-            lp = read(jp);
+            lp = X.lw[jp];
             if (ln_f64(u01_f64(q.w)) <= lp - lj) {
               j = jp;
               lj = lp;
@@ -175,9 +173,8 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
   int cand = -1;
 #pragma unroll
   for (int e = 0; e < ROWS; ++e) {
-    const double lv = X.lw[j0 + e];
-    const double we = (j0 + e < N && lv == lv) ? exp_nonpos(lv - M) : 0.0;
-    if (we > 0.0) cand = j0 + e;
+    const double we = exp_nonpos(X.lw[j0 + e] - M);  // 0 past N
+    cand = we > 0.0 ? j0 + e : cand;
     run += we;
     loc[e] = run;
   }
@@ -208,28 +205,52 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
   for (int e = 0; e < ROWS; ++e) W[e] = fmin(fmax(V[e], vprev), hi_off);
   if (marked) {
     const double invS = 1.0 / S;
-    const bool strat = rs.scheme == RS_STRATIFIED;
+    const bool strat = !SYS && rs.scheme == RS_STRATIFIED;
     auto count = [&](double v) -> int32_t {
       return strat ? stratum_count_strat(v, S, invS, N, key, t, b, iter)
                    : stratum_count(v, S, invS, u, N);
     };
-    // the count before the lane's first particle is the previous lane's last
-    // count, of the same clamped value
-    int cprev = j0 < N ? count(fmin(vprev, hi_off)) : 0;
+    // c[e + 1]: the count of the lane's particle e; c[0]: the one before its
+    // first, the previous lane's last, of the same clamped value
+    const double v[ROWS + 1] = {fmin(vprev, hi_off), W[0], W[1], W[2], W[3]};
+    int32_t c[ROWS + 1];
+    if (strat) {
+#pragma unroll
+      for (int e = 0; e <= ROWS; ++e) c[e] = count(v[e]);
+    } else {
+      // stratum_count's estimates side by side; it decides the few that lie
+      // near an integer
+      const double Nd = (double)N, thr = Nd * 0x1p-44;
+      bool near = false;
+#pragma unroll
+      for (int e = 0; e <= ROWS; ++e) {
+        const double xv = (Nd * v[e]) * invS - u;
+        const double cl = __builtin_ceil(xv);
+        c[e] = (int32_t)fmin(fmax(cl, 0.0), Nd);
+        const double fr = xv - __builtin_floor(xv);
+        near = near || !(fr > thr && fr < 1.0 - thr);
+      }
+      if (near) {
+#pragma unroll 1
+        for (int e = 0; e <= ROWS; ++e) {
+          const int32_t x = stratum_count(
+              e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : e == 3 ? v[3] : v[4], S, invS, u, N);
+#pragma unroll
+          for (int q = 0; q <= ROWS; ++q) c[q] = q == e ? x : c[q];
+        }
+      }
+    }
 #pragma unroll
     for (int e = 0; e < ROWS; ++e) {
       const int j = j0 + e;
-      if (j < N) {
-        const int c = count(W[e]);
-        if (cprev < c) X.marks[cprev] = j;
-        cprev = c;
-        if (j == N - 1) {
-          X.cn1 = c;
-        } else if (e == ROWS - 1 && (j & (K3_SPAN - 1)) == K3_SPAN - 1) {
-          // strata below the next span's first count belong to its first particle
-          if (c < count(hi_off)) X.marks[c] = j + 1;
-        }
-      }
+      if (j < N && c[e] < c[e + 1]) X.marks[c[e]] = j;
+    }
+    const int jl = j0 + ROWS - 1;
+    if (j0 < N && jl >= N - 1) {  // the lane of the last particle
+      X.cn1 = N - 1 == j0 ? c[1] : N - 1 == j0 + 1 ? c[2] : N - 1 == j0 + 2 ? c[3] : c[4];
+    } else if (jl < N && (jl & (K3_SPAN - 1)) == K3_SPAN - 1) {
+      // strata below the next span's first count belong to its first particle
+      if (c[ROWS] < count(hi_off)) X.marks[c[ROWS]] = jl + 1;
     }
   } else {
 #pragma unroll
@@ -312,7 +333,7 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_systematic(const double* __
   }
   int32_t a[ROWS];
   const ResampleArgs rs{RS_SYSTEMATIC, 0, INFINITY};
-  const SmallOut o = small_collective<NQ>(X, l, N, u, rs, Key{0, 0}, 0, 0, 0, nullptr, a, [] {});
+  const SmallOut o = small_collective<NQ, true>(X, l, N, u, rs, Key{0, 0}, 0, 0, 0, nullptr, a, [] {});
 #pragma unroll
   for (int r = 0; r < ROWS; ++r)
     if (base + r * WAVE < N) anc[base + r * WAVE] = a[r];
@@ -332,6 +353,307 @@ hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* a
     hipLaunchKernelGGL(k_small_systematic<2>, 1, 2 * K3_NT, 0, s, lw, n, u, anc, stats);
   else
     hipLaunchKernelGGL(k_small_systematic<4>, 1, 4 * K3_NT, 0, s, lw, n, u, anc, stats);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- windkessel runs
+// One interval's record: the resampling uniform, Z q(t), y(t), then c q of
+// its K substeps (FP32 forms: the FP32 product), each as the multi-kernel
+// path forms it.
+constexpr int REC_HEAD = 3;
+
+// The random numbers of n intervals from every filter's counter on: sigma_p z
+// (FP64; the FP32 forms keep z, which enters a fused multiply-add), and the
+// intervals' records.  Every filter has fb whole 256-particle blocks of
+// numbers; within a block a lane's four rows lie together:
+// nz[(((i K + s) B + b) fb + block) 256 + 4 lane + row].  One lane per
+// particle and interval; bound by the normals' FP64 instructions (1,024
+// particles, 100 intervals of K = 10: NOISEUS us for all of them).
+template <typename Real>
+__global__ __launch_bounds__(K1_NT) void k_small_noise(PlainArgs A,
+                                                       const int64_t* __restrict__ offs,
+                                                       Real* __restrict__ nz,
+                                                       double* __restrict__ rec, int n) {
+  const int i = blockIdx.y, b = blockIdx.z;
+  const int N = (int)(offs[b + 1] - offs[b]);
+  const FilterState* fs = A.fs + b;
+  const uint32_t iter = fs->iter;
+  const int t = fs->t + 1 + i;
+  const int n0 = (t - 1) * A.K;
+  const double* th = A.theta + (size_t)b * 8;
+  const Key key{A.key.lo, A.key.hi};
+  if (blockIdx.x == 0) {
+    double* o = rec + ((int64_t)b * n + i) * (A.K + REC_HEAD);
+    for (int s = threadIdx.x; s < A.K + REC_HEAD; s += K1_NT) {
+      double v;
+      if (s == 0)
+        v = u01_f64(draw(key, TAG_RESAMPLE, 0, iter, 0, (uint32_t)t, (uint32_t)b).x);
+      else if (s == 1)
+        v = th[2] * A.q[(int64_t)t * A.K];
+      else if (s == 2)
+        v = A.obs[t - 1];
+      else if constexpr (sizeof(Real) == 8)
+        v = th[1] * A.q[n0 + s - REC_HEAD];
+      else
+        v = (double)((float)th[1] * (float)A.q[n0 + s - REC_HEAD]);
+      o[s] = v;
+    }
+  }
+  if ((int)blockIdx.x * K1_NT >= N) return;
+  // thread 4 lane + row of the block
+  const int j = blockIdx.x * K1_NT + (threadIdx.x & 3) * WAVE + (threadIdx.x >> 2);
+  const int64_t step = (int64_t)gridDim.z * gridDim.x * K1_NT;
+  Real* o = nz + (int64_t)i * A.K * step + ((int64_t)b * gridDim.x + blockIdx.x) * K1_NT +
+            threadIdx.x;
+  for (int s = 1; s <= A.K; ++s, o += step) {
+    const uint4 w = draw(key, TAG_NOISE, 0, iter, (uint32_t)j, (uint32_t)(n0 + s), (uint32_t)b);
+    if constexpr (sizeof(Real) == 8) {
+      double z0, z1;
+      bm_pair_f64(w.x, w.y, z0, z1);
+      *o = th[3] * z0;
+    } else {
+      float z0, z1;
+      bm_pair_f32(w.x, w.y, z0, z1);
+      *o = z0;
+    }
+  }
+}
+
+// n intervals of one filter per workgroup, from the ancestors pending as the
+// identity or the array; leaves what the multi-kernel path leaves, with the
+// ancestors in the array.  Bound by the chain of an interval: the substeps'
+// dependent adds, two exponentials, five barriers.  The next interval's
+// numbers are loaded during the collective, and the likelihood's logarithms
+// wait for 64 intervals to be taken by 64 lanes.  1,024 particles, K = 10,
+// FP64: RUNUS us an interval (17.6 on the multi-kernel path's graphs).
+template <typename Real, bool ACC, int NQ, bool SYS>
+__global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
+                                                         Real* __restrict__ xb,
+                                                         double* __restrict__ lw,
+                                                         int32_t* __restrict__ anc_all,
+                                                         PlainArgs A,
+                                                         const int64_t* __restrict__ offs,
+                                                         const Real* __restrict__ nz,
+                                                         const double* __restrict__ rec, int n,
+                                                         int fb) {
+  constexpr int NT = K3_NT * NQ;
+  // substeps loaded ahead, as many as the registers leave room for
+  constexpr int AHEAD = NQ == 4 ? 4 : 12;
+  typedef Real Row4 __attribute__((ext_vector_type(ROWS)));
+  constexpr int RING = WAVE;
+  __shared__ SmallLds<NQ> X;
+  __shared__ Real xs[2][NQ * K3_SPAN];
+  __shared__ double recL[2][SMALL_MAXK + REC_HEAD];
+  __shared__ double rM[RING], rS[RING], rS2[RING];
+  __shared__ int32_t rflag[RING];  // 1: a positive weight, 2: weights kept
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int base = wave * K1_NT + lane;
+  const int64_t off = offs[b];
+  const int N = (int)(offs[b + 1] - off), K = A.K;
+  FilterState* fs = A.fs + b;
+  const int t0 = fs->t;
+  const uint32_t iter = fs->iter;
+  const int amode = fs->amode;
+  bool carry = fs->carry != 0;
+  const double* th = A.theta + (size_t)b * 8;
+  const Key key{A.key.lo, A.key.hi};
+  const double a64 = th[0];
+  const float am1 = (float)(th[0] - 1.0), sp = (float)th[3];
+  // this wave's block of numbers (a wave past the filter's blocks reads the last)
+  const int64_t step = (int64_t)gridDim.x * fb * K1_NT;
+  nz += ((int64_t)b * fb + min(wave, fb - 1)) * K1_NT;
+  rec += (int64_t)b * n * (K + REC_HEAD);
+  double* ell_tr = A.ell_tr + (int64_t)b * A.T;
+  double* ess_tr = A.ess_tr + (int64_t)b * A.T;
+  uint32_t jr[ROWS];
+  Real p[ROWS];
+  double l[ROWS];
+  int32_t anc[ROWS];
+  const Real* x0 = (t0 & 1) ? xb : xa;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    jr[r] = min(base + r * WAVE, N - 1);
+    X.marks[base + r * WAVE] = -1;
+    const int a = amode == AMODE_ARRAY ? anc_all[off + jr[r]] : (int)jr[r];
+    p[r] = x0[off + a];
+    l[r] = carry ? lw[off + jr[r]] : 0.0;
+    anc[r] = base + r * WAVE;
+  }
+  Row4 zn[AHEAD];
+  auto load_ahead = [&](int i) {
+    const Real* zi = nz + (int64_t)i * K * step;
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+      if (s < K) zn[s] = *(const Row4*)(zi + s * step + ROWS * lane);
+  };
+  load_ahead(0);
+  if (tid < K + REC_HEAD) recL[0][tid] = rec[tid];
+  __syncthreads();
+  // the running scalars, held by wave 0
+  double loglik = fs->loglik, lprev = fs->lprev, ell_last = 0.0, ess_last = 0.0;
+  bool carry_before = carry, none = false;
+  SmallOut o{};
+  for (int i = 0; i < n; ++i) {
+    const int par = i & 1;
+    const double* R = recL[par];
+    const bool more = i + 1 < n;
+    double rn = 0.0;
+    if (more && tid < K + REC_HEAD) rn = rec[(int64_t)(i + 1) * (K + REC_HEAD) + tid];
+    double pa[ROWS];  // the accurate form carries the pressure in FP64
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) pa[r] = (double)p[r];
+    auto substep = [&](double cq, const Row4& z) {
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) {
+        if constexpr (sizeof(Real) == 8)
+          p[r] = (a64 * p[r] + cq) + z[r];
+        else if constexpr (ACC)
+          pa[r] = pa[r] + (double)fmaf(sp, z[r], fmaf(am1, (float)pa[r], (float)cq));
+        else
+          p[r] = p[r] + fmaf(sp, z[r], fmaf(am1, p[r], (float)cq));
+      }
+    };
+    {
+      const double head = R[min(lane, SMALL_MAXK - 1) + REC_HEAD];  // c q of substep `lane`
+#pragma unroll
+      for (int s = 0; s < AHEAD; ++s)
+        if (s < K) substep(lane_val(head, s), zn[s]);
+      const Real* zi = nz + (int64_t)i * K * step + ROWS * lane;
+      for (int s0 = AHEAD; s0 < K; s0 += 4) {
+        Row4 z[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) z[s] = *(const Row4*)(zi + min(s0 + s, K - 1) * step);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          if (s0 + s < K) substep(R[REC_HEAD + s0 + s], z[s]);
+      }
+    }
+    const double u = R[0], zq = R[1], y = R[2];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      if constexpr (ACC) p[r] = (Real)pa[r];
+      else pa[r] = (double)p[r];
+      const double e = (y - (pa[r] + zq)) * A.inv_sd;
+      const double ln = -0.5 * (e * e) + A.lw_cst;
+      l[r] = carry ? l[r] + ln : ln;
+      xs[par][base + r * WAVE] = p[r];
+    }
+    o = small_collective<NQ, SYS>(X, l, N, u, A.rs, key, t0 + 1 + i, (uint32_t)b, iter, &fs->pad, anc,
+                             [&] {
+                               if (tid < K + REC_HEAD) recL[par ^ 1][tid] = rn;
+                               if (more) load_ahead(i + 1);
+                             });
+    carry = o.carry;
+    if (more)
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r)
+        if (base + r * WAVE < N) p[r] = xs[par][anc[r]];
+    // the bookkeeping of up to 64 intervals at once, by wave 0
+    if (tid < WAVE) {
+      const int k = i & (RING - 1);
+      if (tid == 0) {
+        rM[k] = o.M;
+        rS[k] = o.S;
+        rS2[k] = o.S2;
+        rflag[k] = (o.pos ? 1 : 0) | (o.carry ? 2 : 0);
+      }
+      if (k == RING - 1 || !more) {
+        __builtin_amdgcn_wave_barrier();
+        const bool in = lane <= k;
+        const int fl = in ? rflag[lane] : 0;
+        const double S = in ? rS[lane] : 1.0;
+        const bool pos = fl & 1;
+        const double L = pos ? rM[in ? lane : 0] + log(S) : 0.0;
+        // the factor's normaliser: ln N after a resampling, else the carried
+        // weights' ln sum exp
+        const double Lp = wave_prev(L, lprev);
+        const int kept = dpp_move_i<0x138, 0xf>(fl, carry_before ? 2 : 0) & 2;
+        const double ell = pos ? L - (kept ? Lp : log((double)N)) : -INFINITY;
+        const double ess = pos ? (S * S) / rS2[in ? lane : 0] : 0.0;
+        if (in) {
+          ell_tr[t0 + i - k + lane] = ell;
+          ess_tr[t0 + i - k + lane] = ess;
+        }
+        none = none || __ballot(in && !pos) != 0;
+        for (int q = 0; q <= k; ++q) loglik = loglik + lane_val(ell, q);
+        lprev = lane_val(L, k);
+        ell_last = lane_val(ell, k);
+        ess_last = lane_val(ess, k);
+        carry_before = o.carry;
+      }
+    }
+  }
+  const int t = t0 + n;
+  Real* xn = (t & 1) ? xb : xa;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const int j = base + r * WAVE;
+    if (j < N) {
+      xn[off + j] = p[r];
+      lw[off + j] = l[r];
+      anc_all[off + j] = anc[r];
+    }
+  }
+  if (tid == 0) {
+    fs->loglik = loglik;
+    fs->M = o.finite ? o.M : -INFINITY;
+    fs->S = o.S;
+    fs->u = recL[(n - 1) & 1][0];
+    fs->ell = ell_last;
+    fs->ess = ess_last;
+    fs->t = t;
+    if (none) fs->status = 4;
+    fs->lprev = lprev;
+    fs->carry = o.carry;
+    fs->tk = t;
+    fs->cn1 = 0;
+    fs->amode = AMODE_ARRAY;
+  }
+}
+
+template <typename Real, bool ACC>
+static void small_run(int nq, int fb, int B, void* xa, void* xb, double* lw, int32_t* anc,
+                      const PlainArgs& a, const int64_t* off, const void* nz, const double* rec,
+                      int n, hipStream_t s) {
+#define PF_SMALL(Q, SYS)                                                                       \
+  hipLaunchKernelGGL((k_small_run<Real, ACC, Q, SYS>), (unsigned)B, K3_NT* Q, 0, s, (Real*)xa, \
+                     (Real*)xb, lw, anc, a, off, (const Real*)nz, rec, n, fb)
+  const bool sys = a.rs.scheme == RS_SYSTEMATIC;
+  if (nq == 1) {
+    if (sys) PF_SMALL(1, true);
+    else PF_SMALL(1, false);
+  } else if (nq == 2) {
+    if (sys) PF_SMALL(2, true);
+    else PF_SMALL(2, false);
+  } else {
+    if (sys) PF_SMALL(4, true);
+    else PF_SMALL(4, false);
+  }
+#undef PF_SMALL
+}
+
+hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, double* lw,
+                            int32_t* anc, const PlainArgs& a, const int64_t* off, void* nz,
+                            double* rec, int n, hipStream_t s) {
+  if (max_n < 1 || max_n > SMALL_MAXN || a.K > SMALL_MAXK || n < 1 || B < 1 || B > 65535 ||
+      n > 65535)
+    return hipErrorInvalidValue;
+  // (as a replayed graph of the multi-kernel path would be, a call under the
+  // caller's own capture is refused: its replays would run past T)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s, &cap);
+  if (e != hipSuccess) return e;
+  if (cap != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
+  const dim3 g((unsigned)((max_n + K1_NT - 1) / K1_NT), (unsigned)n, (unsigned)B);
+  if (prec == 0)
+    hipLaunchKernelGGL(k_small_noise<double>, g, K1_NT, 0, s, a, off, (double*)nz, rec, n);
+  else
+    hipLaunchKernelGGL(k_small_noise<float>, g, K1_NT, 0, s, a, off, (float*)nz, rec, n);
+  const int nq = max_n <= K3_SPAN ? 1 : max_n <= 2 * K3_SPAN ? 2 : 4;
+  if (prec == 0) small_run<double, false>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
+  else if (prec == 1) small_run<float, false>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
+  else small_run<float, true>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
   return hipGetLastError();
 }
 

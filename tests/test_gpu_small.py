@@ -20,3 +20,60 @@ def test_systematic_small_sizes(env, n):  # noqa: F811
         for u in (0.0, float(rng.random()), 1.0 - 2.0 ** -40):
             a, stats = run(env, lw, u)
             check(lw, u, a, stats)
+
+
+SCHEMES = {"systematic": (0, 0, float("inf")), "stratified": (1, 0, float("inf")),
+           "multinomial": (3, 0, float("inf")), "metropolis": (2, 5, float("inf")),
+           "ess": (0, 0, 0.5)}
+
+
+def _outputs(f):
+    ll, ess, t = f.loglik(allow_numeric=True)
+    return [f.logweights(), f.ancestors(), f.get_state(), ll, ess, np.array([t]), *f.trace()]
+
+
+@pytest.mark.parametrize("n,K", [(1, 1), (64, 3), (65, 2), (256, 12), (257, 13), (1000, 10), (1024, 1),
+                                 (1025, 5), (2048, 14), (2049, 2), (4095, 3), (4096, 17)])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_small_run_equals_eager_steps(env, n, K, precision):  # noqa: F811
+    """A windkessel filter's run in one launch has the bits of the eager
+    steps' kernels, whatever comes before and after it."""
+    _, pfm = env
+    import workloads as W
+    T = 9
+    pb = W.windkessel(N=n, T=T, K=K, seed=n + K)
+    pb = pb.with_obs(90.0 + 5.0 * np.random.default_rng(n).standard_normal((T, 1)))
+    for name, (scheme, steps, frac) in SCHEMES.items():
+        f, g = (pfm.Filter(pb, precision=precision) for _ in range(2))
+        for h in (f, g):
+            h.set_resampler(scheme, steps, frac)
+        f.advance(T)
+        g.graph_run(4)
+        g.advance(2)
+        g.graph_run(3)
+        for a, b in zip(_outputs(f), _outputs(g)):
+            np.testing.assert_array_equal(a, b, err_msg=name)
+        f.close()
+        g.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_small_run_of_uneven_filters_and_lost_weights(env, precision):  # noqa: F811
+    _, pfm = env
+    import dataclasses
+
+    import workloads as W
+    T = 70  # more than the 64 intervals whose likelihoods are formed at once
+    base = W.windkessel(N=1, T=T, K=2, B=4)
+    obs = 90.0 + 4.0 * np.random.default_rng(2).standard_normal((T, 1))
+    obs[66] = 1e200  # no particle explains it: every weight 0
+    pb = dataclasses.replace(base.with_obs(obs),
+                             n_particles=np.array([5, 1500, 256, 3000], dtype=np.int64))
+    f, g = (pfm.Filter(pb, precision=precision) for _ in range(2))
+    f.advance(T)
+    g.graph_run(T)
+    for a, b in zip(_outputs(f), _outputs(g)):
+        np.testing.assert_array_equal(a, b)
+    assert np.all(np.isneginf(g.loglik(allow_numeric=True)[0]))
+    f.close()
+    g.close()
