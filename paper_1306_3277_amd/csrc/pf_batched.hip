@@ -237,6 +237,38 @@ __device__ __forceinline__ void lane_weights(const double* stage, int N, double 
   }
 }
 
+// A lane's counts over its run of P particles, four side by side (more would
+// hold more registers than the propagation running beside it can spare), the
+// count before its first particle and the count of the whole filter.
+// cum(e): particle e's cumulative weight.
+template <int MAXP, class Cum>
+__device__ __forceinline__ void lane_counts(int P, int i0, int i1, double vprev, double S,
+                                            double invS, double u, int N, Cum cum,
+                                            int32_t (&cnt)[MAXP], int32_t& before,
+                                            int32_t& total) {
+  constexpr int G = MAXP < 4 ? MAXP : 4;
+  const int n = i1 - i0;
+  {
+    const double W[2] = {S, vprev};
+    int32_t c[2];
+    stratum_counts(W, S, invS, u, N, n > 0 ? 2 : 1, c);
+    total = c[0];
+    before = c[1];
+  }
+#pragma unroll
+  for (int g = 0; g < MAXP; g += G) {
+    if (g < P) {
+      double W[G];
+      int32_t c[G];
+#pragma unroll
+      for (int e = 0; e < G; ++e) W[e] = cum(g + e);
+      stratum_counts(W, S, invS, u, N, n - g, c);
+#pragma unroll
+      for (int e = 0; e < G; ++e) cnt[g + e] = c[e];
+    }
+  }
+}
+
 // MAXP bounds the particles per lane: the launcher picks the smallest of
 // BATCH_MAXN / NT, half and a quarter of it that covers the group's largest
 // filter, so the unrolled per-lane phases do no work for absent particles.
@@ -271,6 +303,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
   const double lprev0 = fs->lprev;
   const int carry0 = fs->carry;
   const uint32_t iter = fs->iter;
+  // the likelihood factor's normaliser (thread 0): ln N after a resampling,
+  // else the carried weights' ln sum exp
+  double lprev = 0.0;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   const bool resample_only = A.mode != 0;
   const int t = resample_only ? fs->t : fs->t + 1;
@@ -287,11 +322,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 #pragma unroll
     for (int r = 0; r < MAXP; ++r) v[r] = lw[off + min((int)threadIdx.x + r * NT, N - 1)];
     // the resampling uniform, drawn while the loads are in flight and
-    // published with the first exchange
-    if (threadIdx.x == 0)
+    // published with the first exchange; the likelihood's ln N with it
+    if (threadIdx.x == 0) {
       bc = resample_only ? A.u_override[f]
                          : u01_f64(draw(bkey(A.key), TAG_RESAMPLE, 0, iter, 0, (uint32_t)t,
                                         (uint32_t)f).x);
+      lprev = carry0 ? lprev0 : log((double)N);
+    }
 #pragma unroll
     for (int r = 0; r < MAXP; ++r) {
       const int i = (int)threadIdx.x + r * NT;
@@ -372,18 +409,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
   // weights, or has none positive, gives every particle one offspring:
   // itself
   const bool ok = finite && S > 0.0;
-  const double ess = ok ? (S * S) / S2 : 0.0;
-  const int carry = (!resample_only && ok) ? !(ess < A.rs.ess_frac * (double)N) : 0;
+  int carry = 0;
+  if (!resample_only && ok && A.rs.ess_frac < INFINITY)
+    carry = !((S * S) / S2 < A.rs.ess_frac * (double)N);
   const bool draw_rs = finite && !carry;
   // the filter's bookkeeping, by one lane once nothing waits on it
-  auto finish = [&]() {
+  auto finish = [&](double lnS, double ess) {
     if (threadIdx.x != 0 || resample_only) return;
     double ell;
-    // the factor's normaliser: ln N after a resampling, else the carried
-    // weights' ln sum exp
-    const double lprev = carry0 ? lprev0 : log((double)N);
     if (ok) {
-      const double L = M + log(S);
+      const double L = M + lnS;
       ell = L - lprev;
       fs->lprev = L;
     } else {
@@ -433,7 +468,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
       anc[off + k] = j;
       if (ha) ha[k] = j;
     }
-    finish();
+    finish(log(S), ok ? (S * S) / S2 : 0.0);
     return;
   }
   if constexpr (RS == RS_REJECTION) {
@@ -441,7 +476,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
     // per output over the whole group (a collapsed filter's outputs take
     // about N attempts each, too many for one workgroup); here only the
     // filter's bookkeeping
-    finish();
+    finish(log(S), ok ? (S * S) / S2 : 0.0);
     return;
   }
   if constexpr (RS == RS_MULTINOMIAL) {
@@ -472,31 +507,35 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
       anc[off + k] = a;
       if (ha) ha[k] = a;
     }
-    finish();
+    finish(log(S), ok ? (S * S) / S2 : 0.0);
     return;
   }
   // (3) stratum counts of this lane's particles, in registers.  Particle i
   // owns strata [c_{i-1}, c_i).  The count before the lane's first particle
   // is the one the lane before computed for its last, at the same V_{l-1}.
-  auto count_at = [&](double W, int i) -> int32_t {
-    if (!draw_rs) return i + 1;
-    if constexpr (RS == RS_STRATIFIED)
-      return stratum_count_strat(W, S, invS, N, bkey(A.key), t, (uint32_t)f, iter);
-    else
-      return stratum_count(W, S, invS, u, N);
-  };
-  int32_t cnt[MAXP];
+  int32_t cnt[MAXP], cbefore, ctot;
+  if (!draw_rs) {
 #pragma unroll
-  for (int e = 0; e < MAXP; ++e) {
-    const int i = i0 + e;
-    cnt[e] = (e < P && i < i1) ? count_at(cum(e), i) : 0;
+    for (int e = 0; e < MAXP; ++e) cnt[e] = i0 + e + 1;
+    cbefore = i0;
+    ctot = N;
+  } else if constexpr (RS == RS_STRATIFIED) {
+    auto count_at = [&](double W) -> int32_t {
+      return stratum_count_strat(W, S, invS, N, bkey(A.key), t, (uint32_t)f, iter);
+    };
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e) cnt[e] = (e < P && i0 + e < i1) ? count_at(cum(e)) : 0;
+    cbefore = (i0 > 0 && i0 < N) ? count_at(vprev) : 0;
+    ctot = count_at(S);
+  } else {
+    lane_counts<MAXP>(P, i0, i1, vprev, S, invS, u, N, cum, cnt, cbefore, ctot);
   }
   // (4) ancestors: each particle with offspring marks the first stratum it
   // owns, and a running maximum over the strata then gives each its owner
   // (the runs are in particle order), so every lane does the same work
   // however the offspring fall.
   {
-    int cprev = (i0 > 0 && i0 < N) ? count_at(vprev, i0 - 1) : 0;
+    int cprev = i0 > 0 ? cbefore : 0;
 #pragma unroll
     for (int e = 0; e < MAXP; ++e) {
       const int i = i0 + e;
@@ -513,6 +552,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
   // 64 consecutive ancestors per wave
   const int seg = ((N + NW - 1) / NW + WAVE - 1) & ~(WAVE - 1);  // <= 64 MAXP
   const int sbase = wv * seg;
+  // (the bookkeeping's logarithm and division, in the shadow of the rows)
+  const double lnS = log(S);
+  const double ess = ok ? (S * S) / S2 : 0.0;
   int mk[MAXP];
   int rowmax = -1;
 #pragma unroll
@@ -528,9 +570,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 #pragma unroll
   for (int w = 0; w < NW; ++w)
     if (w < wv) before = max(before, xi[w]);
-  // strata past the last count (never expected: the last particle's
+  // strata past the last count ctot (never expected: the last particle's
   // cumulative weight is S) go to the last positive particle
-  const int ctot = count_at(S, N - 1);
   bool bad = false;
   auto owner = [&](int r, int k) -> int32_t {
     int32_t aj = k < ctot ? max(before, mk[r]) : jstar;
@@ -558,7 +599,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
     }
   }
   if (bad) atomicOr(&fs->pad, 1);
-  finish();
+  finish(lnS, ess);
 }
 
 // Rejection resampling (RS_REJECTION), after the collective's bookkeeping:

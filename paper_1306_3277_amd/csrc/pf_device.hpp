@@ -752,16 +752,21 @@ __device__ __forceinline__ double block_incl_max_scan(double v, double* red) {
 // check fails (the estimate rounded across a stratum edge) steps to the
 // exact count, so the result does not depend on how the estimate rounds.
 // N < 2^31.
-__device__ __forceinline__ int32_t stratum_count(double W, double S, double invS, double u,
-                                                 int32_t N) {
-  const double Nd = (double)N;
-  const double NW = Nd * W;
-  const double xv = NW * invS - u;
-  // fmax maps a NaN estimate to 0; the exact checks below then decide
-  int32_t est = (int32_t)__builtin_ceil(fmin(fmax(xv, 0.0), Nd));
+//
+// The estimate, and whether it lies near an integer (or is NaN):
+__device__ __forceinline__ int32_t stratum_estimate(double W, double invS, double u, double Nd,
+                                                    bool& near) {
+  const double xv = (Nd * W) * invS - u;
   const double fr = xv - __builtin_floor(xv);  // NaN for a NaN estimate
   const double thr = Nd * 0x1p-44;
-  if (fr > thr && fr < 1.0 - thr) return est;
+  near = !(fr > thr && fr < 1.0 - thr);
+  // fmax maps a NaN estimate to 0; the exact checks then decide
+  return (int32_t)__builtin_ceil(fmin(fmax(xv, 0.0), Nd));
+}
+// The exact count from an estimate near it.
+__device__ __forceinline__ int32_t stratum_exact(double W, double S, double u, int32_t N,
+                                                 int32_t est) {
+  const double NW = (double)N * W;
   const bool down = est > 0 && !((u + (double)(est - 1)) * S < NW);
   const bool up = est < N && (u + (double)est) * S < NW;
   if (down) {
@@ -772,6 +777,31 @@ __device__ __forceinline__ int32_t stratum_count(double W, double S, double invS
     while (est < N && (u + (double)est) * S < NW) ++est;
   }
   return est;
+}
+__device__ __forceinline__ int32_t stratum_count(double W, double S, double invS, double u,
+                                                 int32_t N) {
+  bool near;
+  const int32_t est = stratum_estimate(W, invS, u, (double)N, near);
+  return near ? stratum_exact(W, S, u, N, est) : est;
+}
+// A lane's P counts (those from index `live` on count for nothing): the
+// estimates side by side, one test for all of them, so that their chains
+// interleave instead of ending in a branch each.
+template <int P>
+__device__ __forceinline__ void stratum_counts(const double (&W)[P], double S, double invS,
+                                               double u, int32_t N, int live, int32_t (&c)[P]) {
+  const double Nd = (double)N;
+  bool near[P], any = false;
+#pragma unroll
+  for (int e = 0; e < P; ++e) {
+    c[e] = stratum_estimate(W[e], invS, u, Nd, near[e]);
+    any = any || (near[e] && e < live);
+  }
+  if (__builtin_expect(any, 0)) {
+#pragma unroll
+    for (int e = 0; e < P; ++e)
+      if (near[e] && e < live) c[e] = stratum_exact(W[e], S, u, N, c[e]);
+  }
 }
 
 // ---------------------------------------------------------------- resampling variants

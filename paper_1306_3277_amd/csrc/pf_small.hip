@@ -218,27 +218,7 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
 #pragma unroll
       for (int e = 0; e <= ROWS; ++e) c[e] = count(v[e]);
     } else {
-      // stratum_count's estimates side by side; it decides the few that lie
-      // near an integer
-      const double Nd = (double)N, thr = Nd * 0x1p-44;
-      bool near = false;
-#pragma unroll
-      for (int e = 0; e <= ROWS; ++e) {
-        const double xv = (Nd * v[e]) * invS - u;
-        const double cl = __builtin_ceil(xv);
-        c[e] = (int32_t)fmin(fmax(cl, 0.0), Nd);
-        const double fr = xv - __builtin_floor(xv);
-        near = near || !(fr > thr && fr < 1.0 - thr);
-      }
-      if (near) {
-#pragma unroll 1
-        for (int e = 0; e <= ROWS; ++e) {
-          const int32_t x = stratum_count(
-              e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : e == 3 ? v[3] : v[4], S, invS, u, N);
-#pragma unroll
-          for (int q = 0; q <= ROWS; ++q) c[q] = q == e ? x : c[q];
-        }
-      }
+      stratum_counts(v, S, invS, u, N, j0 < N ? ROWS + 1 : 0, c);
     }
 #pragma unroll
     for (int e = 0; e < ROWS; ++e) {
