@@ -59,7 +59,8 @@ struct Layout {
   int64_t nblk_total = 0;
   // byte offsets into the workspace
   size_t x_cur, x_tmp, lw, marks, anc, part, boff, owner, jc, fs, ell, ess, theta, obs, obs_pos,
-      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, nz, rec, total;
+      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, nz, rec, lw2, b_fused, total;
+  int32_t fused_cap = 0;  // entries of one fused table
   int32_t n_chunks = 0;
   // plain windkessel filters small enough for one workgroup each: the
   // intervals whose random numbers the workspace holds at a time (0: none)
@@ -209,6 +210,14 @@ Layout make_layout(const pf_config* c) {
       L.rec = take(8 * (size_t)c->B * (size_t)L.small_n * ((size_t)c->K + 3));
     }
   }
+  // fused intervals: the log-weights' other buffer and the launch tables
+  // (workgroups of 256 and of 512 particles; every group padded to whole rows
+  // of 8 entries)
+  if (c->layout == PF_LAYOUT_BATCHED) {
+    L.lw2 = take(8 * (size_t)N);
+    L.fused_cap = L.n_chunks + 8 * 8 * 34;
+    L.b_fused = take(2 * sizeof(pfk::FilterSlot) * (size_t)L.fused_cap);
+  }
   L.total = p;
   return L;
 }
@@ -248,6 +257,9 @@ struct pf_handle {
   int batch_nt = 256;
   int groups = 1;
   std::vector<int32_t> grp_chunk0, grp_nchunks, grp_order0, grp_nfilt, grp_maxn;
+  // the groups' parts of the fused launch tables, for 256 and 512 threads
+  std::vector<int32_t> grp_fused0[2], grp_nfused[2];
+  int64_t scanned[2] = {0, 0};  // particles that a fused launch of all groups scans
   // with G > 1 groups, group g's kernels run on side[g]; ev_a[0] forks the
   // side streams from the caller's, ev_b[g] joins group g back.  These
   // events are only ever recorded and waited on outside stream capture.
@@ -345,6 +357,7 @@ BatchArgs batch_args(const pf_handle* H) {
   a.chunk_k = H->at<int32_t>(H->L.b_chunk_k);
   a.chunk0 = 0;
   a.order0 = 0;
+  a.step = 1;
   a.fs = H->at<FilterState>(H->L.fs);
   a.ell_tr = H->at<double>(H->L.ell);
   a.ess_tr = H->at<double>(H->L.ess);
@@ -479,44 +492,76 @@ void set_history(const pf_handle* H, BatchArgs& a) {
   a.ha = h.ah;
 }
 
-// Propagation (K5a) of filter group g on stream s.
-pf_status enqueue_group_propagate(pf_handle* H, int g, hipStream_t s) {
+// Whether filter group g's runs of several intervals are fused (pf_fused.hip).
+// A fused interval saves a launch boundary and the ancestors' way through
+// memory, and pays for every workgroup scanning its whole filter: about 2.3 us
+// per million particles scanned in all.  Measured, us per interval, fused
+// against two launches (Lorenz '96 d = 8, K = 8, fast FP32, one group, 256
+// threads): 64 filters of 256: 11.6 / 13.0, of 2,048 (1.05 million scanned):
+// 17.2 / 18.8; 256 of 512: 15.6 / 17.2, of 1,024 (1.05 million): 26.8 / 26.4, of
+// 2,048 (4.2 million): 47 / 41.  Workgroups of 512 gain less, as their
+// propagation has two waves on a SIMD where two launches would spread them
+// (4 filters of 1,024: 13.7 / 13.1): they fuse only filters of more than 2,048
+// in groups that overlap (64 of 4,096, 2.1 million scanned, two groups: 24.4 /
+// 25.5; one group: 28.3 / 28.5).
+bool group_fused(const pf_handle* H, int g) {
   const pf_config& c = H->cfg;
+  if (H->timing || H->rs.scheme != pfk::RS_SYSTEMATIC ||
+      !pfk::fused_supported(c.model, c.d, H->batch_nt, H->grp_maxn[g]))
+    return false;
+  if (H->batch_nt == 256) return H->scanned[0] <= (1 << 20) + (1 << 17);
+  return H->groups > 1 && H->grp_maxn[g] > 2048 && H->scanned[1] <= (1 << 21) + (1 << 18);
+}
+
+// A run of n intervals of filter group g is a sequence of launches on one
+// stream (no events: this is what a group's graph holds): propagation (K5a)
+// and collective (K5b: likelihood, ESS, resampling) in turn; or, fused, the
+// first propagation, n - 1 launches of a collective with the propagation
+// after it, and the last collective.
+int group_launches(const pf_handle* H, int g, int n) {
+  return n > 1 && group_fused(H, g) ? n + 1 : 2 * n;
+}
+
+// Launch i of such a run on stream s.
+pf_status enqueue_group_launch(pf_handle* H, int g, hipStream_t s, int n, int i) {
+  const pf_config& c = H->cfg;
+  const bool fused = n > 1 && group_fused(H, g);
   BatchArgs a = batch_args(H);
   a.chunk0 = H->grp_chunk0[g];
   a.order0 = H->grp_order0[g];
   set_history(H, a);
+  // fused: the log-weights alternate between two buffers, interval n's in lw
+  double* const lw = H->at<double>(H->L.lw);
+  auto lw_of = [&](int k) { return fused && ((n - k) & 1) ? H->at<double>(H->L.lw2) : lw; };
+  const bool propagate = fused ? i == 0 : (i & 1) == 0;
+  const bool collective = fused ? i == n : (i & 1) == 1;
   hipEvent_t e0{};
   pf_status st = ev_begin(H, &e0, s);
   if (st) return st;
-  HIP_TRY(pfk::launch_batched_propagate(c.model, c.d, c.precision, H->ws + H->L.x_cur,
-                                        H->ws + H->L.x_tmp, H->at<double>(H->L.lw),
-                                        H->at<int32_t>(H->L.anc), a, H->grp_nchunks[g], s));
-  return ev_end(H, e0, 0, s);
+  if (propagate) {
+    HIP_TRY(pfk::launch_batched_propagate(c.model, c.d, c.precision, H->ws + H->L.x_cur,
+                                          H->ws + H->L.x_tmp, lw, lw_of(1),
+                                          H->at<int32_t>(H->L.anc), a, H->grp_nchunks[g], s));
+  } else if (collective) {
+    a.step = fused ? n : 1;
+    HIP_TRY(pfk::launch_batched_resample(H->batch_nt, lw, H->at<int32_t>(H->L.anc), a,
+                                         H->grp_nfilt[g], H->grp_maxn[g], H->grp_nchunks[g], s));
+  } else {
+    const int w = H->batch_nt == 256 ? 0 : 1;
+    a.step = i;
+    a.fused = H->at<pfk::FilterSlot>(H->L.b_fused) + (size_t)w * H->L.fused_cap +
+              H->grp_fused0[w][g];
+    HIP_TRY(pfk::launch_batched_fused(c.model, c.d, c.precision, H->batch_nt,
+                                      H->ws + H->L.x_cur, H->ws + H->L.x_tmp, lw_of(i),
+                                      lw_of(i + 1), a, H->grp_nfused[w][g], s));
+  }
+  return ev_end(H, e0, propagate ? 0 : 4, s);
 }
 
-// Collective (K5b: likelihood, ESS, resampling) of filter group g on stream s.
-pf_status enqueue_group_collective(pf_handle* H, int g, hipStream_t s) {
-  BatchArgs a = batch_args(H);
-  a.chunk0 = H->grp_chunk0[g];
-  a.order0 = H->grp_order0[g];
-  set_history(H, a);
-  hipEvent_t e0{};
-  pf_status st = ev_begin(H, &e0, s);
-  if (st) return st;
-  HIP_TRY(pfk::launch_batched_resample(H->batch_nt, H->at<double>(H->L.lw),
-                                       H->at<int32_t>(H->L.anc), a, H->grp_nfilt[g],
-                                       H->grp_maxn[g], H->grp_nchunks[g], s));
-  return ev_end(H, e0, 4, s);
-}
-
-// n intervals of filter group g, back to back on stream s (one stream, no
-// events: this is what a group's graph holds).
 pf_status enqueue_group(pf_handle* H, int g, hipStream_t s, int n) {
-  pf_status st;
-  for (int i = 0; i < n; ++i)
-    if ((st = enqueue_group_propagate(H, g, s)) || (st = enqueue_group_collective(H, g, s)))
-      return st;
+  const int m = group_launches(H, g, n);
+  for (int i = 0; i < m; ++i)
+    if (pf_status st = enqueue_group_launch(H, g, s, n, i)) return st;
   return PF_OK;
 }
 
@@ -542,16 +587,17 @@ pf_status join_groups(pf_handle* H, hipStream_t s) {
 // back to back on side[g]: the groups start together after everything
 // issued on s so far, drift against each other, and one group's collective
 // overlaps another's propagation; s waits for every group at the end.  The
-// launches are issued interval by interval across the groups, so no group
+// launches are issued in turn across the groups, so no group
 // waits for the host to issue another group's whole run.
 pf_status enqueue_batched(pf_handle* H, hipStream_t s, int n) {
   pf_status st;
   const int G = H->groups;
   if (G == 1) return enqueue_group(H, 0, s, n);
   if ((st = fork_groups(H, s))) return st;
-  for (int i = 0; i < n; ++i)
+  for (int i = 0; i < 2 * n; ++i)
     for (int g = 0; g < G; ++g)
-      if ((st = enqueue_group(H, g, H->side[g], 1))) return st;
+      if (i < group_launches(H, g, n) && (st = enqueue_group_launch(H, g, H->side[g], n, i)))
+        return st;
   return join_groups(H, s);
 }
 
@@ -727,8 +773,15 @@ pf_status build_groups(pf_handle* H, int G) {
     members[gbest].push_back(b);
     load[gbest] += H->np[b];
   }
-  std::vector<pfk::FilterSlot> ord;
+  std::vector<pfk::FilterSlot> ord, fused[2];
   std::vector<int32_t> chf, chk;
+  for (int w = 0; w < 2; ++w) {
+    H->grp_fused0[w].assign(G, 0);
+    H->grp_nfused[w].assign(G, 0);
+    H->scanned[w] = 0;
+    for (int b = 0; b < c.B; ++b)
+      H->scanned[w] += H->np[b] * ((H->np[b] + (256 << w) - 1) / (256 << w));
+  }
   H->grp_chunk0.assign(G, 0);
   H->grp_nchunks.assign(G, 0);
   H->grp_order0.assign(G, 0);
@@ -753,6 +806,26 @@ pf_status build_groups(pf_handle* H, int G) {
         chk.push_back((int32_t)k);
       }
     }
+    // Fused launches: a workgroup per 256 (512) particles.  Workgroups go to
+    // the 8 XCDs in turn, so a filter's take every eighth entry: its
+    // log-weights, which all of them read whole, then pass through one L2.
+    for (int w = 0; w < 2 && c.layout == PF_LAYOUT_BATCHED; ++w) {
+      const int64_t nt = 256 << w;
+      std::vector<pfk::FilterSlot> lane[8];
+      for (int32_t b : mg) {
+        auto* l = &lane[0];
+        for (auto& x : lane)
+          if (x.size() < l->size()) l = &x;
+        for (int64_t k = 0; k < H->np[b]; k += nt)
+          l->push_back({b, (int32_t)H->L.off[b], (int32_t)H->np[b], (int32_t)k});
+      }
+      size_t rows = 0;
+      for (auto& x : lane) rows = std::max(rows, x.size());
+      H->grp_fused0[w][g] = (int32_t)fused[w].size();
+      for (size_t r = 0; r < rows; ++r)
+        for (auto& x : lane) fused[w].push_back(r < x.size() ? x[r] : pfk::FilterSlot{0, 0, 0, 0});
+      H->grp_nfused[w][g] = (int32_t)fused[w].size() - H->grp_fused0[w][g];
+    }
     H->grp_nfilt[g] = (int32_t)ord.size() - H->grp_order0[g];
     if (m > 0) H->grp_maxn[g] = (int32_t)H->np[mg[0]];  // members are largest first
     H->grp_nchunks[g] = (int32_t)chf.size() - H->grp_chunk0[g];
@@ -763,6 +836,14 @@ pf_status build_groups(pf_handle* H, int G) {
                          hipMemcpyHostToDevice, H->stream));
   HIP_TRY(hipMemcpyAsync(H->ws + H->L.b_chunk_k, chk.data(), 4 * chk.size(),
                          hipMemcpyHostToDevice, H->stream));
+  for (int w = 0; w < 2; ++w) {
+    if (fused[w].empty()) continue;
+    if (fused[w].size() > (size_t)H->L.fused_cap)
+      return fail(PF_E_DEVICE, "internal: fused table of %zu entries", fused[w].size());
+    HIP_TRY(hipMemcpyAsync(H->at<pfk::FilterSlot>(H->L.b_fused) + (size_t)w * H->L.fused_cap,
+                           fused[w].data(), sizeof(pfk::FilterSlot) * fused[w].size(),
+                           hipMemcpyHostToDevice, H->stream));
+  }
   HIP_TRY(hipStreamSynchronize(H->stream));
   // a stream and two events per group (default priority); graphs captured
   // for another group count are rebuilt

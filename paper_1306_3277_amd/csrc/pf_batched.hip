@@ -13,14 +13,13 @@
 //        global memory for the next K5a.
 // Both kernels read the filter's step counter from device memory and pick
 // the state buffers by its parity, so one captured graph replays every step.
+// Runs of several intervals may fuse each K5b with the next K5a
+// (pf_fused.hip).
 #include <math.h>
 
-#include "pf_device.hpp"
-#include "pf_internal.hpp"
+#include "pf_batch_parts.hpp"
 
 namespace pfk {
-
-__device__ __forceinline__ Key bkey(const KeyArg& k) { return Key{k.lo, k.hi}; }
 
 // ---------------------------------------------------------------- init
 template <int MODEL, int D, typename Real>
@@ -53,26 +52,10 @@ __global__ __launch_bounds__(BATCH_NT) void k_batch_init(Real* __restrict__ x,
 }
 
 // ---------------------------------------------------------------- K5a
-template <int D, typename Real>
-__device__ __forceinline__ double batch_logdens(const Real (&x)[D], const double* yrow,
-                                                const int32_t* obs_pos, double inv_sd,
-                                                double cst) {
-  double acc = 0.0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const int o = obs_pos[i];
-    if (o >= 0) {
-      const double e = (yrow[o] - (double)x[i]) * inv_sd;
-      acc = acc + e * e;
-    }
-  }
-  return -0.5 * acc + cst;
-}
-
 template <int MODEL, int D, typename Real, bool HIST, bool ACC>
 __global__ __launch_bounds__(BATCH_NT) void k_batch_propagate(Real* __restrict__ xa,
                                                               Real* __restrict__ xb,
-                                                              double* __restrict__ lw,
+                                                              const double* lw_in, double* lw,
                                                               const int32_t* __restrict__ anc,
                                                               BatchArgs A) {
   const int f = A.chunk_f[A.chunk0 + blockIdx.x];
@@ -85,99 +68,13 @@ __global__ __launch_bounds__(BATCH_NT) void k_batch_propagate(Real* __restrict__
   // state written by step s lives in buffer s % 2
   const Real* xp = ((t - 1) & 1) ? xb : xa;
   Real* xn = (t & 1) ? xb : xa;
-  const Key key = bkey(A.key);
-  const double* th = A.theta + (size_t)f * 8;
-  const double* yrow = A.obs + (int64_t)(t - 1) * A.n_obs;
-  const int n0 = (t - 1) * A.K;
   const int64_t src = off + anc[off + k];
   const int64_t dst = off + k;
-  double l;
-  if constexpr (MODEL == 1) {
-    if constexpr (sizeof(Real) == 8) {
-      double p = xp[src];
-      for (int s = 1; s <= A.K; ++s) {
-        const uint4 w = draw(key, TAG_NOISE, 0, iter, (uint32_t)k, (uint32_t)(n0 + s), (uint32_t)f);
-        double z0, z1;
-        bm_pair_f64(w.x, w.y, z0, z1);
-        p = wk_substep_f64(p, th, A.q[n0 + s - 1], z0);
-      }
-      xn[dst] = p;
-      if constexpr (HIST) ((Real*)A.hx)[(int64_t)t * A.ld + dst] = p;
-      const double e = (yrow[0] - (p + th[2] * A.q[(int64_t)t * A.K])) * A.inv_sd;
-      l = -0.5 * (e * e) + A.lw_cst;
-    } else {
-      float p = xp[src];
-      double pa = p;  // the accurate form carries the pressure in FP64
-      const float a = (float)(th[0] - 1.0), c = (float)th[1], sp = (float)th[3];
-      for (int s = 1; s <= A.K; ++s) {
-        const uint4 w = draw(key, TAG_NOISE, 0, iter, (uint32_t)k, (uint32_t)(n0 + s), (uint32_t)f);
-        float z0, z1;
-        bm_pair_f32(w.x, w.y, z0, z1);
-        if constexpr (ACC)
-          pa = pa + (double)wk_increment_f32((float)pa, a, c, sp, (float)A.q[n0 + s - 1], z0);
-        else
-          p = wk_substep_f32(p, a, c, sp, (float)A.q[n0 + s - 1], z0);
-      }
-      if constexpr (ACC) p = (float)pa;
-      else pa = p;
-      xn[dst] = p;
-      if constexpr (HIST) ((Real*)A.hx)[(int64_t)t * A.ld + dst] = p;
-      const double e = (yrow[0] - (pa + th[2] * A.q[(int64_t)t * A.K])) * A.inv_sd;
-      l = -0.5 * (e * e) + A.lw_cst;
-    }
-  } else {
-    Real x[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) x[i] = xp[(int64_t)i * A.ld + src];
-    if constexpr (sizeof(Real) == 8) {
-      ModelConsts mc{A.h, A.hh, A.h6, A.inv_sd, A.lw_cst};
-      for (int s = 1; s <= A.K; ++s) {
-        if constexpr (MODEL == 3)
-          l96_substep_stage_f64<D>(x, th[0], th[1], mc, key, TAG_NOISE, iter, (uint32_t)k,
-                                   (uint32_t)(n0 + s), (uint32_t)f);
-        else
-          l96_substep_f64<D>(x, th[0], th[1], mc, key, TAG_NOISE, iter, (uint32_t)k,
-                             (uint32_t)(n0 + s), (uint32_t)f);
-      }
-    } else if constexpr (ACC) {
-      double xa[D];
-#pragma unroll
-      for (int i = 0; i < D; ++i) xa[i] = (double)x[i];
-      const L96F32A c = l96_f32a_consts(th[0], th[1], A.h);
-      for (int s = 1; s <= A.K; ++s) {
-        if constexpr (MODEL == 3)
-          l96_substep_stage_f32acc<D>(xa, c, key, TAG_NOISE, iter, (uint32_t)k,
-                                      (uint32_t)(n0 + s), (uint32_t)f);
-        else
-          l96_substep_f32acc<D>(xa, c, key, TAG_NOISE, iter, (uint32_t)k, (uint32_t)(n0 + s),
-                                (uint32_t)f);
-      }
-#pragma unroll
-      for (int i = 0; i < D; ++i) x[i] = (Real)xa[i];
-      // the log-weight from the state before it is rounded for storage
-      l = batch_logdens<D, double>(xa, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
-    } else {
-      const L96F32 c = l96_f32_consts(th[0], th[1], A.h);
-      for (int s = 1; s <= A.K; ++s) {
-        if constexpr (MODEL == 3)
-          l96_substep_stage_f32<D>(x, c, key, TAG_NOISE, iter, (uint32_t)k, (uint32_t)(n0 + s),
-                                   (uint32_t)f);
-        else
-          l96_substep_f32<D>(x, c, key, TAG_NOISE, iter, (uint32_t)k, (uint32_t)(n0 + s),
-                             (uint32_t)f);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < D; ++i) xn[(int64_t)i * A.ld + dst] = x[i];
-    if constexpr (HIST) {  // the history's slot t, written from the same registers
-      Real* xh = (Real*)A.hx + (int64_t)t * D * A.ld;
-#pragma unroll
-      for (int i = 0; i < D; ++i) xh[(int64_t)i * A.ld + dst] = x[i];
-    }
-    if constexpr (!ACC || sizeof(Real) == 8) l = batch_logdens<D, Real>(x, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
-  }
+  // the history's slot t is written from the same registers
+  Real* xh = HIST ? (Real*)A.hx + (int64_t)t * (MODEL == 1 ? 1 : D) * A.ld : nullptr;
+  double l = propagate_one<MODEL, D, Real, ACC, HIST>(xp, xn, xh, src, dst, k, f, t, iter, A);
   // weights kept from a step that did not resample carry over
-  if (A.fs[f].carry) l = lw[dst] + l;
+  if (A.fs[f].carry) l = lw_in[dst] + l;
   lw[dst] = l;
 }
 
@@ -201,74 +98,6 @@ __global__ __launch_bounds__(BATCH_NT) void k_batch_propagate(Real* __restrict__
 // could lengthen, no search); each row of owners is stored as it stands.
 // The resampling uniform is drawn while the loads are in flight, off the
 // critical path.  At most 66 KB of LDS per workgroup.
-__device__ __forceinline__ int stage_slot(int i) { return i ^ ((i >> 4) & 15); }
-
-// The ancestors in LDS (the stage, once its weights are read): one padding
-// word after every 16, so that lanes reading or writing their own runs of
-// P consecutive entries hit distinct banks (8,704 words for 8192 entries).
-__device__ __forceinline__ int anc_slot(int i) { return i + (i >> 4); }
-
-// A lane's weights e^{lw - M} over its run [i0, i1) of P <= CNT particles,
-// their in-lane prefix sums, sum of squares and last positive index.  The
-// body is straight-line over CNT slots (weights past the run are 0 and add
-// nothing), so the exponentials interleave; P is the same for every lane,
-// so the choice of CNT (the smallest power of two >= P) is a uniform branch.
-template <int CNT, int MAXP>
-__device__ __forceinline__ void lane_weights(const double* stage, int N, double M, bool finite,
-                                             int P, int i0, int i1, double (&loc)[MAXP],
-                                             double& run, double& run2, int& cand) {
-  if constexpr (CNT > 1) {
-    if (P <= CNT / 2) {
-      lane_weights<CNT / 2, MAXP>(stage, N, M, finite, P, i0, i1, loc, run, run2, cand);
-      return;
-    }
-  }
-  double lv[CNT];
-#pragma unroll
-  for (int e = 0; e < CNT; ++e) lv[e] = stage[stage_slot(min(i0 + e, N - 1))];
-#pragma unroll
-  for (int e = 0; e < CNT; ++e) {
-    const double we = exp_nonpos(lv[e] - M);  // exp(-inf) = 0
-    const double w = (finite && e < P && i0 + e < i1) ? we : 0.0;
-    cand = (w > 0.0) ? i0 + e : cand;
-    run += w;
-    run2 += w * w;
-    loc[e] = run;
-  }
-}
-
-// A lane's counts over its run of P particles, four side by side (more would
-// hold more registers than the propagation running beside it can spare), the
-// count before its first particle and the count of the whole filter.
-// cum(e): particle e's cumulative weight.
-template <int MAXP, class Cum>
-__device__ __forceinline__ void lane_counts(int P, int i0, int i1, double vprev, double S,
-                                            double invS, double u, int N, Cum cum,
-                                            int32_t (&cnt)[MAXP], int32_t& before,
-                                            int32_t& total) {
-  constexpr int G = MAXP < 4 ? MAXP : 4;
-  const int n = i1 - i0;
-  {
-    const double W[2] = {S, vprev};
-    int32_t c[2];
-    stratum_counts(W, S, invS, u, N, n > 0 ? 2 : 1, c);
-    total = c[0];
-    before = c[1];
-  }
-#pragma unroll
-  for (int g = 0; g < MAXP; g += G) {
-    if (g < P) {
-      double W[G];
-      int32_t c[G];
-#pragma unroll
-      for (int e = 0; e < G; ++e) W[e] = cum(g + e);
-      stratum_counts(W, S, invS, u, N, n - g, c);
-#pragma unroll
-      for (int e = 0; e < G; ++e) cnt[g + e] = c[e];
-    }
-  }
-}
-
 // MAXP bounds the particles per lane: the launcher picks the smallest of
 // BATCH_MAXN / NT, half and a quarter of it that covers the group's largest
 // filter, so the unrolled per-lane phases do no work for absent particles.
@@ -288,9 +117,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
   constexpr int NAL = SEP ? NT * MAXP + NT * MAXP / 16 : 1;
   __shared__ double stage[NT * MAXP];
   __shared__ int32_t al_own[NAL];
-  __shared__ double xa[NW], xs[NW], xb[NW];
-  __shared__ int xi[NW];
-  __shared__ double bc;
+  __shared__ ScanLds<NT> X;
   int32_t* al = SEP ? al_own : reinterpret_cast<int32_t*>(stage);
   const FilterSlot slot = A.order[A.order0 + blockIdx.x];
   const int f = slot.f;
@@ -308,102 +135,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
   double lprev = 0.0;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   const bool resample_only = A.mode != 0;
-  const int t = resample_only ? fs->t : fs->t + 1;
+  const int t = resample_only ? fs->t : fs->t + A.step;
   // the history's ancestor slot t-1 of this filter, if one is attached
   int32_t* const ha = A.ha ? A.ha + (int64_t)(t - 1) * A.ld + off : nullptr;
   if constexpr (SEP)
     for (int k = (int)threadIdx.x; k < N; k += NT) al[anc_slot(k)] = -1;
-  // (1) coalesced load to the stage and the maximum; the loads are issued
-  // together (indices past the filter read its last element and are
-  // dropped), so their latencies overlap
-  double m = -INFINITY;
-  {
-    double v[MAXP];
-#pragma unroll
-    for (int r = 0; r < MAXP; ++r) v[r] = lw[off + min((int)threadIdx.x + r * NT, N - 1)];
-    // the resampling uniform, drawn while the loads are in flight and
-    // published with the first exchange; the likelihood's ln N with it
-    if (threadIdx.x == 0) {
-      bc = resample_only ? A.u_override[f]
-                         : u01_f64(draw(bkey(A.key), TAG_RESAMPLE, 0, iter, 0, (uint32_t)t,
-                                        (uint32_t)f).x);
-      lprev = carry0 ? lprev0 : log((double)N);
-    }
-#pragma unroll
-    for (int r = 0; r < MAXP; ++r) {
-      const int i = (int)threadIdx.x + r * NT;
-      if (i < N) {
-        const double x = (v[r] == v[r]) ? v[r] : -INFINITY;  // NaN counts as zero weight
-        stage[stage_slot(i)] = x;
-        m = fmax(m, x);
-      }
-    }
-  }
-  m = wave_max(m);
-  if (lane == 0) xa[wv] = m;
-  __syncthreads();  // 1
-  double u = bc;
-  double M = xa[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) M = fmax(M, xa[w]);
-  const bool finite = (M > -INFINITY) && (M < INFINITY);
-  // (2) this lane's run: weights, in-lane prefix, square sum, last positive
-  const int P = (N + NT - 1) / NT;
-  const int i0 = min(N, (int)threadIdx.x * P), i1 = min(N, i0 + P);
-  double loc[MAXP];
-  double run = 0.0, run2 = 0.0;
-  int cand = -1;
-  lane_weights<MAXP, MAXP>(stage, N, M, finite, P, i0, i1, loc, run, run2, cand);
-  // one exchange: scan of the lanes' sums, total of squares, last positive
-  // The scan's partial sums are rounded along different trees, so one
-  // lane's may fall an ulp below the lane before: a running maximum makes
-  // them non-decreasing, held past the filter's last particle (lanes with no
-  // particles take -inf there), so that a wave's total is its last
-  // particle's.
-  const double incl = wave_incl_scan(run);
-  const double inclm = wave_incl_max_scan((i1 > i0) ? incl : -INFINITY);
-  const double s2w = wave_sum(run2);
-  const int cw = wave_max_i(cand);
-  // (the lane sums go to their own array, so no barrier separates them from
-  // the maxima read above; the stage is reused only after this exchange)
-  if (lane == WAVE - 1) xs[wv] = (inclm > -INFINITY) ? inclm : 0.0;
-  if (lane == 0) {
-    xb[wv] = s2w;
-    xi[wv] = cw;
-  }
-  __syncthreads();  // 3
-  // S: the waves' totals added in order; base: the same sum over the waves
-  // before this one (the same operations, so the same bits)
-  double base = 0.0, S = 0.0, S2 = 0.0;
-  int jstar = -1;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w == wv) base = S;
-    S += xs[w];
-    S2 += xb[w];
-    jstar = max(jstar, xi[w]);
-  }
+  // (1), (2): the scan; the likelihood's ln N is taken beside the uniform
+  BatchScan<MAXP> sc;
+  batch_scan<NT, MAXP>(
+      lw + off, N, stage, X,
+      [&]() -> double {
+        lprev = carry0 ? lprev0 : log((double)N);
+        return resample_only ? A.u_override[f]
+                             : u01_f64(draw(bkey(A.key), TAG_RESAMPLE, 0, iter, 0, (uint32_t)t,
+                                            (uint32_t)f).x);
+      },
+      sc);
+  const double M = sc.M, S = sc.S, S2 = sc.S2, u = sc.u, vprev = sc.vprev;
+  const bool finite = sc.finite;
+  const int P = sc.P, i0 = sc.i0, i1 = sc.i1, jstar = sc.jstar;
+  auto cum = [&](int e) -> double { return sc.cum(e); };
   // the ancestor slots in the stage start empty once its weights are read
   // (the Metropolis, rejection and multinomial forms still use the stage)
   if constexpr (!SEP && (RS == RS_SYSTEMATIC || RS == RS_STRATIFIED)) {
     for (int k = (int)threadIdx.x; k < N; k += NT) al[anc_slot(k)] = -1;
     __syncthreads();  // 4
   }
-  // The cumulative weights: lane l's last particle has V_l = base + its
-  // running total; before its first particle stands V_{l-1}, which the lane
-  // before computes from the same two values (at a wave's first lane it is
-  // base, the previous wave's last V); the particles between take
-  // min(V_{l-1} + in-lane prefix, V_l).  Each value lies in [V_{l-1}, V_l]
-  // (the prefixes are non-negative), so the sequence never decreases across
-  // lanes and waves, and the filter's last particle has exactly S.
-  // (the lane move runs in every lane, outside the select: a lane whose
-  // source lane is switched off would read nothing)
-  const double inprev = wave_prev(inclm, 0.0);
-  const double vprev = (lane == 0) ? base : base + inprev;
-  const double vlast = base + inclm;
-  auto cum = [&](int e) -> double {
-    return (i0 + e == i1 - 1) ? vlast : fmin(vprev + loc[e], vlast);
-  };
   // every lane holds the same S and S2, so every lane takes the trigger's
   // decision itself (resample when ESS < ess_frac N); a step that keeps its
   // weights, or has none positive, gives every particle one offspring:
@@ -564,12 +321,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
     mk[r] = max(wave_incl_max_scan_rows(v), rowmax);
     rowmax = __builtin_amdgcn_readlane(mk[r], WAVE - 1);
   }
-  if (lane == 0) xi[wv] = rowmax;
+  if (lane == 0) X.xi[wv] = rowmax;
   __syncthreads();  // 8
   int before = -1;
 #pragma unroll
   for (int w = 0; w < NW; ++w)
-    if (w < wv) before = max(before, xi[w]);
+    if (w < wv) before = max(before, X.xi[w]);
   // strata past the last count ctot (never expected: the last particle's
   // cumulative weight is S) go to the last positive particle
   bool bad = false;
@@ -679,47 +436,47 @@ hipError_t launch_batched_init(int model, int d, int prec, void* x, int32_t* anc
 // kernel without a history carries no trace of them); ACC selects the
 // accurate FP32 form
 template <int MODEL, int D, typename Real, bool ACC = false>
-void launch_k5a(unsigned g, hipStream_t s, void* xa, void* xb, double* lw, const int32_t* anc,
-                const BatchArgs& a) {
+void launch_k5a(unsigned g, hipStream_t s, void* xa, void* xb, const double* lw_in, double* lw,
+                const int32_t* anc, const BatchArgs& a) {
   if (a.hx)
     hipLaunchKernelGGL((k_batch_propagate<MODEL, D, Real, true, ACC>), g, BATCH_NT, 0, s,
-                       (Real*)xa, (Real*)xb, lw, anc, a);
+                       (Real*)xa, (Real*)xb, lw_in, lw, anc, a);
   else
     hipLaunchKernelGGL((k_batch_propagate<MODEL, D, Real, false, ACC>), g, BATCH_NT, 0, s,
-                       (Real*)xa, (Real*)xb, lw, anc, a);
+                       (Real*)xa, (Real*)xb, lw_in, lw, anc, a);
 }
 
-hipError_t launch_batched_propagate(int model, int d, int prec, void* xa, void* xb, double* lw,
-                                    const int32_t* anc, const BatchArgs& a, int nchunks,
-                                    hipStream_t s) {
+hipError_t launch_batched_propagate(int model, int d, int prec, void* xa, void* xb,
+                                    const double* lw_in, double* lw, const int32_t* anc,
+                                    const BatchArgs& a, int nchunks, hipStream_t s) {
   if (nchunks <= 0) return hipSuccess;
   const unsigned g = (unsigned)nchunks;
   if (model == 1) {
     if (prec == 0)
-      launch_k5a<1, 1, double>(g, s, xa, xb, lw, anc, a);
+      launch_k5a<1, 1, double>(g, s, xa, xb, lw_in, lw, anc, a);
     else if (prec == 1)
-      launch_k5a<1, 1, float>(g, s, xa, xb, lw, anc, a);
+      launch_k5a<1, 1, float>(g, s, xa, xb, lw_in, lw, anc, a);
     else
-      launch_k5a<1, 1, float, true>(g, s, xa, xb, lw, anc, a);
+      launch_k5a<1, 1, float, true>(g, s, xa, xb, lw_in, lw, anc, a);
     return hipGetLastError();
   }
   switch (d * 4 + model) {
 #define X(DD)                                                  \
   case DD * 4 + 2:                                             \
     if (prec == 0)                                             \
-      launch_k5a<2, DD, double>(g, s, xa, xb, lw, anc, a);     \
+      launch_k5a<2, DD, double>(g, s, xa, xb, lw_in, lw, anc, a);     \
     else if (prec == 1)                                        \
-      launch_k5a<2, DD, float>(g, s, xa, xb, lw, anc, a);      \
+      launch_k5a<2, DD, float>(g, s, xa, xb, lw_in, lw, anc, a);      \
     else                                                       \
-      launch_k5a<2, DD, float, true>(g, s, xa, xb, lw, anc, a); \
+      launch_k5a<2, DD, float, true>(g, s, xa, xb, lw_in, lw, anc, a); \
     break;                                                     \
   case DD * 4 + 3:                                             \
     if (prec == 0)                                             \
-      launch_k5a<3, DD, double>(g, s, xa, xb, lw, anc, a);     \
+      launch_k5a<3, DD, double>(g, s, xa, xb, lw_in, lw, anc, a);     \
     else if (prec == 1)                                        \
-      launch_k5a<3, DD, float>(g, s, xa, xb, lw, anc, a);      \
+      launch_k5a<3, DD, float>(g, s, xa, xb, lw_in, lw, anc, a);      \
     else                                                       \
-      launch_k5a<3, DD, float, true>(g, s, xa, xb, lw, anc, a); \
+      launch_k5a<3, DD, float, true>(g, s, xa, xb, lw_in, lw, anc, a); \
     break;
     PF_L96_DIMS_B(X)
 #undef X

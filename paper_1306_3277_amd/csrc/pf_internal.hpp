@@ -115,6 +115,11 @@ struct BatchArgs {
   const int32_t* chunk_k;   // device [n_chunks] first particle of each chunk
   int32_t chunk0;           // first chunk of the launch (its filter group)
   int32_t order0;           // first filter slot of the launch in `order`
+  // Fused runs advance the filters' counters at their end only: the intervals
+  // since then of a fused interval (>= 1), and of the run's last collective
+  // (1 when every interval has its own).
+  int32_t step;
+  const FilterSlot* fused;  // device table of the fused launch (pad: first particle)
   FilterState* fs;          // device [B]
   double* ell_tr;           // device [B][T]
   double* ess_tr;
@@ -202,9 +207,23 @@ hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, doub
 // ---- batched (pf_batched.hip) ----
 hipError_t launch_batched_init(int model, int d, int prec, void* x, int32_t* anc,
                                const BatchArgs& a, hipStream_t s);
-hipError_t launch_batched_propagate(int model, int d, int prec, void* xa, void* xb, double* lw,
-                                    const int32_t* anc, const BatchArgs& a, int nchunks,
-                                    hipStream_t s);
+// (weights that a step kept are read from lw_in, new ones written to lw)
+hipError_t launch_batched_propagate(int model, int d, int prec, void* xa, void* xb,
+                                    const double* lw_in, double* lw, const int32_t* anc,
+                                    const BatchArgs& a, int nchunks, hipStream_t s);
+// Fused intervals (pf_fused.hip): the collective of interval t - 1 and the
+// propagation of interval t = counter + 1 + a.step in one launch of nentries
+// workgroups of nt threads, one per entry of a.fused; reads the log-weights
+// lw_in, writes lw (another buffer).  fused_supported: whether such a kernel
+// exists (systematic resampling, filters of up to max_n particles).
+constexpr int FUSED_PER = 8;  // particles of the filter per thread in its scan
+inline bool fused_supported(int model, int d, int nt, int max_n) {
+  return (nt == 256 || nt == 512) && max_n <= FUSED_PER * nt &&
+         (model == 1 || d == 4 || d == 8 || d == 16);
+}
+hipError_t launch_batched_fused(int model, int d, int prec, int nt, void* xa, void* xb,
+                                const double* lw_in, double* lw, const BatchArgs& a,
+                                int nentries, hipStream_t s);
 // The collective of nfilters filters (the launch's slots in `order`); with
 // rejection resampling also the ancestors of the launch's nchunks chunks.
 hipError_t launch_batched_resample(int nt, const double* lw, int32_t* anc, const BatchArgs& a,
