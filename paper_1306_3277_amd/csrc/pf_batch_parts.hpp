@@ -10,22 +10,6 @@ namespace pfk {
 __device__ __forceinline__ Key bkey(const KeyArg& k) { return Key{k.lo, k.hi}; }
 
 // ---------------------------------------------------------------- one particle's interval
-template <int D, typename Real>
-__device__ __forceinline__ double batch_logdens(const Real (&x)[D], const double* yrow,
-                                                const int32_t* obs_pos, double inv_sd,
-                                                double cst) {
-  double acc = 0.0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const int o = obs_pos[i];
-    if (o >= 0) {
-      const double e = (yrow[o] - (double)x[i]) * inv_sd;
-      acc = acc + e * e;
-    }
-  }
-  return -0.5 * acc + cst;
-}
-
 // Interval t of particle k of filter f (f uniform): the state at column src
 // of xp through K substeps to column dst of xn (and of the history's slot xh,
 // with HIST); returns the log-weight of the observation.
@@ -77,6 +61,8 @@ __device__ __forceinline__ double propagate_one(const Real* __restrict__ xp,
       l = -0.5 * (e * e) + A.lw_cst;
     }
   } else {
+    ObsAhead<D> obs;
+    if constexpr (D <= OBS_AHEAD) obs.fetch(yrow, A.obs_pos);
     Real x[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) x[i] = xp[(int64_t)i * A.ld + src];
@@ -106,7 +92,7 @@ __device__ __forceinline__ double propagate_one(const Real* __restrict__ xp,
 #pragma unroll
       for (int i = 0; i < D; ++i) x[i] = (Real)xa[i];
       // the log-weight from the state before it is rounded for storage
-      l = batch_logdens<D, double>(xa, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
+      l = l96_logdens<D, double>(xa, obs, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
     } else {
       const L96F32 c = l96_f32_consts(th[0], th[1], A.h);
       for (int s = 1; s <= A.K; ++s) {
@@ -124,7 +110,9 @@ __device__ __forceinline__ double propagate_one(const Real* __restrict__ xp,
 #pragma unroll
       for (int i = 0; i < D; ++i) xh[(int64_t)i * A.ld + dst] = x[i];
     }
-    if constexpr (!ACC || sizeof(Real) == 8) l = batch_logdens<D, Real>(x, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
+    if constexpr (!ACC || sizeof(Real) == 8) {
+      l = l96_logdens<D, Real>(x, obs, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
+    }
   }
   return l;
 }

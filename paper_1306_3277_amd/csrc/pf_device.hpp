@@ -569,6 +569,70 @@ __device__ __forceinline__ void l96_substep_stage_f32(float (&x)[D], const L96F3
   for (int i = 0; i < D; ++i) x[i] = x[i] + acc[i];
 }
 
+// ---------------------------------------------------------------- observation density
+// One time's observations by component, fetched together (uniform loads: the
+// positions, then the values): testing and fetching them one component after
+// the other was a chain of dependent scalar loads at the end of a propagation
+// (2,800 of 20,500 cycles at d = 8 with a wave per SIMD).  Up to OBS_AHEAD
+// components are fetched before the substeps, which hide them; more would push
+// other uniform values out of the scalar registers, so larger states fetch
+// eight at a time when they need them.
+constexpr int OBS_AHEAD = 8;
+template <int D>
+struct ObsRow {
+  double y[D];
+  uint32_t seen;  // components observed
+  // (no kernel writes either array: as constant memory they load on the
+  // scalar unit also after the kernel's own stores)
+  __device__ __forceinline__ void fetch(const double* yrow_, const int32_t* obs_pos_) {
+    typedef const __attribute__((address_space(4))) double* CD;
+    typedef const __attribute__((address_space(4))) int32_t* CI;
+    const CD yrow = (CD)(uintptr_t)yrow_;
+    const CI obs_pos = (CI)(uintptr_t)obs_pos_;
+    int32_t o[D];
+    seen = 0;
+#pragma unroll
+    for (int i = 0; i < D; ++i) o[i] = obs_pos[i];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      y[i] = yrow[o[i] < 0 ? 0 : o[i]];
+      seen |= (uint32_t)(o[i] >= 0) << i;
+    }
+  }
+};
+// what is held ahead of the substeps (nothing for a large state)
+template <int D>
+using ObsAhead = ObsRow<(D <= OBS_AHEAD ? D : 1)>;
+
+// Observation log-density of one particle, in FP64 from the (FP32 or FP64)
+// state: the residuals are formed after widening the state, so an FP32 path
+// adds no rounding of its own here (a log-weight stored in FP32 would carry
+// ~2^-24 |lw|, above the per-step accuracy once |lw| reaches the hundreds).
+// Components are visited in increasing index, the order of the sorted
+// observation list.
+template <int D, typename Real>
+__device__ __forceinline__ double l96_logdens(const Real (&x)[D], const ObsAhead<D>& ahead,
+                                              const double* __restrict__ yrow,
+                                              const int32_t* __restrict__ obs_pos,
+                                              double inv_sd, double cst) {
+  constexpr int G = D <= OBS_AHEAD ? D : 8;
+  static_assert(D % G == 0, "whole groups");
+  double acc = 0.0;
+#pragma unroll
+  for (int g = 0; g < D; g += G) {
+    ObsRow<G> o;
+    if constexpr (D <= OBS_AHEAD) o = ahead;
+    else o.fetch(yrow, obs_pos + g);
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+      if ((o.seen >> i) & 1) {
+        const double e = (o.y[i] - (double)x[g + i]) * inv_sd;
+        acc = acc + e * e;
+      }
+  }
+  return -0.5 * acc + cst;
+}
+
 // e^x for x <= 0, x = -inf included (weights exp(lw - max lw)).  Reduction
 // x = n ln2 + r with |r| <= ln2/2 (ln2 split in two parts, so r is exact to
 // about 2^-60), e^r by its Taylor polynomial to degree 13 (truncation below
@@ -654,6 +718,12 @@ __device__ __forceinline__ int wave_incl_max_scan_i(int v, int = 0) {
 __device__ __forceinline__ double last_lane(double v) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), WAVE - 1);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), WAVE - 1);
+  return __hiloint2double(hi, lo);
+}
+// the value of a (uniform) lane, in every lane
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
   return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ double wave_max(double v) { return last_lane(wave_incl_max_scan(v)); }

@@ -80,12 +80,6 @@ struct KfSeriesLds {
   __device__ __forceinline__ double y(int t) const { return yp[t]; }
 };
 
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // inclusive scan of the affine maps (a, b): lane l gets the composition of
 // lanes 0..l's, first lane applied first
 template <int CTRL, int ROWS>

@@ -84,104 +84,202 @@ __global__ void k_reset(FilterState* fs, double* ell, double* ess, int B, int T,
 // the rounding, so the cumulative weights built on them are monotone.
 //
 // Two forms.  A filter of at most FUSE_NB blocks has every K3 block combine
-// all of its partials itself (the same order, the same code, so every block
-// obtains the same bits with no extra launch and no communication between
-// blocks); the partials are read coalesced and their scaled totals staged
-// in LDS.  A larger filter has one K2 workgroup combine them once and store
-// the offsets, before K3.
+// all of its partials itself, each wave in the same order and with the same
+// code as if a workgroup of COMB_NT lanes did, so that all obtain the same bits
+// with no extra launch and no communication between blocks (a block's waves
+// sharing the scans took five barriers, 6,450 of the block's 13,500 cycles at
+// 256 partials).  A larger filter has one K2 workgroup combine them once and
+// store the offsets, before K3.
 struct Combined {
   double M, S, S2, lo, hi;
 };
 
-template <int NT, int MAXNB>
-__device__ __forceinline__ Combined combine_block_lds(const double* __restrict__ P, int nb,
-                                                      int k1b, int span) {
-  constexpr int NW = NT / WAVE;
-  __shared__ double sT[MAXNB + MAXNB / 16];  // T_i at i + i/16 (padded against bank conflicts)
-  __shared__ double xm[NW], xs[NW], xs2[NW], xv[NW], xo[2];
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  // exchange 1: the global maximum (coalesced reads)
-  double m = -INFINITY;
-  for (int i = threadIdx.x; i < nb; i += NT) m = fmax(m, P[3 * i]);
-  m = wave_max(m);
-  if (lane == 0) xm[wv] = m;
-  __syncthreads();
-  double M = xm[0];
+// The wave's lane l stands for lanes l, l + 64, l + 128 and l + 192 (its rows)
+// of a combining workgroup of COMB_NT lanes, each of which owns `chunk`
+// consecutive partials.  lo, hi: the offsets of partials k1b and k1b + span (S
+// at the end).  Up to 64 partials fill one row, up to COMB_NT all four with a
+// partial each; beyond, the block's waves share the exponentials through LDS
+// (two barriers) and each scans them all (16 exponentials per lane took
+// 10,500 cycles at 780 partials).
+constexpr int COMB_NT = 256;
+constexpr int COMB_PER = 4;  // partials per lane, at most
+static_assert(FUSE_NB <= COMB_PER * COMB_NT, "partials per lane");
+struct CombineLds {
+  double T[FUSE_NB + FUSE_NB / 16];  // T_i at i + i/16 (padded against bank conflicts)
+  double xm[COMB_NT / WAVE], xs2[COMB_NT / WAVE];
+};
+
+// The scan, from the lanes' totals T[r][c] of partials (64 r + lane) chunk + c.
+template <int ROWS, int CH>
+__device__ __forceinline__ void combine_scan(const double (&T)[ROWS][CH], int nb, int chunk,
+                                             int k1b, int span, Combined& o) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  double pre[ROWS], tot[ROWS], S = 0.0;
 #pragma unroll
-  for (int w = 1; w < NW; ++w) M = fmax(M, xm[w]);
-  const bool finite = (M > -INFINITY) && (M < INFINITY);
-  // block totals T_i = s_i exp(m_i - M) to LDS; sum of squares per lane
-  double loc2 = 0.0;
-  for (int i = threadIdx.x; i < nb; i += NT) {
-    const double mb = P[3 * i];
-    double T = 0.0;
-    if (finite && mb > -INFINITY) {
-      const double sc = exp_nonpos(mb - M);
-      T = P[3 * i + 1] * sc;
-      loc2 += P[3 * i + 2] * (sc * sc);
-    }
-    sT[i + (i >> 4)] = T;
-  }
-  __syncthreads();
-  // each lane's contiguous chunk, summed sequentially
-  const int chunk = (nb + NT - 1) / NT;
-  const int i0 = min(nb, (int)threadIdx.x * chunk), i1 = min(nb, i0 + chunk);
-  double loc = 0.0;
-  for (int i = i0; i < i1; ++i) loc += sT[i + (i >> 4)];
-  // exchange 2: scan of the lanes' sums, total of squares
-  const double incl = wave_incl_scan(loc, lane);
-  const double s2w = wave_sum(loc2);
-  if (lane == WAVE - 1) xs[wv] = incl;
-  if (lane == 0) xs2[wv] = s2w;
-  __syncthreads();
-  double pre = incl - loc, S = 0.0, S2 = 0.0;
+  for (int r = 0; r < ROWS; ++r) {
+    double loc = 0.0;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w < wv) pre += xs[w];
-    S += xs[w];
-    S2 += xs2[w];
+    for (int c = 0; c < CH; ++c) loc += T[r][c];
+    const double incl = wave_incl_scan(loc);
+    pre[r] = incl - loc;
+    tot[r] = last_lane(incl);
   }
-  // this lane's last offset; an exact running maximum over earlier lanes
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+    for (int q = 0; q < r; ++q) pre[r] += tot[q];
+    S += tot[r];
+  }
+  // each lane's last offset; an exact running maximum over earlier lanes
   // makes the offsets non-decreasing whatever the rounding of the scan
-  double last = -INFINITY;
-  {
-    double run = pre;
-    for (int i = i0; i < i1; ++i) {
-      last = run;
-      run += sT[i + (i >> 4)];
-    }
-  }
-  const double vin = wave_incl_max_scan(last, lane);
-  const double vup = wave_prev(vin, -INFINITY);
-  if (lane == WAVE - 1) xv[wv] = vin;
-  __syncthreads();  // exchange 3
-  double vw = -INFINITY, vall = -INFINITY;
+  double vprev[ROWS], vall = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w < wv) vw = fmax(vw, xv[w]);
-    vall = fmax(vall, xv[w]);
+  for (int r = 0; r < ROWS; ++r) {
+    double last = -INFINITY, run = pre[r];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+      if (c < chunk && (r * WAVE + lane) * chunk + c < nb) {
+        last = run;
+        run += T[r][c];
+      }
+    const double vin = wave_incl_max_scan(last);
+    vprev[r] = fmax(wave_prev(vin, -INFINITY), vall);
+    vall = fmax(vall, last_lane(vin));
   }
-  const double vprev = (lane == 0) ? vw : fmax(vup, vw);
-  const double Sf = fmax(S, vall);
-  // the two offsets this block needs, from the lanes that own them
-  const int k1e = k1b + span;
-  {
-    double run = pre;
-    for (int i = i0; i < i1; ++i) {
-      if (i == k1b) xo[0] = fmax(run, vprev);
-      if (i == k1e) xo[1] = fmax(run, vprev);
-      run += sT[i + (i >> 4)];
+  o.S = fmax(S, vall);
+  // the offset of partial i, from the lane that owns it
+  auto offset = [&](int i) -> double {
+    if (i >= nb) return o.S;
+    const int q = CH == 1 ? i : i / chunk, c0 = CH == 1 ? 0 : i - q * chunk, r0 = q / WAVE;
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+      double run = pre[r];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        if (r == r0 && c == c0) v = fmax(run, vprev[r]);
+        run += T[r][c];
+      }
     }
+    return lane_value(v, q & (WAVE - 1));
+  };
+  o.lo = offset(k1b);
+  o.hi = offset(k1b + span);
+}
+
+// nb <= 64 ROWS partials, each wave for itself.  between() runs while they
+// load.  S2 only if want2.
+template <int ROWS, class Between>
+__device__ __forceinline__ Combined combine_wave(const double* __restrict__ P, int nb, int k1b,
+                                                 int span, bool want2, Between between) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  double pm[ROWS], ps[ROWS], p2[ROWS];
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const int i = min(r * WAVE + lane, nb - 1);
+    pm[r] = P[3 * i];
+    ps[r] = P[3 * i + 1];
+    p2[r] = want2 ? P[3 * i + 2] : 0.0;
   }
-  if (threadIdx.x == 0 && k1e >= nb) xo[1] = Sf;
+  between();
+  double m = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    pm[r] = r * WAVE + lane < nb ? pm[r] : -INFINITY;
+    m = fmax(m, pm[r]);
+  }
+  Combined o;
+  const double M = wave_max(m);
+  const bool finite = (M > -INFINITY) && (M < INFINITY);
+  o.M = finite ? M : -INFINITY;
+  // block totals T_i = s_i exp(m_i - M) (0 without a finite maximum or weight)
+  double T[ROWS][1];
+  o.S2 = 0.0;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const double e = exp_nonpos(pm[r] - M);
+    const double sc = finite ? e : 0.0;
+    T[r][0] = ps[r] * sc;
+    p2[r] = p2[r] * (sc * sc);
+  }
+  if (want2) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) o.S2 += wave_sum(p2[r]);
+  }
+  combine_scan<ROWS, 1>(T, nb, 1, k1b, span, o);
+  return o;
+}
+
+// 64 < nb <= FUSE_NB partials, the block's waves together.
+template <class Between>
+__device__ __forceinline__ Combined combine_block(const double* __restrict__ P, int nb, int k1b,
+                                                  int span, bool want2, CombineLds& X,
+                                                  Between between) {
+  constexpr int NW = COMB_NT / WAVE, ROWS = NW;
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  double pm[COMB_PER], ps[COMB_PER], p2[COMB_PER];
+#pragma unroll
+  for (int k = 0; k < COMB_PER; ++k) {
+    const int i = min((int)threadIdx.x + k * COMB_NT, nb - 1);
+    pm[k] = P[3 * i];
+    ps[k] = P[3 * i + 1];
+    p2[k] = want2 ? P[3 * i + 2] : 0.0;
+  }
+  between();
+  double m = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < COMB_PER; ++k) {
+    pm[k] = (int)threadIdx.x + k * COMB_NT < nb ? pm[k] : -INFINITY;
+    m = fmax(m, pm[k]);
+  }
+  m = wave_max(m);
+  if (lane == 0) X.xm[wv] = m;
   __syncthreads();
-  Combined c;
-  c.M = finite ? M : -INFINITY;
-  c.S = Sf;
-  c.S2 = S2;
-  c.lo = xo[0];
-  c.hi = xo[1];
-  return c;
+  double M = X.xm[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) M = fmax(M, X.xm[w]);
+  Combined o;
+  const bool finite = (M > -INFINITY) && (M < INFINITY);
+  o.M = finite ? M : -INFINITY;
+  double loc2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < COMB_PER; ++k) {
+    const int i = (int)threadIdx.x + k * COMB_NT;
+    const double e = exp_nonpos(pm[k] - M);
+    const double sc = finite ? e : 0.0;
+    if (i < FUSE_NB) X.T[i + (i >> 4)] = i < nb ? ps[k] * sc : 0.0;
+    if (i < nb) loc2 += p2[k] * (sc * sc);
+  }
+  if (want2) {
+    const double s2w = wave_sum(loc2);
+    if (lane == 0) X.xs2[wv] = s2w;
+  }
+  __syncthreads();
+  o.S2 = 0.0;
+  if (want2) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) o.S2 += X.xs2[w];
+  }
+  const int chunk = (nb + COMB_NT - 1) / COMB_NT;
+  double T[ROWS][COMB_PER];
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+    for (int c = 0; c < COMB_PER; ++c) {
+      const int i = (r * WAVE + lane) * chunk + c;
+      T[r][c] = (c < chunk && i < nb) ? X.T[i + (i >> 4)] : 0.0;
+    }
+  combine_scan<ROWS, COMB_PER>(T, nb, chunk, k1b, span, o);
+  return o;
+}
+
+template <class Between>
+__device__ __forceinline__ Combined combine(const double* __restrict__ P, int nb, int k1b,
+                                            int span, bool want2, CombineLds& X,
+                                            Between between) {
+  if (nb <= WAVE) return combine_wave<1>(P, nb, k1b, span, want2, between);
+  if (nb <= COMB_NT) return combine_wave<COMB_NT / WAVE>(P, nb, k1b, span, want2, between);
+  return combine_block(P, nb, k1b, span, want2, X, between);
 }
 
 // K2 (filters of more than FUSE_NB blocks): one workgroup combines the
@@ -353,26 +451,34 @@ __global__ __launch_bounds__(K2_NT) void k_combine(const double* __restrict__ pa
 
 
 // ---------------------------------------------------------------- K1
-// Observation log-density of one particle, in FP64 from the (FP32 or FP64)
-// state: the residuals are formed after widening the state, so an FP32 path
-// adds no rounding of its own here (a log-weight stored in FP32 would carry
-// ~2^-24 |lw|, above the per-step accuracy once |lw| reaches the hundreds).
-// Components are visited in increasing index, the order of the sorted
-// observation list.
-template <int D, typename Real>
-__device__ __forceinline__ double l96_logdens(const Real (&x)[D], const double* yrow,
-                                              const int32_t* obs_pos, double inv_sd,
-                                              double cst) {
-  double acc = 0.0;
+// A K1 block's partials from its lanes' log-weights: the maximum, the sum and
+// the sum of squares of exp(lw - max), valid in thread 0.  The waves' sums are
+// added in order; two exchanges (a reduction of its own for each of the three
+// took six barriers, 1,850 cycles).  `red` is LDS of 3 K1_NT / WAVE doubles.
+__device__ __forceinline__ void block_partials(double lc, double* red, double& m, double& s1,
+                                               double& s2) {
+  constexpr int NW = K1_NT / WAVE;
+  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+  const double mw = wave_max(lc);
+  if (lane == 0) red[w] = mw;
+  __syncthreads();
+  m = red[0];
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    const int o = obs_pos[i];
-    if (o >= 0) {
-      const double e = (yrow[o] - (double)x[i]) * inv_sd;
-      acc = acc + e * e;
-    }
+  for (int i = 1; i < NW; ++i) m = fmax(m, red[i]);
+  // (without a finite maximum lc - m is -inf or NaN and the weight 0)
+  const double e = exp_nonpos(lc - m);
+  const double a = wave_sum(e), b = wave_sum(e * e);
+  if (lane == 0) {
+    red[NW + w] = a;
+    red[2 * NW + w] = b;
   }
-  return -0.5 * acc + cst;
+  __syncthreads();
+  s1 = s2 = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    s1 += red[NW + i];
+    s2 += red[2 * NW + i];
+  }
 }
 
 // The particle output j continues in this interval (plain layout, every
@@ -389,13 +495,18 @@ __device__ __forceinline__ int64_t plain_ancestor(int64_t j, int32_t* __restrict
                                                   int32_t* __restrict__ anc,
                                                   const PlainArgs& A, int32_t* wtop,
                                                   int32_t* s_js) {
-  const int32_t amode = A.fs->amode;
   const int64_t N = A.N;
+  int32_t* marks = marks_all + A.off;
+  // the mark and the tile's owner are fetched beside the filter's scalars,
+  // wanted or not: one latency instead of two
+  const int32_t mark = j < N ? marks[j] : -1;
+  const int32_t own = owner_all[A.own0 + blockIdx.x];
+  const int32_t amode = A.fs->amode;
+  const int64_t cn1 = A.fs->cn1;
   if (amode == AMODE_IDENTITY) return j;
   if (amode == AMODE_ARRAY) return j < N ? (int64_t)anc[A.off + j] : j;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   const int64_t k0 = (int64_t)blockIdx.x * K1_NT;
-  const int64_t cn1 = A.fs->cn1;
   if (threadIdx.x < WAVE) {
     int found = -1;
     if (k0 + K1_NT > cn1 && cn1 < N) {
@@ -407,12 +518,8 @@ __device__ __forceinline__ int64_t plain_ancestor(int64_t j, int32_t* __restrict
     }
     if (threadIdx.x == 0) *s_js = found;
   }
-  int32_t* marks = marks_all + A.off;
-  int32_t run = k0 < cn1 ? owner_all[A.own0 + blockIdx.x] : -1;
-  if (j < N) {
-    run = max(run, marks[j]);
-    marks[j] = -1;
-  }
+  const int32_t run = max(k0 < cn1 ? own : -1, mark);
+  if (j < N) marks[j] = -1;
   const int32_t incl = wave_incl_max_scan_i(run, lane);
   if (lane == WAVE - 1) wtop[wv] = incl;
   __syncthreads();
@@ -440,7 +547,7 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
                                                             const int32_t* __restrict__ jc,
                                                             int32_t* __restrict__ anc,
                                                             PlainArgs A) {
-  __shared__ double red[K1_NT / WAVE];
+  __shared__ double red[3 * K1_NT / WAVE];
   __shared__ int32_t wtop[K1_NT / WAVE];
   __shared__ int32_t s_js;
   const int64_t j = (int64_t)blockIdx.x * K1_NT + threadIdx.x;
@@ -450,11 +557,11 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
   // interval t gathers buffer (t - 1) % 2 and writes buffer t % 2
   const Real* __restrict__ xcur = ((t - 1) & 1) ? xb : xa;
   Real* __restrict__ xprop = (t & 1) ? xb : xa;
+  const double* __restrict__ yrow = A.obs + (int64_t)(t - 1) * A.n_obs;
   const int64_t src = A.off + plain_ancestor(j, marks, owner, jc, anc, A, wtop, &s_js);
   double l = -INFINITY;
   if (j < A.N) {
     const int64_t col = A.off + j;
-    const double* yrow = A.obs + (int64_t)(t - 1) * A.n_obs;
     const int n0 = (t - 1) * A.K;
     if constexpr (MODEL == 1) {
       if constexpr (sizeof(Real) == 8) {
@@ -492,6 +599,8 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
       Real x[D];
 #pragma unroll
       for (int i = 0; i < D; ++i) x[i] = xcur[pidx(src, i, D)];
+      ObsAhead<D> obs;  // on its way beside the state
+      if constexpr (D <= OBS_AHEAD) obs.fetch(yrow, A.obs_pos);
       if constexpr (sizeof(Real) == 8) {
         const double F = A.theta[0], sq = A.theta[1];
         ModelConsts mc{A.h, A.hh, A.h6, A.inv_sd, A.lw_cst};
@@ -519,7 +628,7 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
 #pragma unroll
         for (int i = 0; i < D; ++i) xprop[pidx(col, i, D)] = (Real)xa[i];
         // the log-weight from the state before it is rounded for storage
-        l = l96_logdens<D, double>(xa, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
+        l = l96_logdens<D, double>(xa, obs, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
       } else {
         const L96F32 c = l96_f32_consts(A.theta[0], A.theta[1], A.h);
         for (int s = 1; s <= A.K; ++s) {
@@ -533,7 +642,7 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
       if constexpr (!ACC || sizeof(Real) == 8) {
 #pragma unroll
         for (int i = 0; i < D; ++i) xprop[pidx(col, i, D)] = x[i];
-        l = l96_logdens<D, Real>(x, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
+        l = l96_logdens<D, Real>(x, obs, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
       }
     }
     // weights kept from a step that did not resample carry over
@@ -542,10 +651,8 @@ __global__ __launch_bounds__(K1_NT) void k_propagate_weight(Real* __restrict__ x
   }
   // a NaN log-weight counts as zero weight
   const double lc = (l == l) ? l : -INFINITY;
-  const double m = block_max<K1_NT>(lc, red);
-  const double e = (m > -INFINITY && m < INFINITY) ? exp_nonpos(lc - m) : 0.0;
-  const double s1 = block_sum<K1_NT>(e, red);
-  const double s2 = block_sum<K1_NT>(e * e, red);
+  double m, s1, s2;
+  block_partials(lc, red, m, s1, s2);
   if (threadIdx.x == 0) {
     double* p = part + 3 * (A.boff0 + blockIdx.x);
     p[0] = m;
@@ -566,15 +673,13 @@ __global__ __launch_bounds__(K1_NT) void k_lw_partials(const double* __restrict_
                                                        double* __restrict__ part,
                                                        int32_t* __restrict__ marks, double u,
                                                        PlainArgs A) {
-  __shared__ double red[K1_NT / WAVE];
+  __shared__ double red[3 * K1_NT / WAVE];
   const int64_t j = (int64_t)blockIdx.x * K1_NT + threadIdx.x;
   const double l = j < A.N ? lw[j] : -INFINITY;
   if (j < A.N) marks[j] = -1;
   const double lc = (l == l) ? l : -INFINITY;  // a NaN log-weight counts as zero weight
-  const double m = block_max<K1_NT>(lc, red);
-  const double e = (m > -INFINITY && m < INFINITY) ? exp_nonpos(lc - m) : 0.0;
-  const double s1 = block_sum<K1_NT>(e, red);
-  const double s2 = block_sum<K1_NT>(e * e, red);
+  double m, s1, s2;
+  block_partials(lc, red, m, s1, s2);
   if (threadIdx.x == 0) {
     double* p = part + 3 * (int64_t)blockIdx.x;
     p[0] = m;
@@ -611,6 +716,9 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 // next block's first particle; the block's last lane records them, because
 // only it knows that count.  Strata past the last particle's count (rounding
 // overflow) go to the last particle of positive weight (jstar).
+// FUSED: the block's waves combine the partials themselves, and (but in mode
+// 1) the launch has one block more, the first, that does the filter's
+// bookkeeping: its two logarithms and division, on another CU's time.
 template <bool FUSED>
 __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ lw,
                                                      const double* __restrict__ part,
@@ -621,68 +729,86 @@ __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ 
                                                      PlainArgs A) {
   constexpr int NW = K3_NT / WAVE;
   __shared__ double xsum[NW], xvmax[NW];
-  __shared__ int64_t xcnt[NW];
   __shared__ int xcand[NW];
-  const int64_t N = A.N;
-  const int64_t jb = (int64_t)blockIdx.x * K3_SPAN;
-  const int64_t j0 = jb + (int64_t)threadIdx.x * K3_PER;
+  __shared__ CombineLds X;
+  const int blk = (int)blockIdx.x - (FUSED && A.mode != 1 ? 1 : 0);
+  const int32_t N = (int32_t)A.N;
+  FilterState* fst = A.fs;
+  const Key key = key_of(A.key);
+  if (FUSED && blk < 0) {
+    int32_t t;
+    double lprev, u;
+    const Combined cb = combine(part + 3 * A.boff0, A.nblk, 0, 1, true, X, [&] {
+      t = fst->tk;  // the interval K1 just propagated
+      lprev = fst->carry ? fst->lprev : log((double)N);
+      // mode 0 draws the resampling uniform, mode 2 has it in the scalars
+      u = A.mode == 0 ? u01_f64(draw(key, TAG_RESAMPLE, 0, fst->iter, 0, (uint32_t)t, A.b).x)
+                      : fst->u;
+    });
+    const bool pos = (cb.M > -INFINITY) && (cb.M < INFINITY) && (cb.S > 0.0);
+    const double ess = pos ? (cb.S * cb.S) / cb.S2 : 0.0;
+    if (threadIdx.x != 0) return;
+    // likelihood increment (the normaliser is ln N after a resampling, else
+    // the carried weights' ln sum exp), ESS, trigger (resample when ESS <
+    // ess_frac N), uniform, traces, and the interval counter
+    double ell;
+    if (pos) {
+      const double L = cb.M + log(cb.S);
+      ell = L - lprev;
+      fst->lprev = L;
+    } else {
+      ell = -INFINITY;
+      fst->status = 4;
+    }
+    fst->carry = pos && !(ess < A.rs.ess_frac * (double)N);
+    fst->loglik = fst->loglik + ell;
+    fst->M = cb.M;
+    fst->S = cb.S;
+    fst->ell = ell;
+    fst->ess = ess;
+    fst->u = u;
+    A.ell_tr[t - 1] = ell;
+    A.ess_tr[t - 1] = ess;
+    fst->t = t;
+    return;
+  }
+  // no cumulative weights needed
+  if (A.rs.scheme == RS_METROPOLIS || A.rs.scheme == RS_REJECTION) return;
+  const int32_t jb = blk * K3_SPAN;
+  const int32_t j0 = jb + (int)threadIdx.x * K3_PER;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   // the lane's K3_PER consecutive log-weights, loaded first so that they
   // arrive while the partials are combined (past the end they reread the
   // last weight)
   double lv[K3_PER];
 #pragma unroll
-  for (int e = 0; e < K3_PER; ++e) lv[e] = lw[A.off + min(j0 + e, N - 1)];
-  FilterState* fst = A.fs;
-  const int32_t t_now = fst->tk;  // the interval K1 just propagated
-  const uint32_t it_now = fst->iter;
-  const Key key = key_of(A.key);
-  const int k1b = (int)blockIdx.x * (K3_SPAN / K1_NT);  // first K1 block of this block
+  for (int e = 0; e < K3_PER; ++e) lv[e] = lw[A.off + min((int64_t)j0 + e, (int64_t)N - 1)];
+  const int k1b = blk * (K3_SPAN / K1_NT);  // first K1 block of this block
   double M, S, u, lo_off, hi_off;
   bool pos, carry;
+  int32_t t_now;
+  uint32_t it_now;
   if constexpr (FUSED) {
-    // mode 0 draws the resampling uniform (while the partials load); modes 1
-    // and 2 take the uniform already in the filter's scalars (1 redraws only
-    // the ancestors, 2 also does the bookkeeping)
-    u = A.mode == 0 ? u01_f64(draw(key, TAG_RESAMPLE, 0, it_now, 0, (uint32_t)t_now, A.b).x)
-                    : fst->u;
-    const Combined cb =
-        combine_block_lds<K3_NT, FUSE_NB>(part + 3 * A.boff0, A.nblk, k1b, K3_SPAN / K1_NT);
+    const Combined cb = combine(
+        part + 3 * A.boff0, A.nblk, k1b, K3_SPAN / K1_NT, A.rs.ess_frac < INFINITY, X, [&] {
+          t_now = fst->tk;
+          it_now = fst->iter;
+          // modes 1 and 2 take the uniform already in the filter's scalars
+          // (1 redraws only the ancestors)
+          u = A.mode == 0
+                  ? u01_f64(draw(key, TAG_RESAMPLE, 0, it_now, 0, (uint32_t)t_now, A.b).x)
+                  : fst->u;
+        });
     M = cb.M;
     S = cb.S;
     lo_off = cb.lo;
     hi_off = cb.hi;
     pos = (M > -INFINITY) && (M < INFINITY) && (S > 0.0);
-    const double ess = pos ? (S * S) / cb.S2 : 0.0;
-    // resample when ESS < ess_frac N
-    carry = pos && !(ess < A.rs.ess_frac * (double)N);
-    if (A.mode != 1 && blockIdx.x == 0 && threadIdx.x == 0) {
-      // the filter's bookkeeping: likelihood increment (the normaliser is
-      // ln N after a resampling, else the carried weights' ln sum exp), ESS,
-      // trigger, uniform, traces, and the interval counter
-      const double lprev = fst->carry ? fst->lprev : log((double)N);
-      double ell;
-      if (pos) {
-        const double L = M + log(S);
-        ell = L - lprev;
-        fst->lprev = L;
-      } else {
-        ell = -INFINITY;
-        fst->status = 4;
-      }
-      fst->carry = carry;
-      fst->loglik = fst->loglik + ell;
-      fst->M = M;
-      fst->S = S;
-      fst->ell = ell;
-      fst->ess = ess;
-      fst->u = u;
-      A.ell_tr[t_now - 1] = ell;
-      A.ess_tr[t_now - 1] = ess;
-      fst->t = t_now;
-    }
+    carry = pos && A.rs.ess_frac < INFINITY && !((S * S) / cb.S2 < A.rs.ess_frac * (double)N);
   } else {
     // K2 has combined the partials and done the bookkeeping
+    t_now = fst->tk;
+    it_now = fst->iter;
     M = fst->M;
     S = fst->S;
     u = fst->u;
@@ -692,39 +818,28 @@ __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ 
     lo_off = bo[k1b];
     hi_off = bo[min(k1b + K3_SPAN / K1_NT, A.nblk)];
   }
-  // no cumulative weights needed
-  if (A.rs.scheme == RS_METROPOLIS || A.rs.scheme == RS_REJECTION) return;
   // a step that keeps its weights (ESS above the trigger) or has none
   // positive gives every particle one offspring: itself
   const bool finite = pos && !carry;
   const double invS = 1.0 / S;
-  const bool strat = A.rs.scheme == RS_STRATIFIED;
-  auto count = [&](double W) -> int64_t {
-    return strat ? stratum_count_strat(W, S, invS, (int32_t)N, key, t_now, A.b, it_now)
-                 : stratum_count(W, S, invS, u, (int32_t)N);
-  };
   // in-lane sequential prefix of K3_PER consecutive weights, and the lane's
   // last particle of positive weight (for the rare case where rounding
   // leaves the final strata without an owner)
-  double w[K3_PER], loc[K3_PER];
+  double loc[K3_PER];
   double run = 0.0;
   int cand = -1;
 #pragma unroll
   for (int e = 0; e < K3_PER; ++e) {
-    const int64_t j = j0 + e;
-    double we = 0.0;
-    if (j < N && finite) {
-      const double l = lv[e];
-      we = (l == l) ? exp_nonpos(l - M) : 0.0;
-    }
-    w[e] = we;
-    if (we > 0.0) cand = (int)j;
-    run += we;
+    const bool in = j0 + e < N && lv[e] == lv[e];
+    const double we = exp_nonpos((in ? lv[e] : -INFINITY) - M);
+    const double w = finite ? we : 0.0;
+    cand = w > 0.0 ? j0 + e : cand;
+    run += w;
     loc[e] = run;
   }
   // exchange 1: the lanes' sums scanned across the block (and the block's
   // candidate, which only lane 0 needs)
-  const double incl = wave_incl_scan(run, lane);
+  const double incl = wave_incl_scan(run);
   const int cw = wave_max_i(cand);
   if (lane == WAVE - 1) xsum[wv] = incl;
   if (lane == 0) xcand[wv] = cw;
@@ -739,7 +854,7 @@ __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ 
   // exchange 2: an exact running maximum over earlier lanes keeps W
   // non-decreasing across lanes whatever the rounding of the tree scan;
   // capped by the next offset
-  const double vin = wave_incl_max_scan(V[K3_PER - 1], lane);
+  const double vin = wave_incl_max_scan(V[K3_PER - 1]);
   const double vup = wave_prev(vin, -INFINITY);
   if (lane == WAVE - 1) xvmax[wv] = vin;
   __syncthreads();
@@ -748,86 +863,86 @@ __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ 
   for (int q = 0; q < NW; ++q)
     if (q < wv) vw = fmax(vw, xvmax[q]);
   const double vprev = lane > 0 ? fmax(vup, vw) : (wv > 0 ? vw : lo_off);
-  int64_t c[K3_PER];
+  // W[e + 1]: particle e's cumulative weight; W[0]: the one before the lane's
+  // first (the previous lane's last, or this block's offset); then the next
+  // block's offset.  Their stratum counts c: particle e owns the strata
+  // [c[e], c[e + 1]), and those up to c[K3_PER + 1] below the next block's
+  // first count belong to its first particle: this block's last lane records
+  // them, because only it knows its own last count.
+  double W[K3_PER + 2];
+  W[0] = fmin(vprev, hi_off);
 #pragma unroll
-  for (int e = 0; e < K3_PER; ++e) {
-    const int64_t j = j0 + e;
-    const double W = fmin(fmax(V[e], vprev), hi_off);
-    c[e] = (j < N) ? (finite ? count(W) : j + 1) : 0;
-    if (A.rs.scheme == RS_MULTINOMIAL && j < N) A.wcum[j] = W;
+  for (int e = 0; e < K3_PER; ++e) W[e + 1] = fmin(fmax(V[e], vprev), hi_off);
+  W[K3_PER + 1] = hi_off;
+  if (A.rs.scheme == RS_MULTINOMIAL) {
+#pragma unroll
+    for (int e = 0; e < K3_PER; ++e)
+      if (j0 + e < N) A.wcum[j0 + e] = W[e + 1];
   }
-  // the strata counts at this block's edges (the same function of the same
-  // offset values as the neighbouring blocks compute)
-  const int64_t g_lo = finite ? count(lo_off) : jb;
-  const int64_t jnext = jb + K3_SPAN;
-  const int64_t g_hi = (jnext < N) ? (finite ? count(hi_off) : jnext) : N;
-  // exchange 3: each lane's first particle continues from the previous
-  // lane's last count
-  const int64_t cup = wave_prev_i64(c[K3_PER - 1], 0);
-  if (lane == WAVE - 1) xcnt[wv] = c[K3_PER - 1];
-  __syncthreads();
-  int64_t cprev = lane > 0 ? cup : (wv > 0 ? xcnt[wv - 1] : g_lo);
-  // strata [rlo, rhi) owned by particle rj: one range per particle, plus,
-  // for the block's last particle, the strata below the next block's first
-  // count, which belong to the next block's first particle
-  int64_t rj[K3_PER + 1], rlo[K3_PER + 1], rhi[K3_PER + 1];
+  // the lane before the next block, if there is one
+  const bool ends = threadIdx.x == K3_NT - 1 && (int64_t)jb + K3_SPAN < N;
+  int32_t c[K3_PER + 2];
+  if (!finite) {
 #pragma unroll
-  for (int e = 0; e <= K3_PER; ++e) {
-    rj[e] = 0;
-    rlo[e] = 0;
-    rhi[e] = 0;  // empty
-  }
+    for (int e = 0; e <= K3_PER; ++e) c[e] = j0 + e;
+    c[K3_PER + 1] = c[K3_PER];
+  } else if (A.rs.scheme == RS_STRATIFIED) {
+    auto count = [&](double w) -> int32_t {
+      return stratum_count_strat(w, S, invS, N, key, t_now, A.b, it_now);
+    };
 #pragma unroll
-  for (int e = 0; e < K3_PER; ++e) {
-    const int64_t j = j0 + e;
-    if (j < N) {
-      rj[e] = j;
-      rlo[e] = cprev;
-      rhi[e] = c[e];
-      if (j == N - 1) {
-        fst->cn1 = (int32_t)c[e];
-      } else if (j == jnext - 1) {
-        rj[K3_PER] = j + 1;
-        rlo[K3_PER] = c[e];
-        rhi[K3_PER] = g_hi;
-      }
-    }
-    cprev = c[e];
+    for (int e = 0; e <= K3_PER; ++e) c[e] = j0 < N ? count(W[e]) : 0;
+    c[K3_PER + 1] = ends ? count(hi_off) : 0;
+  } else {
+    stratum_counts(W, S, invS, u, N, j0 < N ? (ends ? K3_PER + 2 : K3_PER + 1) : 0, c);
   }
   if (A.rs.scheme != RS_MULTINOMIAL) {
     int32_t* marks = marks_all + A.off;
     int32_t* owner = owner_all + A.own0;
-    if (threadIdx.x == 0) fst->amode = AMODE_MARKS;  // the next propagation reads them
+    if (blk == 0 && threadIdx.x == 0) fst->amode = AMODE_MARKS;  // for the next propagation
+    // ranges [rlo, rhi) of particle j0 + e (e = K3_PER: the next block's first)
+    int32_t rlo[K3_PER + 1], rhi[K3_PER + 1];
 #pragma unroll
-    for (int e = 0; e <= K3_PER; ++e)
-      if (rlo[e] < rhi[e]) marks[rlo[e]] = (int32_t)rj[e];
+    for (int e = 0; e <= K3_PER; ++e) {
+      const bool in = e < K3_PER ? j0 + e < N : ends;
+      rlo[e] = in ? c[e] : 0;
+      rhi[e] = in ? c[e + 1] : 0;
+      if (rlo[e] < rhi[e]) marks[rlo[e]] = j0 + e;
+    }
     // Tile q's first stratum q K4_TILE lies in at most one range.  A range
     // covering at most two tile starts is stored by its lane; a longer one
     // (a particle owning many strata) by the whole wave, strided over the
     // lanes, so no lane loops over hundreds of tiles.
 #pragma unroll
     for (int e = 0; e <= K3_PER; ++e) {
-      const int64_t first = (rlo[e] + K4_TILE - 1) / K4_TILE;
-      const int64_t last = rhi[e] > rlo[e] ? (rhi[e] - 1) / K4_TILE : first - 1;
+      const int32_t first = (int32_t)(((uint32_t)rlo[e] + (K4_TILE - 1)) / K4_TILE);
+      const int32_t last = rhi[e] > rlo[e] ? (rhi[e] - 1) / K4_TILE : first - 1;
+      if (__ballot(first <= last) == 0) continue;
       const bool big = last - first + 1 > 2;
       if (!big)
-        for (int64_t q = first; q <= last; ++q) owner[q] = (int32_t)rj[e];
+        for (int32_t q = first; q <= last; ++q) owner[q] = j0 + e;
       uint64_t mask = __ballot(big);
       while (mask) {
         const int src = __ffsll((unsigned long long)mask) - 1;
         mask &= mask - 1;
-        const long long bj = __shfl((long long)rj[e], src, WAVE);
-        const long long bq0 = __shfl((long long)first, src, WAVE);
-        const long long bq1 = __shfl((long long)last, src, WAVE);
-        for (long long q = bq0 + lane; q <= bq1; q += WAVE) owner[q] = (int32_t)bj;
+        const int32_t bj = __builtin_amdgcn_readlane(j0 + e, src);
+        const int32_t bq0 = __builtin_amdgcn_readlane(first, src);
+        const int32_t bq1 = __builtin_amdgcn_readlane(last, src);
+        for (int64_t q = (int64_t)bq0 + lane; q <= bq1; q += WAVE) owner[q] = bj;
       }
     }
+  }
+  if (j0 < N && N - j0 <= K3_PER) {  // the lane of the last particle
+    int32_t cn1 = c[1];
+#pragma unroll
+    for (int e = 1; e < K3_PER; ++e) cn1 = j0 + e == N - 1 ? c[e + 1] : cn1;
+    fst->cn1 = cn1;
   }
   if (threadIdx.x == 0) {
     int cb = xcand[0];
 #pragma unroll
     for (int q = 1; q < NW; ++q) cb = max(cb, xcand[q]);
-    jc_all[A.own0 + blockIdx.x] = cb;
+    jc_all[A.own0 + blk] = cb;
   }
 }
 
@@ -1146,7 +1261,7 @@ hipError_t launch_scan_mark(const double* lw, const double* part, const double* 
                             hipStream_t s) {
   const unsigned g = nblocks(a.N, K3_SPAN);
   if (a.nblk <= FUSE_NB)
-    hipLaunchKernelGGL(k_scan_mark<true>, g, K3_NT, 0, s, lw, part, boff, marks, owner, jc, a);
+    hipLaunchKernelGGL(k_scan_mark<true>, g + (a.mode != 1 ? 1 : 0), K3_NT, 0, s, lw, part, boff, marks, owner, jc, a);
   else
     hipLaunchKernelGGL(k_scan_mark<false>, g, K3_NT, 0, s, lw, part, boff, marks, owner, jc, a);
   return hipGetLastError();

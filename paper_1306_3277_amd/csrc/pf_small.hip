@@ -49,12 +49,6 @@ struct SmallOut {
   bool finite, pos, carry;
 };
 
-__device__ __forceinline__ double lane_val(double v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // The collective over one workgroup's log-weights l (row layout; particles
 // past N are ignored): likelihood sums, the resampling decision and, for
 // every output of the rows, its ancestor.  `between` runs after the first
@@ -119,8 +113,8 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
     o.M = M;
     o.S = fmax(last_lane(incl), last_lane(vin));
     const int k1b = w & ~3, k1e = k1b + 4;
-    lo_off = lane_val(off, k1b);
-    hi_off = k1e < nb ? lane_val(off, k1e) : o.S;
+    lo_off = lane_value(off, k1b);
+    hi_off = k1e < nb ? lane_value(off, k1e) : o.S;
   }
   const double M = o.M, S = o.S;
   o.pos = o.finite && S > 0.0;
@@ -498,7 +492,7 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
       const double head = R[min(lane, SMALL_MAXK - 1) + REC_HEAD];  // c q of substep `lane`
 #pragma unroll
       for (int s = 0; s < AHEAD; ++s)
-        if (s < K) substep(lane_val(head, s), zn[s]);
+        if (s < K) substep(lane_value(head, s), zn[s]);
       const Real* zi = nz + (int64_t)i * K * step + ROWS * lane;
       for (int s0 = AHEAD; s0 < K; s0 += 4) {
         Row4 z[4];
@@ -556,10 +550,10 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
           ess_tr[t0 + i - k + lane] = ess;
         }
         none = none || __ballot(in && !pos) != 0;
-        for (int q = 0; q <= k; ++q) loglik = loglik + lane_val(ell, q);
-        lprev = lane_val(L, k);
-        ell_last = lane_val(ell, k);
-        ess_last = lane_val(ess, k);
+        for (int q = 0; q <= k; ++q) loglik = loglik + lane_value(ell, q);
+        lprev = lane_value(L, k);
+        ell_last = lane_value(ell, k);
+        ess_last = lane_value(ess, k);
         carry_before = o.carry;
       }
     }
