@@ -67,9 +67,50 @@ __device__ __forceinline__ uint4 draw(Key key, uint32_t tag, uint32_t blk, uint3
 // ---------------------------------------------------------------- FP64 normals
 // u = (w + 1/2) 2^-32; ln from the atanh series on [sqrt(1/2), sqrt(2));
 // sin/cos of 2 pi u by quarter-turn reduction and Taylor series; radius
-// sqrt(-2 ln u_a).  IEEE +, -, *, / and sqrt only, so the host and the device
-// produce the same bits.
-__device__ __forceinline__ double u01_f64(uint32_t w) { return ((double)w + 0.5) * 0x1p-32; }
+// sqrt(-2 ln u_a).  Every value is that of IEEE +, -, *, / and sqrt in the
+// order the oracle writes them, so the host and the device produce the same
+// bits.  What is exact is not spent operations on: sums with an exact product
+// are one fused operation, the quarter turn is taken from the integer, and the
+// quotient and the root, whose arguments lie well inside the exponent range,
+// take the Newton (Markstein) iterations without the scaling, the special
+// cases and the selects of the general ones.  About 93 instructions a pair
+// against 115 (checked for every 32-bit word); the normals are two thirds of an
+// FP64 propagation.
+__device__ __forceinline__ double u01_f64(uint32_t w) {
+  return __builtin_fma((double)w, 0x1p-32, 0x1p-33);  // exact
+}
+
+// a / b, correctly rounded, for 2^-500 < |b| < 2^500 and a quotient (or a
+// zero a) as far from the ends of the range: the reciprocal by two Newton
+// steps, then the quotient corrected by its remainder.
+__device__ __forceinline__ double div_mid(double a, double b) {
+  double y = __builtin_amdgcn_rcp(b);
+  y = __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
+  y = __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
+  const double q = a * y;
+  return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// a / b from the correctly rounded reciprocal y of b, in the same range: the
+// remainder's correction then gives the correctly rounded quotient (Markstein,
+// IBM J. Res. Dev. 34, 1990).
+__device__ __forceinline__ double div_by(double a, double b, double y) {
+  const double q = a * y;
+  return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// sqrt(x), correctly rounded, for 2^-500 < x < 2^500: Goldschmidt's coupled
+// iteration for root and half reciprocal root, then two corrections by the
+// remainder.
+__device__ __forceinline__ double sqrt_mid(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, r, g);
+  h = __builtin_fma(h, r, h);
+  g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
 
 __device__ __forceinline__ double ln_f64(double x) {
   uint64_t bits = (uint64_t)__double_as_longlong(x);
@@ -79,7 +120,7 @@ __device__ __forceinline__ double ln_f64(double x) {
     f = f + f;
     e = e - 1;
   }
-  const double s = (f - 1.0) / (f + 1.0);
+  const double s = div_mid(f - 1.0, f + 1.0);
   const double s2 = s * s;
   double p = 1.0 / 21.0;
   p = p * s2 + 1.0 / 19.0;
@@ -92,16 +133,17 @@ __device__ __forceinline__ double ln_f64(double x) {
   p = p * s2 + 1.0 / 5.0;
   p = p * s2 + 1.0 / 3.0;
   p = p * s2 + 1.0;
-  const double lnf = (2.0 * s) * p;
   const double de = (double)e;
-  return de * 0x1.62e42feep-1 + (de * 0x1.a39ef35793c76p-33 + lnf);
+  // ln f = 2 s p; both doublings and de times the 32-bit head of ln 2 are exact
+  return __builtin_fma(de, 0x1.62e42feep-1,
+                       __builtin_fma(2.0, s * p, de * 0x1.a39ef35793c76p-33));
 }
 
-__device__ __forceinline__ void sincos2pi_f64(double u, double& s_out, double& c_out) {
-  const double v = 4.0 * u;
-  const double kf = __builtin_floor(v + 0.5);
-  const double f = v - kf;
-  const int k = ((int)kf) & 3;
+// sin and cos of 2 pi (w + 1/2) 2^-32
+__device__ __forceinline__ void sincos2pi_f64(uint32_t w, double& s_out, double& c_out) {
+  // the nearest quarter turn, and what is left of it: f in [-1/2, 1/2)
+  const uint32_t k = (w + 0x20000000u) >> 30;  // mod 4
+  const double f = __builtin_fma((double)(int32_t)(w - (k << 30)), 0x1p-30, 0x1p-31);
   const double p = f * 0x1.921fb54442d18p0;
   const double p2 = p * p;
   double sp = -1.0 / 121645100408832000.0;
@@ -125,18 +167,19 @@ __device__ __forceinline__ void sincos2pi_f64(double u, double& s_out, double& c
   cp = cp * p2 + 1.0 / 24.0;
   cp = cp * p2 - 1.0 / 2.0;
   cp = cp * p2 + 1.0;
+  // quarter turns 1 and 3 exchange the two; sin changes sign in 2 and 3, cos
+  // in 1 and 2 (sign bits by integer operations)
   const bool odd = (k & 1) != 0;
-  const double s0 = odd ? cp : sp;
-  const double c0 = odd ? -sp : cp;
-  const bool neg = (k & 2) != 0;
-  s_out = neg ? -s0 : s0;
-  c_out = neg ? -c0 : c0;
+  const double s0 = odd ? cp : sp, c0 = odd ? sp : cp;
+  const uint32_t ss = (k << 30) & 0x80000000u, cs = ((k + 1) << 30) & 0x80000000u;
+  s_out = __hiloint2double((int)((uint32_t)__double2hiint(s0) ^ ss), __double2loint(s0));
+  c_out = __hiloint2double((int)((uint32_t)__double2hiint(c0) ^ cs), __double2loint(c0));
 }
 
 __device__ __forceinline__ void bm_pair_f64(uint32_t wa, uint32_t wb, double& z0, double& z1) {
-  const double r = __builtin_sqrt(-2.0 * ln_f64(u01_f64(wa)));
+  const double r = sqrt_mid(-2.0 * ln_f64(u01_f64(wa)));
   double s, c;
-  sincos2pi_f64(u01_f64(wb), s, c);
+  sincos2pi_f64(wb, s, c);
   z0 = r * c;
   z1 = r * s;
 }
@@ -243,7 +286,8 @@ __device__ __forceinline__ void l96_substep_f64(double (&x)[D], double F, double
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const int i = 4 * blk + m;
-      const double xn = x[i] + mc.h6 * (s14[i] + 2.0 * s23[i]);
+      // (2 s23 is exact)
+      const double xn = x[i] + mc.h6 * __builtin_fma(2.0, s23[i], s14[i]);
       x[i] = xn + sq * z[m];
     }
   }
@@ -484,12 +528,23 @@ __device__ __forceinline__ void l96_substep_stage_f64(double (&x)[D], double F, 
                                                       uint32_t tag, uint32_t iter, uint32_t j,
                                                       uint32_t n, uint32_t b) {
   double Fi[D];
+  // h is the same for every quotient: two operations each with its reciprocal
+  // (z is between 2^-70 and 8 in size; sq and h well inside the range)
+  const double inv_h = 1.0 / mc.h, as = __builtin_fabs(sq);
+  const bool mid = mc.h > 0x1p-100 && mc.h < 0x1p100 && as > 0x1p-300 && as < 0x1p300;
 #pragma unroll
   for (int blk = 0; blk < D / 4; ++blk) {
     double z[4];
     normals4_f64(draw(key, tag, blk, iter, j, n, b), z);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) Fi[4 * blk + m] = F + (sq * z[m]) / mc.h;
+    for (int m = 0; m < 4; ++m) Fi[4 * blk + m] = sq * z[m];
+  }
+  if (mid) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) Fi[i] = F + div_by(Fi[i], mc.h, inv_h);
+  } else {
+#pragma unroll
+    for (int i = 0; i < D; ++i) Fi[i] = F + Fi[i] / mc.h;
   }
   double k[D], xt[D], s14[D], s23[D];
   l96_drift_vec_f64<D>(x, Fi, k);
@@ -514,7 +569,7 @@ __device__ __forceinline__ void l96_substep_stage_f64(double (&x)[D], double F, 
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     s14[i] = s14[i] + k[i];
-    x[i] = x[i] + mc.h6 * (s14[i] + 2.0 * s23[i]);
+    x[i] = x[i] + mc.h6 * __builtin_fma(2.0, s23[i], s14[i]);  // (2 s23 is exact)
   }
 }
 
