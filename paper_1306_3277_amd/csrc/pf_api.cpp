@@ -260,11 +260,16 @@ struct pf_handle {
   // the groups' parts of the fused launch tables, for 256 and 512 threads
   std::vector<int32_t> grp_fused0[2], grp_nfused[2];
   int64_t scanned[2] = {0, 0};  // particles that a fused launch of all groups scans
-  // with G > 1 groups, group g's kernels run on side[g]; ev_a[0] forks the
-  // side streams from the caller's, ev_b[g] joins group g back.  These
-  // events are only ever recorded and waited on outside stream capture.
+  // With G > 1 groups, group 0's kernels run on the caller's stream and group
+  // g's on side[g - 1]; ev_fork forks the side streams from the caller's,
+  // ev_join[g - 1] joins group g back.  These events are only ever recorded
+  // and waited on outside stream capture.  (The device runs a process's
+  // streams on four queues; a second one for every handle put both groups of
+  // some handles on one: 12.6 against 9.4 ms for the second of three handles
+  // of 512 filters in two groups, T = 100.)
   std::vector<hipStream_t> side;
-  std::vector<hipEvent_t> ev_a, ev_b;
+  hipEvent_t ev_fork = nullptr;
+  std::vector<hipEvent_t> ev_join;
   // timing
   bool timing = false;
   struct Ev {
@@ -281,7 +286,6 @@ struct pf_handle {
   // batched layout: pf_graph_run issues its intervals as eager launches
   // (the autotuner found them faster than the graph replay on this host)
   bool eager_replay = false;
-  hipStream_t cap_stream = nullptr;
   // attached history (ancestry storage), or null
   char* hist = nullptr;
   // resampling variant and ESS trigger (default: systematic, every time)
@@ -565,26 +569,31 @@ pf_status enqueue_group(pf_handle* H, int g, hipStream_t s, int n) {
   return PF_OK;
 }
 
-// Fork the filter groups' streams from s (they start after everything
-// issued on s so far) and join them back into s.  Never used inside a
-// capture.
+// Fork the side streams from s (they start after everything issued on s so
+// far) and join them back into s.  Never used inside a capture.
 pf_status fork_groups(pf_handle* H, hipStream_t s) {
-  HIP_TRY(hipEventRecord(H->ev_a[0], s));
-  for (int g = 0; g < H->groups; ++g) HIP_TRY(hipStreamWaitEvent(H->side[g], H->ev_a[0], 0));
+  HIP_TRY(hipEventRecord(H->ev_fork, s));
+  for (int g = 1; g < H->groups; ++g)
+    HIP_TRY(hipStreamWaitEvent(H->side[g - 1], H->ev_fork, 0));
   return PF_OK;
 }
 pf_status join_groups(pf_handle* H, hipStream_t s) {
-  for (int g = 0; g < H->groups; ++g) {
-    HIP_TRY(hipEventRecord(H->ev_b[g], H->side[g]));
-    HIP_TRY(hipStreamWaitEvent(s, H->ev_b[g], 0));
+  for (int g = 1; g < H->groups; ++g) {
+    HIP_TRY(hipEventRecord(H->ev_join[g - 1], H->side[g - 1]));
+    HIP_TRY(hipStreamWaitEvent(s, H->ev_join[g - 1], 0));
   }
   return PF_OK;
+}
+// the stream of group g in a run issued from s
+hipStream_t group_stream(const pf_handle* H, int g, hipStream_t s) {
+  return g == 0 ? s : H->side[g - 1];
 }
 
 // n intervals of the batched layout issued eagerly from stream s.  With one
 // group both kernels go on s.  With G groups (filters dealt so that every
 // group holds about the same number of particles) group g's intervals run
-// back to back on side[g]: the groups start together after everything
+// back to back on a stream of its own (group 0's on s): the groups start
+// together after everything
 // issued on s so far, drift against each other, and one group's collective
 // overlaps another's propagation; s waits for every group at the end.  The
 // launches are issued in turn across the groups, so no group
@@ -596,7 +605,7 @@ pf_status enqueue_batched(pf_handle* H, hipStream_t s, int n) {
   if ((st = fork_groups(H, s))) return st;
   for (int i = 0; i < 2 * n; ++i)
     for (int g = 0; g < G; ++g)
-      if (i < group_launches(H, g, n) && (st = enqueue_group_launch(H, g, H->side[g], n, i)))
+      if (i < group_launches(H, g, n) && (st = enqueue_group_launch(H, g, group_stream(H, g, s), n, i)))
         return st;
   return join_groups(H, s);
 }
@@ -845,17 +854,17 @@ pf_status build_groups(pf_handle* H, int G) {
                            hipMemcpyHostToDevice, H->stream));
   }
   HIP_TRY(hipStreamSynchronize(H->stream));
-  // a stream and two events per group (default priority); graphs captured
-  // for another group count are rebuilt
-  while (G > 1 && (int)H->side.size() < G) {
+  // a stream and an event per group beyond the first (default priority);
+  // graphs captured for another group count are rebuilt
+  if (G > 1 && !H->ev_fork)
+    HIP_TRY(hipEventCreateWithFlags(&H->ev_fork, hipEventDisableTiming));
+  while ((int)H->side.size() < G - 1) {
+    hipEvent_t ej;
+    HIP_TRY(hipEventCreateWithFlags(&ej, hipEventDisableTiming));
+    H->ev_join.push_back(ej);
     hipStream_t st;
     HIP_TRY(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
     H->side.push_back(st);
-    hipEvent_t ea, eb;
-    HIP_TRY(hipEventCreateWithFlags(&ea, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&eb, hipEventDisableTiming));
-    H->ev_a.push_back(ea);
-    H->ev_b.push_back(eb);
   }
   if (G != H->groups) destroy_graphs(H);
   H->groups = G;
@@ -863,20 +872,20 @@ pf_status build_groups(pf_handle* H, int G) {
 }
 
 void destroy_graphs(pf_handle* H) {
-  for (auto g : H->gexecs) (void)hipGraphExecDestroy(g);
-  for (auto g : H->graphs) (void)hipGraphDestroy(g);
+  for (auto g : H->gexecs)
+    if (g) (void)hipGraphExecDestroy(g);
+  for (auto g : H->graphs)
+    if (g) (void)hipGraphDestroy(g);
   H->gexecs.clear();
   H->graphs.clear();
   H->gnv = 0;
 }
 
-// Waits for everything the handle has issued: its stream, the capture stream,
-// and the group streams.  Graphs, streams and events are only
-// destroyed after this, so none is destroyed while work that uses it is in
-// flight.
+// Waits for everything the handle has issued: its stream and the side
+// streams.  Graphs, streams and events are only destroyed after this, so none
+// is destroyed while work that uses it is in flight.
 pf_status drain(pf_handle* H) {
   HIP_TRY(hipStreamSynchronize(H->stream));
-  if (H->cap_stream) HIP_TRY(hipStreamSynchronize(H->cap_stream));
   for (auto s : H->side) HIP_TRY(hipStreamSynchronize(s));
   return PF_OK;
 }
@@ -884,79 +893,84 @@ pf_status drain(pf_handle* H) {
 void destroy_streams(pf_handle* H) {
   destroy_graphs(H);
   for (auto s : H->side) (void)hipStreamDestroy(s);
-  for (auto e : H->ev_a) (void)hipEventDestroy(e);
-  for (auto e : H->ev_b) (void)hipEventDestroy(e);
-  if (H->cap_stream) (void)hipStreamDestroy(H->cap_stream);
+  for (auto e : H->ev_join) (void)hipEventDestroy(e);
+  if (H->ev_fork) (void)hipEventDestroy(H->ev_fork);
   H->side.clear();
-  H->ev_a.clear();
-  H->ev_b.clear();
-  H->cap_stream = nullptr;
+  H->ev_join.clear();
+  H->ev_fork = nullptr;
 }
 
-// The stream graphs are captured on: the caller's, or one of our own when the
-// caller uses the null stream (which cannot be captured).  They are launched
-// on the caller's in either case: on another stream every run would wait for
-// the null stream's work and make it wait in turn, about 15 us each way.
-pf_status capture_stream(pf_handle* H, hipStream_t* out) {
-  if (H->stream) {
-    *out = H->stream;
-    return PF_OK;
-  }
-  if (!H->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&H->cap_stream, hipStreamNonBlocking));
-  *out = H->cap_stream;
+// The ladder steps of a run of n intervals, the longest graphs first: f(v)
+// for each graph of 2^v intervals (n = 200 is 128 + 64 + 8).
+template <class F>
+pf_status for_graphs(int nv, int n, F f) {
+  for (int v = nv - 1; v >= 0; --v)
+    for (; n >= (1 << v); n -= 1 << v)
+      if (pf_status st = f(v)) return st;
   return PF_OK;
 }
 
-// Captures the graphs pf_graph_run replays.  Every capture is on one
-// stream and holds kernel launches only (no event, copy or memset), so a
-// graph never refers to an event or another stream: 2^v intervals for each
-// step v of the ladder, of every filter (plain layout) or of each filter
-// group (batched layout).  The groups' graphs are launched on their own
-// streams between an eager fork and join.
-pf_status ensure_graphs(pf_handle* H) {
-  if (!H->gexecs.empty()) return PF_OK;
-  hipStream_t cs;
-  pf_status st = capture_stream(H, &cs);
-  if (st) return st;
-  const bool tm = H->timing;
-  H->timing = false;
-  const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
-  const int ng = batched ? H->groups : 1;
-  const int nv = graph_ladder(H);
-  for (int g = 0; g < ng && !st; ++g) {
-    for (int v = 0; v < nv && !st; ++v) {
-      HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-      if (batched) {
-        st = enqueue_group(H, g, cs, 1 << v);
-      } else {
-        for (int i = 0; i < (1 << v) && !st; ++i) {
-          st = enqueue_step(H, cs);
-          if (!st) st = enqueue_resample(H, cs, nullptr);
-        }
-      }
-      hipGraph_t graph = nullptr;
-      hipError_t e = hipStreamEndCapture(cs, &graph);
-      if (st) {
-        if (graph) (void)hipGraphDestroy(graph);
-        break;
-      }
-      if (e != hipSuccess) {
-        st = fail(PF_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-        break;
-      }
-      H->graphs.push_back(graph);
-      hipGraphExec_t ex = nullptr;
-      e = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
-      if (e != hipSuccess) {
-        st = fail(PF_E_DEVICE, "graph instantiation failed: %s", hipGetErrorString(e));
-        break;
-      }
-      H->gexecs.push_back(ex);
+// Graph of 2^v intervals (group g), captured on cs.
+pf_status capture_graph(pf_handle* H, hipStream_t cs, int g, int v) {
+  hipGraph_t& graph = H->graphs[(size_t)g * H->gnv + v];
+  HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+  pf_status st = PF_OK;
+  if (H->cfg.layout == PF_LAYOUT_BATCHED) {
+    st = enqueue_group(H, g, cs, 1 << v);
+  } else {
+    for (int i = 0; i < (1 << v) && !st; ++i) {
+      st = enqueue_step(H, cs);
+      if (!st) st = enqueue_resample(H, cs, nullptr);
     }
   }
+  hipError_t e = hipStreamEndCapture(cs, &graph);
+  if (st) return st;
+  if (e != hipSuccess) return fail(PF_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
+  e = hipGraphInstantiate(&H->gexecs[(size_t)g * H->gnv + v], graph, nullptr, nullptr, 0);
+  if (e != hipSuccess)
+    return fail(PF_E_DEVICE, "graph instantiation failed: %s", hipGetErrorString(e));
+  return PF_OK;
+}
+
+// Captures the graphs that a run of n intervals replays and that are not
+// there yet.  Every capture is on one stream and holds kernel launches only
+// (no event, copy or memset), so a graph never refers to an event or another
+// stream: 2^v intervals for a step v of the ladder, of every filter (plain
+// layout) or of each filter group (batched layout).  The groups' graphs are
+// launched on their own streams between an eager fork and join.  The null
+// stream cannot be captured: a caller that uses it has its graphs captured on
+// another stream, and launched on the null stream all the same (on another,
+// every run would wait for the null stream's work and make it wait in turn,
+// about 15 us each way).
+pf_status ensure_graphs(pf_handle* H, int n) {
+  const int ng = H->cfg.layout == PF_LAYOUT_BATCHED ? H->groups : 1;
+  const int nv = graph_ladder(H);
+  if (H->gexecs.empty()) {
+    H->gnv = nv;
+    H->graphs.assign((size_t)ng * nv, nullptr);
+    H->gexecs.assign((size_t)ng * nv, nullptr);
+  }
+  hipStream_t cs = H->stream, own = nullptr;
+  const bool tm = H->timing;
+  H->timing = false;
+  pf_status st = for_graphs(nv, n, [&](int v) -> pf_status {
+    for (int g = 0; g < ng; ++g) {
+      if (H->gexecs[(size_t)g * nv + v]) continue;
+      if (!cs) {
+        HIP_TRY(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
+        cs = own;
+      }
+      if (pf_status e = capture_graph(H, cs, g, v)) return e;
+    }
+    return PF_OK;
+  });
+  if (own) {  // (nothing was issued on it, only captured)
+    (void)hipStreamSynchronize(own);
+    (void)hipStreamDestroy(own);
+  }
   H->timing = tm;
-  if (st) destroy_graphs(H);
-  else H->gnv = nv;
+  // (graphs of an earlier run may still be replaying: wait before they go)
+  if (st && drain(H) == PF_OK) destroy_graphs(H);
   return st;
 }
 
@@ -1213,18 +1227,17 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
     H->t += n_steps;
     return PF_OK;
   }
-  if ((st = ensure_graphs(H))) return st;
+  if ((st = ensure_graphs(H, n_steps))) return st;
   if (H->cfg.layout == PF_LAYOUT_PLAIN) H->marks_pending = true;
   const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
   const int G = batched ? H->groups : 1;
-  // group g's graphs go on its own stream (the caller's with one group)
-  auto gs = [&](int g) { return G == 1 ? ls : H->side[g]; };
   if (G > 1 && (st = fork_groups(H, ls))) return st;
-  // the longest graphs first: n = 200 is 128 + 64 + 8
-  int left = n_steps;
-  for (int v = H->gnv - 1; v >= 0; --v)
-    for (; left >= (1 << v); left -= 1 << v)
-      for (int g = 0; g < G; ++g) HIP_TRY(hipGraphLaunch(H->gexecs[g * H->gnv + v], gs(g)));
+  st = for_graphs(H->gnv, n_steps, [&](int v) -> pf_status {
+    for (int g = 0; g < G; ++g)
+      HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * H->gnv + v], group_stream(H, g, ls)));
+    return PF_OK;
+  });
+  if (st) return st;
   if (G > 1 && (st = join_groups(H, ls))) return st;
   H->t += n_steps;
   return PF_OK;
@@ -1675,8 +1688,12 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
     HIP_TRY(hipMemcpyAsync(ws + L.anc_tr, ident.data(), 4 * (size_t)B, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
   }
-  // capture both handles' graphs before the loop
-  if (!kalman && ((st = ensure_graphs(H)) || (st = ensure_graphs(P)))) return st;
+  // capture the graphs before the loop
+  if (!kalman) {
+    if ((st = ensure_graphs(H, 1))) return st;
+    for (int32_t i = 1; i < T; i <<= 1)
+      if ((st = ensure_graphs(P, std::min(i, 1 << (graph_ladder(P) - 1))))) return st;
+  }
 
   pfk::Smc2Args S{};
   S.B = B;
@@ -1995,7 +2012,7 @@ pf_status time_graph_replay(pf_handle* H, int n, double* ms_out) {
   pf_status st = do_init(H, H->stream);
   if (st) return st;
   H->eager_replay = false;
-  if ((st = pf_graph_run(H, 1))) return st;  // captures the graphs
+  if ((st = ensure_graphs(H, n)) || (st = pf_graph_run(H, 1))) return st;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
