@@ -208,14 +208,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
           const uint4 w = metro_draw(key, t, (uint32_t)f, it, k, s1);
           int jp = metro_index(w.x, N);
           double lp = stage[stage_slot(jp)];
-          if (ln_f64(u01_f64(w.y)) <= lp - lj) {
+          if (ln_u_leq(w.y, lp - lj)) {
             j = jp;
             lj = lp;
           }
           if (s1 + 1 <= A.rs.steps) {
             jp = metro_index(w.z, N);
             lp = stage[stage_slot(jp)];
-            if (ln_f64(u01_f64(w.w)) <= lp - lj) {
+            if (ln_u_leq(w.w, lp - lj)) {
               j = jp;
               lj = lp;
             }

@@ -1014,7 +1014,7 @@ __global__ __launch_bounds__(K1_NT) void k_metropolis(const double* __restrict__
       int32_t jp = metro_index(w.x, N);
       double lp = l[jp];
       lp = (lp == lp) ? lp : -INFINITY;
-      if (ln_f64(u01_f64(w.y)) <= lp - lj) {
+      if (ln_u_leq(w.y, lp - lj)) {
         j = jp;
         lj = lp;
       }
@@ -1022,7 +1022,7 @@ __global__ __launch_bounds__(K1_NT) void k_metropolis(const double* __restrict__
         jp = metro_index(w.z, N);
         lp = l[jp];
         lp = (lp == lp) ? lp : -INFINITY;
-        if (ln_f64(u01_f64(w.w)) <= lp - lj) {
+        if (ln_u_leq(w.w, lp - lj)) {
           j = jp;
           lj = lp;
         }

@@ -139,14 +139,14 @@ __device__ __forceinline__ SmallOut small_collective(SmallLds<NQ>& X, const doub
           const uint4 q = metro_draw(key, t, b, iter, k, s);
           int jp = metro_index(q.x, N);
           double lp = X.lw[jp];
-          if (ln_f64(u01_f64(q.y)) <= lp - lj) {
+          if (ln_u_leq(q.y, lp - lj)) {
             j = jp;
             lj = lp;
           }
           if (s + 1 <= rs.steps) {
             jp = metro_index(q.z, N);
             lp = X.lw[jp];
-            if (ln_f64(u01_f64(q.w)) <= lp - lj) {
+            if (ln_u_leq(q.w, lp - lj)) {
               j = jp;
               lj = lp;
             }

@@ -145,6 +145,20 @@ def test_lorenz96_plain_rejection(pfm):
     assert min(refs[0]["ess"]) < 500
 
 
+@pytest.mark.parametrize("layout", ["plain", "batched"])
+def test_metropolis_moves_close_to_the_bound(pfm, layout):
+    """2.5 million moves over weights of ordinary spread: about 4e-5 of them lie
+    within 2e-5 of their bound, where the decision needs the logarithm itself."""
+    sizes = [20000] if layout == "plain" else [4096, 4095, 4096, 3000]
+    base = W.lorenz96(d=8, N=1, T=4)
+    _, y = oracle.simulate(base)
+    th, _ = W.batched_thetas(4, seed=62)
+    pb = dataclasses.replace(base.with_obs(y), obs_sd=8.0, theta=th[:len(sizes)],
+                             n_particles=np.array(sizes, dtype=np.int64))
+    kind = pfm.PF_LAYOUT_PLAIN if layout == "plain" else pfm.PF_LAYOUT_BATCHED
+    _check(pfm, pb, kind, oracle.RESAMPLE_METROPOLIS, 41, float("inf"))
+
+
 def test_variant_rules(pfm):
     base = W.lorenz96(d=8, N=64, T=3)
     _, y = oracle.simulate(base)
