@@ -1028,7 +1028,7 @@ int systematic_enqueue(const double* lw, int64_t n, double u, int32_t* anc, doub
   if (a.nblk > FUSE_NB) HIP_TRY(launch_combine((double*)(ws + L.part), (double*)(ws + L.boff), a, s));
   HIP_TRY(launch_scan_mark(lw, (double*)(ws + L.part), (double*)(ws + L.boff), marks,
                            (int32_t*)(ws + L.owner), (int32_t*)(ws + L.jc), a, s));
-  HIP_TRY(launch_tile_anc(marks, (int32_t*)(ws + L.owner), (int32_t*)(ws + L.jc), anc, a, s));
+  HIP_TRY(launch_name_ancestors(marks, (int32_t*)(ws + L.owner), (int32_t*)(ws + L.jc), anc, a, s));
   return PF_OK;
 }
 

@@ -166,6 +166,8 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_combine(const double* part, double* boff, const PlainArgs& a, hipStream_t s);
 hipError_t launch_lw_partials(const double* lw, double* part, int32_t* marks, double u,
                               const PlainArgs& a, hipStream_t s);
+hipError_t launch_name_ancestors(const int32_t* marks, const int32_t* owner, const int32_t* jc,
+                                 int32_t* anc, const PlainArgs& a, hipStream_t s);
 hipError_t launch_tile_anc(int32_t* marks, const int32_t* owner, const int32_t* jc, int32_t* anc,
                            const PlainArgs& a, hipStream_t s);
 hipError_t launch_scan_mark(const double* lw, const double* part, const double* boff,

@@ -106,6 +106,27 @@ def test_systematic_full_size(env):
         check(lw, u, a, stats)
 
 
+@pytest.mark.parametrize("n", [4097, 262144 + 256 * 3 + 1, (1 << 20) - 257, (1 << 20) + 1,
+                               1300007])
+def test_systematic_edges_of_the_large_path(env, n):
+    """Either side of the partials one combining workgroup stages, ragged
+    chunks and tiles, and ancestors at an address of 4 bytes' alignment."""
+    torch, pfm = env
+    rng = np.random.default_rng(n)
+    lw = weights("holes", n, rng)
+    u = float(rng.random())
+    d = torch.from_numpy(lw).to("cuda")
+    a0, s0 = run(env, lw, u)
+    check(lw, u, a0, s0)
+    room = torch.full((n + 2,), -7, dtype=torch.int32, device="cuda")
+    _, s1 = pfm.systematic(d, u, anc=room[1:n + 1])
+    torch.cuda.synchronize()
+    got = room.cpu().numpy()
+    np.testing.assert_array_equal(got[1:n + 1], a0)
+    assert got[0] == -7 and got[n + 1] == -7
+    np.testing.assert_array_equal(s1.cpu().numpy(), s0)
+
+
 def test_systematic_no_positive_weight(env):
     for lw in (np.full(300, -np.inf), np.full(5000, np.nan)):
         a, stats = run(env, lw, 0.5)
