@@ -1756,7 +1756,14 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
                              8 * (size_t)B * nth, hipMemcpyDeviceToDevice, s));
     }
   }
-  double* prop_dev = kalman ? nullptr : P->at<double>(P->L.theta);
+  pfk::SmcProposal prop{};
+  if (!kalman) {
+    prop.fs = P->at<FilterState>(P->L.fs);
+    prop.theta_dev = P->at<double>(P->L.theta);
+    prop.ell_tr = P->at<double>(P->L.ell);
+    prop.ess_tr = P->at<double>(P->L.ess);
+    prop.anc = P->at<int32_t>(P->L.anc);
+  }
 
   for (int32_t i = 1; i <= T && !kalman; ++i) {
     const size_t cur = state_buf(H, i - 1), spare = state_buf(H, i);
@@ -1764,25 +1771,29 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
       // 1-2. theta-ancestors from v(t_{i-1}), the slots' moves and filter copies
       HIP_TRY(pfk::launch_theta_resample(S, i - 2, in->u[i - 1], 1, anc_tr + (size_t)(i - 1) * B,
                                          ess_d + (i - 2), s));
-      HIP_TRY(pfk::launch_filter_copy(c.precision, H->ws + cur, H->ws + spare,
-                                      H->at<int32_t>(H->L.anc), A, S, w_d + (size_t)(i - 1) * B,
-                                      s));
+      HIP_TRY(pfk::launch_filter_gather(c.precision, H->ws + cur, H->ws + spare,
+                                        H->at<int32_t>(H->L.anc), A, S,
+                                        w_d + (size_t)(i - 1) * B, s));
     }
-    // 3. rejuvenation: proposals, their filters over t_{0:i-1}, the decisions
-    HIP_TRY(pfk::launch_smc2_propose(S, z_d + (size_t)(i - 1) * B * nth, prop_dev, s));
+    // 3. rejuvenation: proposals, their filters over t_{0:i-1}, the decisions.
+    // The start initialises the proposal handle as do_init would
     P->iter = (uint32_t)i;
-    if ((st = do_init(P, s))) return st;
+    prop.x = P->ws + P->L.x_cur;
+    HIP_TRY(pfk::launch_smc2_start(c.model, c.d, c.precision, H->ws + cur, H->ws + spare,
+                                   H->at<int32_t>(H->L.anc), z_d + (size_t)(i - 1) * B * nth,
+                                   prop, (uint32_t)i, i >= 2, A, S, s));
+    P->t = 0;
+    P->phase = 0;
+    P->marks_pending = false;
     if (i > 1 && (st = pf_graph_run(P, i - 1))) return st;
-    HIP_TRY(pfk::launch_smc2_accept(S, la_d + (size_t)(i - 1) * B, prop_dev,
-                                    P->at<FilterState>(P->L.fs), acc_tr + (size_t)(i - 1) * B,
-                                    s));
-    HIP_TRY(pfk::launch_accept_copy(c.precision, H->ws + cur, H->at<int32_t>(H->L.anc),
-                                    P->ws + state_buf(P, i - 1), P->at<int32_t>(P->L.anc), A, S,
-                                    s));
+    prop.x = P->ws + state_buf(P, i - 1);
+    HIP_TRY(pfk::launch_smc2_finish(c.model == PF_MODEL_WK ? 1 : c.d, c.precision, H->ws + cur,
+                                    H->at<int32_t>(H->L.anc), la_d + (size_t)(i - 1) * B,
+                                    acc_tr + (size_t)(i - 1) * B,
+                                    (double*)(ws + L.theta_tr) + (size_t)(i - 1) * B * nth, prop,
+                                    A, S, s));
     // 4. every attached filter advances one interval
     if ((st = pf_graph_run(H, 1))) return st;
-    HIP_TRY(hipMemcpyAsync(ws + L.theta_tr + 8 * (size_t)(i - 1) * B * nth, ws + L.raw,
-                           8 * (size_t)B * nth, hipMemcpyDeviceToDevice, s));
   }
   HIP_TRY(pfk::launch_theta_resample(S, T - 1, 0.5, 0, nullptr, ess_d + (T - 1), s));
 

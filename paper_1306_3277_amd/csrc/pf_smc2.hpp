@@ -20,7 +20,7 @@ struct Smc2Args {
   double* prop_raw;              // [B][n_theta] proposals
   double* snap_dev;              // [B][8] snapshot during the theta move
   double* snap_raw;              // [B][n_theta]
-  double* snap_ll;               // [B]
+  double* snap_ll;               // [B]; then the likelihoods the decisions compare with
   int32_t* snap_st;              // [B]
   int32_t* a;                    // [B] theta-ancestors
   int32_t* inside;               // [B] proposal inside the prior box
@@ -34,17 +34,30 @@ struct Smc2Args {
   double* ell_tr_w;              // the handle's [B][T] increments, written
 };
 
+// The proposal handle's arrays.
+struct SmcProposal {
+  FilterState* fs;
+  double* theta_dev;      // [B][8] derived parameters
+  double* ell_tr;         // [B][T] traces
+  double* ess_tr;
+  int32_t* anc;
+  void* x;                // the state buffer in question
+};
+
 hipError_t launch_theta_resample(const Smc2Args& S, int32_t col, double u, int32_t draw,
                                  int32_t* anc_tr_row, double* ess_out, hipStream_t s);
-hipError_t launch_filter_copy(int prec, void* xcur, void* xspare, int32_t* anc, const BatchArgs& A,
-                              const Smc2Args& S, const uint32_t* w, hipStream_t s);
+hipError_t launch_filter_gather(int prec, const void* xcur, void* xspare, const int32_t* anc,
+                                const BatchArgs& A, const Smc2Args& S, const uint32_t* w,
+                                hipStream_t s);
 hipError_t launch_smc2_propose(const Smc2Args& S, const double* z_row, double* prop_dev,
                                hipStream_t s);
-hipError_t launch_smc2_accept(const Smc2Args& S, const double* log_alpha_row,
-                              const double* prop_dev, const FilterState* pfs, int32_t* acc_tr_row,
-                              hipStream_t s);
-hipError_t launch_accept_copy(int prec, void* xcur, int32_t* anc, const void* pxcur,
-                              const int32_t* panc, const BatchArgs& A, const Smc2Args& S,
-                              hipStream_t s);
+hipError_t launch_smc2_start(int model, int d, int prec, void* xcur, const void* xspare,
+                             int32_t* anc, const double* z_row, const SmcProposal& P,
+                             uint32_t iter, int copied, const BatchArgs& A, const Smc2Args& S,
+                             hipStream_t s);
+hipError_t launch_smc2_finish(int d, int prec, void* xcur, int32_t* anc,
+                              const double* log_alpha_row, int32_t* acc_tr_row,
+                              double* theta_tr_row, const SmcProposal& P, const BatchArgs& A,
+                              const Smc2Args& S, hipStream_t s);
 
 }  // namespace pfk

@@ -108,6 +108,22 @@ def test_smc2_windkessel_fp64_matches_oracle(pfm):
     _compare(pfm, pb, inp, ref, r)
 
 
+@pytest.mark.parametrize("B", [1, 63, 65, 961, 1025])
+def test_smc2_theta_counts(pfm, B):
+    """A lane per theta-particle up to 1,024 of them, several per lane above;
+    one filter of a single particle and some of more than one chunk of 256."""
+    base = W.lorenz96(d=4, N=1, T=4)
+    _, y = oracle.simulate(base)
+    th0, _ = W.batched_thetas(B, seed=B)
+    n = np.random.default_rng(B).integers(1, 40, B).astype(np.int64)
+    n[0], n[-1] = 1, 600
+    pb = dataclasses.replace(base.with_obs(y), theta=th0, n_particles=n)
+    inp = W.smc2_l96_inputs(th0, pb.T, seed=B + 1, step_f=0.3, step_s=0.03)
+    ref = oracle.smc2(pb, inp)
+    r, _ = _run_gpu(pfm, pb, inp, pfm.PF_FP64)
+    _compare(pfm, pb, inp, ref, r)
+
+
 def test_smc2_shorter_run_than_the_handle(pfm):
     """T_run < T: the run stops after T_run times and matches the oracle's."""
     base = W.lorenz96(d=8, N=1, T=7)
