@@ -59,7 +59,7 @@ struct Layout {
   int64_t nblk_total = 0;
   // byte offsets into the workspace
   size_t x_cur, x_tmp, lw, marks, anc, part, boff, owner, jc, fs, ell, ess, theta, obs, obs_pos,
-      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, nz, rec, lw2, b_fused, total;
+      obs_idx, q, b_off, b_order, b_chunk_f, b_chunk_k, b_u, kf_ll, kf_ell, wcum, w16, w256, nz, rec, lw2, b_fused, total;
   int32_t fused_cap = 0;  // entries of one fused table
   int32_t n_chunks = 0;
   // plain windkessel filters small enough for one workgroup each: the
@@ -187,7 +187,12 @@ Layout make_layout(const pf_config* c) {
   L.b_u = take(8 * (size_t)c->B);
   L.kf_ll = take(8 * (size_t)c->B);
   L.kf_ell = take(8 * (size_t)c->B * c->T);
-  L.wcum = take(c->layout == PF_LAYOUT_PLAIN ? 8 * (size_t)L.n_total : 8);
+  // the multinomial search reads whole nodes of 16 values, the last one's
+  // past its filter's end
+  L.wcum = take(c->layout == PF_LAYOUT_PLAIN ? 8 * ((size_t)L.n_total + 16) : 8);
+  const size_t n256 = (size_t)(L.n_total / 256) + c->B + 1;  // filter b's from off / 256 + b
+  L.w16 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * 16 * n256 : 8);
+  L.w256 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * n256 : 8);
   // Runs of windkessel filters of up to SMALL_MAXN particles draw their random
 // numbers ahead (K values per particle and interval, whole 256-particle
   // blocks of the largest filter's number for each): as many intervals at a time
@@ -331,6 +336,9 @@ PlainArgs plain_args(const pf_handle* H, int b) {
   a.ess_tr = H->at<double>(H->L.ess) + (size_t)b * c.T;
   a.rs = H->rs;
   a.wcum = H->at<double>(H->L.wcum) + (c.layout == PF_LAYOUT_PLAIN ? H->L.off[b] : 0);
+  const int64_t n256 = c.layout == PF_LAYOUT_PLAIN ? H->L.off[b] / 256 + b : 0;
+  a.w16 = H->at<double>(H->L.w16) + 16 * n256;
+  a.w256 = H->at<double>(H->L.w256) + n256;
   return a;
 }
 
@@ -704,7 +712,7 @@ pf_status enqueue_resample(pf_handle* H, hipStream_t s, const double* u) {
         HIP_TRY(pfk::launch_rejection_anc(H->at<double>(H->L.lw), H->at<int32_t>(H->L.anc), a,
                                           s));
       else  // search of the step's cumulative weights
-        HIP_TRY(pfk::launch_multinomial_anc(a.wcum, H->at<int32_t>(H->L.jc),
+        HIP_TRY(pfk::launch_multinomial_anc(H->at<int32_t>(H->L.jc),
                                             H->at<int32_t>(H->L.anc), a, s));
       if ((st = ev_end(H, e0, 3, s))) return st;
     } else if (H->hist) {

@@ -88,6 +88,8 @@ struct PlainArgs {
   double* ess_tr;
   ResampleArgs rs;
   double* wcum;           // this filter's cumulative weights [N] (multinomial only)
+  double* w16;            // the last of every 16 of them, and of every 256
+  double* w256;
   int32_t mode;           // K2/K3: 0 step (bookkeeping, uniform drawn); 1 ancestors only
                           // (given uniform); 2 bookkeeping with the given uniform
 };
@@ -188,7 +190,7 @@ hipError_t launch_metropolis_anc(const double* lw, int32_t* anc, const PlainArgs
                                  hipStream_t s);
 hipError_t launch_rejection_anc(const double* lw, int32_t* anc, const PlainArgs& a,
                                 hipStream_t s);
-hipError_t launch_multinomial_anc(const double* wcum, const int32_t* jc, int32_t* anc,
+hipError_t launch_multinomial_anc(const int32_t* jc, int32_t* anc,
                                   const PlainArgs& a, hipStream_t s);
 hipError_t launch_simulate(int model, int d, double* out, const PlainArgs& a, double obs_sd,
                            hipStream_t s);

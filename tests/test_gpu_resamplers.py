@@ -159,6 +159,19 @@ def test_metropolis_moves_close_to_the_bound(pfm, layout):
     _check(pfm, pb, kind, oracle.RESAMPLE_METROPOLIS, 41, float("inf"))
 
 
+@pytest.mark.parametrize("sizes", [[1024, 1], [15, 1025, 17], [16384, 257], [255, 16385],
+                                   [300, 262145]])
+def test_plain_multinomial_levels(pfm, sizes):
+    """Either side of each level the multinomial search starts from, and
+    several filters, whose tables lie one behind the other."""
+    base = W.lorenz96(d=4, N=1, T=2)
+    _, y = oracle.simulate(base)
+    th, _ = W.batched_thetas(len(sizes), seed=63)
+    pb = dataclasses.replace(base.with_obs(y), theta=th,
+                             n_particles=np.array(sizes, dtype=np.int64))
+    _check(pfm, pb, pfm.PF_LAYOUT_PLAIN, oracle.RESAMPLE_MULTINOMIAL, 0, float("inf"))
+
+
 def test_variant_rules(pfm):
     base = W.lorenz96(d=8, N=64, T=3)
     _, y = oracle.simulate(base)
