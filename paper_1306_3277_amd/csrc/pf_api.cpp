@@ -193,19 +193,21 @@ Layout make_layout(const pf_config* c) {
   const size_t n256 = (size_t)(L.n_total / 256) + c->B + 1;  // filter b's from off / 256 + b
   L.w16 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * 16 * n256 : 8);
   L.w256 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * n256 : 8);
-  // Runs of windkessel filters of up to SMALL_MAXN particles draw their random
-// numbers ahead (K values per particle and interval, whole 256-particle
-  // blocks of the largest filter's number for each): as many intervals at a time
-  // as 64 MiB hold, at least one, in at most 256 MiB.  Measured against the
-  // multi-kernel path's graphs, us per interval, FP64 at K = 1, 10 and 20:
-  // 4.6, 5.5, 7.4 against 11.3, 14.3, 18.6 for 1,024 particles; 5.8, 7.3, 9.5
-  // against 11.2, 15.0, 18.9 for 2,048; 10.6, 13.5, 16.7 against 11.2, 14.8,
-  // 18.7 for 4,096 (FP32 9.1, 11.1, 13.1 against 11.0, 12.4, 13.8): there one
-  // CU's bandwidth for the numbers and its registers run out.  Several
-  // filters run side by side where the other path takes them in turn.
+  // Runs of small windkessel filters draw their random numbers ahead (K values
+  // per particle and interval, whole 256-particle blocks of the largest
+  // filter's number for each): as many intervals at a time as 64 MiB hold, at
+  // least one, in at most 256 MiB.  Small is up to SMALL_MAXN / 2 particles, and
+  // SMALL_MAXN where several filters run side by side that the multi-kernel path
+  // takes in turn.  Measured against that path's graphs, us per interval, FP64
+  // at K = 1, 10 and 20: 4.6, 5.5, 7.3 against 7.9, 10.8, 14.6 for 1,024
+  // particles; 5.8, 7.3, 9.4 against 7.9, 11.2, 14.7 for 2,048; 10.0, 13.0, 16.3
+  // against 8.1, 11.0, 14.5 for 4,096 (FP32 9.1, 10.8, 12.8 against 7.7, 9.1,
+  // 10.5): there one CU's bandwidth for the numbers and its registers run out.
+  // Two filters of 4,096, FP64: 10.1, 13.1, 17.1 against 15.8, 21.7, 29.2.
   if (c->layout == PF_LAYOUT_PLAIN && c->model == PF_MODEL_WK && c->K <= pfk::SMALL_MAXK &&
       c->B <= 65535 &&
-      *std::max_element(c->n_particles, c->n_particles + c->B) <= pfk::SMALL_MAXN) {
+      *std::max_element(c->n_particles, c->n_particles + c->B) <=
+          (c->B > 1 ? pfk::SMALL_MAXN : pfk::SMALL_MAXN / 2)) {
     const int64_t nb = *std::max_element(L.nblk.begin(), L.nblk.end());
     const size_t one = sx * (size_t)c->K * (size_t)(nb * pfk::K1_NT) * (size_t)c->B;
     if (one <= ((size_t)256 << 20)) {
@@ -509,13 +511,13 @@ void set_history(const pf_handle* H, BatchArgs& a) {
 // memory, and pays for every workgroup scanning its whole filter: about 2.3 us
 // per million particles scanned in all.  Measured, us per interval, fused
 // against two launches (Lorenz '96 d = 8, K = 8, fast FP32, one group, 256
-// threads): 64 filters of 256: 11.6 / 13.0, of 2,048 (1.05 million scanned):
-// 17.2 / 18.8; 256 of 512: 15.6 / 17.2, of 1,024 (1.05 million): 26.8 / 26.4, of
-// 2,048 (4.2 million): 47 / 41.  Workgroups of 512 gain less, as their
+// threads): 64 filters of 256: 10.9 / 12.8, of 2,048 (1.05 million scanned):
+// 16.8 / 18.9; 256 of 512: 15.0 / 17.5, of 1,024 (1.05 million): 24.8 / 25.9, of
+// 2,048 (4.2 million): 46 / 41.  Workgroups of 512 gain less, as their
 // propagation has two waves on a SIMD where two launches would spread them
-// (4 filters of 1,024: 13.7 / 13.1): they fuse only filters of more than 2,048
-// in groups that overlap (64 of 4,096, 2.1 million scanned, two groups: 24.4 /
-// 25.5; one group: 28.3 / 28.5).
+// (4 filters of 1,024: 12.9 / 12.7): they fuse only filters of more than 2,048
+// in groups that overlap (64 of 4,096, 2.1 million scanned, two groups: 24.7 /
+// 25.2; one group: 27.7 / 28.7; 128 in two groups: 41.9 / 37.9).
 bool group_fused(const pf_handle* H, int g) {
   const pf_config& c = H->cfg;
   if (H->timing || H->rs.scheme != pfk::RS_SYSTEMATIC ||

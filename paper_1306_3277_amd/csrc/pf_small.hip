@@ -8,8 +8,9 @@
 //
 // The multi-kernel plain layout spends two launches per interval on such a
 // filter and each of its kernels runs on one to sixteen of the 256 CUs,
-// waiting on memory: 17.6 us per interval for 1,024 windkessel particles,
-// 3.4 of them between kernels.  In one workgroup an interval needs no launch
+// waiting on memory: 10.8 us per interval for 1,024 windkessel particles in
+// FP64 (17.6 before its kernels' chains were shortened), 3.4 of them between
+// kernels.  In one workgroup an interval needs no launch
 // and no exchange through memory, but one CU's lanes for the normals, three
 // quarters of the propagation's instructions; those depend on nothing but
 // their counters, so a launch over the whole device draws them beforehand.
@@ -342,7 +343,7 @@ constexpr int REC_HEAD = 3;
 // numbers; within a block a lane's four rows lie together:
 // nz[(((i K + s) B + b) fb + block) 256 + 4 lane + row].  One lane per
 // particle and interval; bound by the normals' FP64 instructions (1,024
-// particles, 100 intervals of K = 10: NOISEUS us for all of them).
+// particles, 100 intervals of K = 10: 13.4 us for all of them).
 template <typename Real>
 __global__ __launch_bounds__(K1_NT) void k_small_noise(PlainArgs A,
                                                        const int64_t* __restrict__ offs,
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(K1_NT) void k_small_noise(PlainArgs A,
 // dependent adds, two exponentials, five barriers.  The next interval's
 // numbers are loaded during the collective, and the likelihood's logarithms
 // wait for 64 intervals to be taken by 64 lanes.  1,024 particles, K = 10,
-// FP64: RUNUS us an interval (17.6 on the multi-kernel path's graphs).
+// FP64: 5.3 us an interval (10.8 on the multi-kernel path's graphs).
 template <typename Real, bool ACC, int NQ, bool SYS>
 __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
                                                          Real* __restrict__ xb,

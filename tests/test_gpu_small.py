@@ -57,6 +57,31 @@ def test_small_run_equals_eager_steps(env, n, K, precision):  # noqa: F811
         g.close()
 
 
+@pytest.mark.parametrize("sizes,K", [((2049, 1), 2), ((4095, 4096), 17), ((4096, 3000, 40), 5)])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_small_run_of_several_large_filters(env, sizes, K, precision):  # noqa: F811
+    """Past 2,048 particles only several filters take one launch."""
+    _, pfm = env
+    import dataclasses
+
+    import workloads as W
+    T = 6
+    base = W.windkessel(N=1, T=T, K=K, B=len(sizes), seed=K)
+    pb = dataclasses.replace(
+        base.with_obs(90.0 + 5.0 * np.random.default_rng(K).standard_normal((T, 1))),
+        n_particles=np.array(sizes, dtype=np.int64))
+    for name, (scheme, steps, frac) in SCHEMES.items():
+        f, g = (pfm.Filter(pb, precision=precision) for _ in range(2))
+        for h in (f, g):
+            h.set_resampler(scheme, steps, frac)
+        f.advance(T)
+        g.graph_run(T)
+        for a, b in zip(_outputs(f), _outputs(g)):
+            np.testing.assert_array_equal(a, b, err_msg=name)
+        f.close()
+        g.close()
+
+
 @pytest.mark.parametrize("precision", [0, 1, 2])
 def test_small_run_of_uneven_filters_and_lost_weights(env, precision):  # noqa: F811
     _, pfm = env
