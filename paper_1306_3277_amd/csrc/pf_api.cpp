@@ -267,13 +267,9 @@ struct pf_handle {
   // the groups' parts of the fused launch tables, for 256 and 512 threads
   std::vector<int32_t> grp_fused0[2], grp_nfused[2];
   int64_t scanned[2] = {0, 0};  // particles that a fused launch of all groups scans
-  // With G > 1 groups, group 0's kernels run on the caller's stream and group
-  // g's on side[g - 1]; ev_fork forks the side streams from the caller's,
-  // ev_join[g - 1] joins group g back.  These events are only ever recorded
-  // and waited on outside stream capture.  (The device runs a process's
-  // streams on four queues; a second one for every handle put both groups of
-  // some handles on one: 12.6 against 9.4 ms for the second of three handles
-  // of 512 filters in two groups, T = 100.)
+  // With G > 1 groups, group g's kernels run on side[g]; ev_fork forks the
+  // side streams from the caller's, ev_join[g] joins group g back.  These
+  // events are only ever recorded and waited on outside stream capture.
   std::vector<hipStream_t> side;
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_join;
@@ -583,31 +579,29 @@ pf_status enqueue_group(pf_handle* H, int g, hipStream_t s, int n) {
 // far) and join them back into s.  Never used inside a capture.
 pf_status fork_groups(pf_handle* H, hipStream_t s) {
   HIP_TRY(hipEventRecord(H->ev_fork, s));
-  for (int g = 1; g < H->groups; ++g)
-    HIP_TRY(hipStreamWaitEvent(H->side[g - 1], H->ev_fork, 0));
+  for (int g = 0; g < H->groups; ++g) HIP_TRY(hipStreamWaitEvent(H->side[g], H->ev_fork, 0));
   return PF_OK;
 }
 pf_status join_groups(pf_handle* H, hipStream_t s) {
-  for (int g = 1; g < H->groups; ++g) {
-    HIP_TRY(hipEventRecord(H->ev_join[g - 1], H->side[g - 1]));
-    HIP_TRY(hipStreamWaitEvent(s, H->ev_join[g - 1], 0));
+  for (int g = 0; g < H->groups; ++g) {
+    HIP_TRY(hipEventRecord(H->ev_join[g], H->side[g]));
+    HIP_TRY(hipStreamWaitEvent(s, H->ev_join[g], 0));
   }
   return PF_OK;
 }
 // the stream of group g in a run issued from s
 hipStream_t group_stream(const pf_handle* H, int g, hipStream_t s) {
-  return g == 0 ? s : H->side[g - 1];
+  return H->groups == 1 ? s : H->side[g];
 }
 
 // n intervals of the batched layout issued eagerly from stream s.  With one
 // group both kernels go on s.  With G groups (filters dealt so that every
 // group holds about the same number of particles) group g's intervals run
-// back to back on a stream of its own (group 0's on s): the groups start
-// together after everything
-// issued on s so far, drift against each other, and one group's collective
-// overlaps another's propagation; s waits for every group at the end.  The
-// launches are issued in turn across the groups, so no group
-// waits for the host to issue another group's whole run.
+// back to back on a stream of its own: the groups start together after
+// everything issued on s so far, drift against each other, and one group's
+// collective overlaps another's propagation; s waits for every group at the
+// end.  The launches are issued in turn across the groups, so no group waits
+// for the host to issue another group's whole run.
 pf_status enqueue_batched(pf_handle* H, hipStream_t s, int n) {
   pf_status st;
   const int G = H->groups;
@@ -615,7 +609,8 @@ pf_status enqueue_batched(pf_handle* H, hipStream_t s, int n) {
   if ((st = fork_groups(H, s))) return st;
   for (int i = 0; i < 2 * n; ++i)
     for (int g = 0; g < G; ++g)
-      if (i < group_launches(H, g, n) && (st = enqueue_group_launch(H, g, group_stream(H, g, s), n, i)))
+      if (i < group_launches(H, g, n) &&
+          (st = enqueue_group_launch(H, g, group_stream(H, g, s), n, i)))
         return st;
   return join_groups(H, s);
 }
@@ -771,6 +766,38 @@ pf_status require_device() {
   return PF_OK;
 }
 
+// Streams and events for G filter groups.  The device runs a process's streams
+// on four hardware queues, and a new stream goes to the one with the fewest (or
+// makes one, while there are fewer than four); groups that share a queue don't
+// overlap (512 filters in two groups: 116 us an interval against 87).  Streams
+// made one after another get queues of their own where the counts are even, and
+// the second handle of a process could find them otherwise: three streams made
+// first, and dropped afterwards, even them out.  (A group on the caller's
+// stream, whose queue is anyone's, shared it with the other group in every
+// fourth or so handle of a process.)
+pf_status add_streams(pf_handle* H, int G) {
+  if (!H->ev_fork) HIP_TRY(hipEventCreateWithFlags(&H->ev_fork, hipEventDisableTiming));
+  if ((int)H->side.size() >= G) return PF_OK;
+  hipStream_t even[3] = {};
+  hipError_t e = hipSuccess;
+  for (auto& x : even)
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&x, hipStreamNonBlocking);
+  while (e == hipSuccess && (int)H->side.size() < G) {
+    hipStream_t st;
+    if ((e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking)) == hipSuccess)
+      H->side.push_back(st);
+  }
+  while (e == hipSuccess && H->ev_join.size() < H->side.size()) {
+    hipEvent_t ej;
+    if ((e = hipEventCreateWithFlags(&ej, hipEventDisableTiming)) == hipSuccess)
+      H->ev_join.push_back(ej);
+  }
+  for (auto x : even)
+    if (x) (void)hipStreamDestroy(x);
+  HIP_TRY(e);
+  return PF_OK;
+}
+
 // Filters largest first (longest-processing-time order), dealt to G groups
 // by always giving the next filter to the group with the fewest particles;
 // each group's filters and 256-particle chunks are contiguous in the device
@@ -864,17 +891,10 @@ pf_status build_groups(pf_handle* H, int G) {
                            hipMemcpyHostToDevice, H->stream));
   }
   HIP_TRY(hipStreamSynchronize(H->stream));
-  // a stream and an event per group beyond the first (default priority);
-  // graphs captured for another group count are rebuilt
-  if (G > 1 && !H->ev_fork)
-    HIP_TRY(hipEventCreateWithFlags(&H->ev_fork, hipEventDisableTiming));
-  while ((int)H->side.size() < G - 1) {
-    hipEvent_t ej;
-    HIP_TRY(hipEventCreateWithFlags(&ej, hipEventDisableTiming));
-    H->ev_join.push_back(ej);
-    hipStream_t st;
-    HIP_TRY(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-    H->side.push_back(st);
+  // a stream and an event per group when there are several (default
+  // priority); graphs captured for another group count are rebuilt
+  if (G > 1) {
+    if (pf_status st = add_streams(H, G)) return st;
   }
   if (G != H->groups) destroy_graphs(H);
   H->groups = G;
