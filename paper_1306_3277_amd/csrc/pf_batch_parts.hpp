@@ -62,7 +62,10 @@ __device__ __forceinline__ double propagate_one(const Real* __restrict__ xp,
     }
   } else {
     ObsAhead<D> obs;
-    if constexpr (D <= OBS_AHEAD) obs.fetch(yrow, A.obs_pos);
+    // (held through the substeps of the accurate form, which leave the scalar
+    // unit less room, they cost 0.7% more instructions: 95.5 us an interval of
+    // 512 filters in one group against 94.4 fetched at their use)
+    if constexpr (D <= OBS_AHEAD && !ACC) obs.fetch(yrow, A.obs_pos);
     Real x[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) x[i] = xp[(int64_t)i * A.ld + src];
@@ -91,6 +94,7 @@ __device__ __forceinline__ double propagate_one(const Real* __restrict__ xp,
       }
 #pragma unroll
       for (int i = 0; i < D; ++i) x[i] = (Real)xa[i];
+      if constexpr (D <= OBS_AHEAD) obs.fetch(yrow, A.obs_pos);
       // the log-weight from the state before it is rounded for storage
       l = l96_logdens<D, double>(xa, obs, yrow, A.obs_pos, A.inv_sd, A.lw_cst);
     } else {
