@@ -496,6 +496,7 @@ def simulate(pb, theta=None, data_seed: Optional[int] = None, stream=None, devic
     n = L.pf_simulate_doubles(C.byref(hc.cfg))
     buf = torch.zeros(int(n), dtype=torch.float64, device=device)
     sh = _stream_handle(stream)
+    torch.cuda.current_stream(buf.device).synchronize()  # cleared there, simulated on `stream`
     _check(L.pf_simulate(C.byref(hc.cfg), _dp(th), int(pb.data_seed if data_seed is None
                                                          else data_seed),
                          C.c_void_p(buf.data_ptr()), C.c_size_t(int(n)), C.c_void_p(sh)))

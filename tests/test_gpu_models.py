@@ -156,3 +156,16 @@ def test_batched_rejects_more_than_the_largest_filter(pfm):
                                                   dtype=np.int64))
     with pytest.raises(pfm.PfError):
         pfm.Filter(pb, precision=pfm.PF_FP64, layout=pfm.PF_LAYOUT_BATCHED)
+
+
+def test_simulate_on_another_stream_waits_for_its_buffer(pfm):
+    """The output buffer is cleared on torch's current stream: work queued there
+    must not clear it under (or after) the simulation on the caller's."""
+    import torch
+    pb = W.windkessel(N=1, T=20)
+    _, y = pfm.simulate(pb)
+    a = torch.ones(4096, 4096, device="cuda")
+    for _ in range(20):
+        a @ a
+    _, z = pfm.simulate(pb, stream=torch.cuda.Stream())
+    np.testing.assert_array_equal(y, z)
