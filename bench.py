@@ -55,6 +55,7 @@ def log(msg):
 
 # the sources each profiled kernel family is built from
 BATCHED_SOURCES = ("paper_1306_3277_amd/csrc/pf_batched.hip",
+                   "paper_1306_3277_amd/csrc/pf_batch_parts.hpp",
                    "paper_1306_3277_amd/csrc/pf_device.hpp",
                    "paper_1306_3277_amd/csrc/pf_internal.hpp")
 PLAIN_SOURCES = ("paper_1306_3277_amd/csrc/pf_kernels.hip",

@@ -171,13 +171,15 @@ pf_status pf_get_trace(pf_handle* h, double* ell_out, double* ess_out);
 pf_status pf_destroy(pf_handle* h);
 
 /* Run n_steps observation intervals (pf_step + pf_resample each) by replaying
- * HIP graphs captured on the first call (and again after a change of tuning
- * or resampler).  Each graph is captured on one stream and holds kernel
- * launches only: graphs of 1, 2, 4, ... 128 intervals (up to 8 for the plain
- * layout with more than four filters), of every filter (plain layout) or of
- * one filter group (batched layout, launched on the group's own stream
- * between a fork from and a join into the handle's stream); a run replays
- * the longest that fit first (200 = 128 + 64 + 8).  A batched handle set to
+ * HIP graphs, each captured when a run first needs one of its length (and
+ * again after a change of tuning or resampler).  Each graph is captured on
+ * one stream and holds kernel launches only: graphs of 1, 2, 4, ... 128
+ * intervals (up to 8 for the plain layout with more than four filters), of
+ * every filter (plain layout) or of one filter group (batched layout: the
+ * first group's on the handle's stream, the others on streams of their own
+ * between a fork from and a join into it); a run replays the longest that fit
+ * first (200 = 128 + 64 + 8).  Plain windkessel filters of up to 2,048
+ * particles (several: 4,096) take one launch per chunk of intervals instead.  A batched handle set to
  * eager replay (pf_set_replay, or pf_autotune when it measured eager
  * launches faster on this host) issues the same kernels as eager launches
  * instead.  Same results as the eager calls either way. */
@@ -229,9 +231,9 @@ typedef struct pf_wk_mh {
 /* B independent chains, one per filter slot of the windkessel handle h (its
  * flow series, observations, observation sd and h; its particles are
  * untouched), all iterations of a chain in one wave (for very many chains,
- * one lane) of one kernel on the
- * handle's stream (asynchronous).  The random numbers are inputs, device
- * arrays (FP64, 8-byte aligned, not overlapping the outputs):
+ * one lane) of one kernel on the handle's stream (asynchronous).  The random
+ * numbers are inputs, device arrays (FP64, 8-byte aligned, not overlapping the
+ * outputs):
  *   theta0 [B][4]       initial (R, C, Z, sigma^2), each > 0;
  *   prop   [iters][B][4] u_R, u_C, u_Z uniforms in (0, 1) and g, a
  *                       Gamma(ig_prop_shape, 1) variate;

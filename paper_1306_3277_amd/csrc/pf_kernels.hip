@@ -9,12 +9,14 @@
 //                           of exp(lw - M); for each particle the number of
 //                           strata its cumulative weight covers, and a mark
 //                           (its index) on the first stratum it owns
-//   K4 tile gather          per tile of 1024 outputs, a running maximum over
+//   K4 tile gather          per tile of 256 outputs, a running maximum over
 //                           the marks names every output's ancestor (the
 //                           work per lane does not depend on the weights),
-//                           then the ancestors' states are copied
-// plus initialisation and the synthetic-data simulator.  pf_step runs K1
-// (K2) K3, pf_resample K4.  The state is kept in 64-particle tiles (pidx).
+//                           then the ancestors' states are copied; only
+//                           where the resampled set itself is wanted, K1
+//                           names and gathers its ancestors the same way
+// plus the stateless resampler's kernels, initialisation and the
+// synthetic-data simulator.  The state is kept in 64-particle tiles (pidx).
 #include <math.h>
 
 #include "pf_device.hpp"
