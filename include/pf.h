@@ -175,12 +175,12 @@ pf_status pf_destroy(pf_handle* h);
  * again after a change of tuning or resampler).  Each graph is captured on
  * one stream and holds kernel launches only: graphs of 1, 2, 4, ... 128
  * intervals (up to 8 for the plain layout with more than four filters), of
- * every filter (plain layout) or of one filter group (batched layout: the
- * first group's on the handle's stream, the others on streams of their own
- * between a fork from and a join into it); a run replays the longest that fit
- * first (200 = 128 + 64 + 8).  Plain windkessel filters of up to 2,048
- * particles (several: 4,096) take one launch per chunk of intervals instead.  A batched handle set to
- * eager replay (pf_set_replay, or pf_autotune when it measured eager
+ * every filter (plain layout) or of one filter group (batched layout; several
+ * groups' are launched on streams of their own between a fork from and a join
+ * into the handle's stream); a run replays the longest that fit first (200 =
+ * 128 + 64 + 8).  Plain windkessel filters of up to 2,048 particles (several:
+ * 4,096) take one launch per chunk of intervals instead.  A batched handle set
+ * to eager replay (pf_set_replay, or pf_autotune when it measured eager
  * launches faster on this host) issues the same kernels as eager launches
  * instead.  Same results as the eager calls either way. */
 pf_status pf_graph_run(pf_handle* h, int32_t n_steps);
