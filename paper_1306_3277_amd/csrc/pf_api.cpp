@@ -728,6 +728,12 @@ pf_status enqueue_resample(pf_handle* H, hipStream_t s, const double* u) {
 // one workgroup.
 pf_status enqueue_small(pf_handle* H, hipStream_t s, int n) {
   const pf_config& c = H->cfg;
+  // a caller's capture is refused before anything is recorded into it: its
+  // replays would run past T, and the write-out below would not have run
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &cap));
+  if (cap != hipStreamCaptureStatusNone)
+    return fail(PF_E_DEVICE, "pf_graph_run on a capturing stream");
   if (H->marks_pending)
     for (int b = 0; b < c.B; ++b)
       if (pf_status st = plain_anc_out(H, b, s)) return st;

@@ -203,8 +203,8 @@ hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* a
 // particles (a: the first filter's arguments; off: [B + 1] first particles),
 // a workgroup each, after a launch that draws their random numbers into nz
 // (n K B ceil(max_n / 256) 256 values in the state's precision) and rec (B n (K + 3)
-// doubles).  The ancestors pending must not be marks; they are the array
-// afterwards.  Refused on a capturing stream.
+// doubles).  The ancestors pending must not be marks (flagged in the filter's
+// scalars if they are); they are the array afterwards.
 hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, double* lw,
                             int32_t* anc, const PlainArgs& a, const int64_t* off, void* nz,
                             double* rec, int n, hipStream_t s);

@@ -430,6 +430,8 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
   const int t0 = fs->t;
   const uint32_t iter = fs->iter;
   const int amode = fs->amode;
+  // marks are the caller's to write out first: flagged, not run past silently
+  if (tid == 0 && amode == AMODE_MARKS) atomicOr(&fs->pad, 1);
   bool carry = fs->carry != 0;
   const double* th = A.theta + (size_t)b * 8;
   const Key key{A.key.lo, A.key.hi};
@@ -614,12 +616,6 @@ hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, doub
   if (max_n < 1 || max_n > SMALL_MAXN || a.K > SMALL_MAXK || n < 1 || B < 1 || B > 65535 ||
       n > 65535)
     return hipErrorInvalidValue;
-  // (as a replayed graph of the multi-kernel path would be, a call under the
-  // caller's own capture is refused: its replays would run past T)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(s, &cap);
-  if (e != hipSuccess) return e;
-  if (cap != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
   const dim3 g((unsigned)((max_n + K1_NT - 1) / K1_NT), (unsigned)n, (unsigned)B);
   if (prec == 0)
     hipLaunchKernelGGL(k_small_noise<double>, g, K1_NT, 0, s, a, off, (double*)nz, rec, n);

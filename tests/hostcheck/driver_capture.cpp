@@ -1,0 +1,82 @@
+// pf_graph_run of small windkessel filters on a stream that its caller is
+// capturing, over the CPU stand-in runtime (fake_hip.cpp): refused, with
+// nothing recorded into the capture, and the ancestors that were pending
+// before are still written out by the next run.  The kernel stubs count their
+// calls by name.
+#include <hip/hip_runtime_api.h>
+
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "pf.h"
+
+static std::map<std::string, int> g_calls;
+extern "C" void note_kernel(const char* name) { ++g_calls[name]; }
+
+#define CHECK_(c)                                          \
+  do {                                                     \
+    if (!(c)) {                                            \
+      printf("FAIL %s (%s)\n", #c, pf_last_error());       \
+      exit(1);                                             \
+    }                                                      \
+  } while (0)
+
+int main() {
+  const int B = 2, T = 8, K = 3;
+  const std::vector<int64_t> np = {300, 70};
+  const std::vector<int32_t> idx = {0};
+  std::vector<double> obs(T, 95.0), q((size_t)T * K + 1, 100.0), theta;
+  const double a = std::exp(-0.01 / 1.5);
+  for (int b = 0; b < B; ++b)
+    for (double v : {a, 1.0 - a, 0.03, 0.5, 90.0, 15.0}) theta.push_back(v);
+  pf_config c{};
+  c.model = PF_MODEL_WK;
+  c.precision = PF_FP64;
+  c.layout = PF_LAYOUT_PLAIN;
+  c.d = 1;
+  c.K = K;
+  c.T = T;
+  c.h = 0.01;
+  c.n_obs = 1;
+  c.obs_idx = idx.data();
+  c.obs_sd = 1.0;
+  c.obs = obs.data();
+  c.q = q.data();
+  c.B = B;
+  c.n_theta = 6;
+  c.n_particles = np.data();
+  c.theta = theta.data();
+  const size_t n = pf_workspace_bytes(&c);
+  CHECK_(n > 0);
+  void* ws = aligned_alloc(256, (n + 255) / 256 * 256);
+  hipStream_t s;
+  CHECK_(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+  pf_handle* h = nullptr;
+  CHECK_(pf_init(&c, ws, n, s, &h) == PF_OK);
+  CHECK_(pf_step(h) == PF_OK);
+  CHECK_(pf_resample(h) == PF_OK);  // the ancestors are pending as marks now
+  const auto before = g_calls;
+  CHECK_(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess);
+  CHECK_(pf_graph_run(h, 2) == PF_E_DEVICE);
+  CHECK_(g_calls == before);
+  hipGraph_t g;
+  CHECK_(hipStreamEndCapture(s, &g) == hipSuccess);
+  CHECK_(hipGraphDestroy(g) == hipSuccess);
+  // the refused call moved nothing on: the run writes the marks out first
+  CHECK_(pf_graph_run(h, 2) == PF_OK);
+  CHECK_(g_calls["launch_tile_anc"] == B);
+  CHECK_(g_calls["launch_small_run"] == 1);
+  // nothing pending as marks after it
+  CHECK_(pf_graph_run(h, 5) == PF_OK);
+  CHECK_(g_calls["launch_tile_anc"] == B);
+  CHECK_(pf_graph_run(h, 1) == PF_E_STATE);  // t = T
+  CHECK_(pf_destroy(h) == PF_OK);
+  CHECK_(hipStreamDestroy(s) == hipSuccess);
+  free(ws);
+  printf("done\n");
+  return 0;
+}

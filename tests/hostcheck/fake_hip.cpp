@@ -261,6 +261,10 @@ hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   g->streams.push_back(f);
   return hipSuccess;
 }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* out) {
+  *out = S(s)->cap ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t* out) {
   FStream* f = S(s);
   CHECK(f->cap && f->origin, "end capture on a stream that did not begin one");

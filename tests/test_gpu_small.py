@@ -102,3 +102,35 @@ def test_small_run_of_uneven_filters_and_lost_weights(env, precision):  # noqa: 
     assert np.all(np.isneginf(g.loglik(allow_numeric=True)[0]))
     f.close()
     g.close()
+
+
+def test_small_run_refused_on_a_capturing_stream(env):  # noqa: F811
+    """pf_graph_run inside a caller's capture is refused with nothing recorded;
+    the resampling that was pending is not lost."""
+    torch, pfm = env
+    import workloads as W
+    T = 6
+    pb = W.windkessel(N=700, T=T, K=3)
+    pb = pb.with_obs(90.0 + 5.0 * np.random.default_rng(1).standard_normal((T, 1)))
+    s = torch.cuda.Stream()
+    f, g = (pfm.Filter(pb, stream=s) for _ in range(2))
+    for h in (f, g):
+        h.advance(2)
+    x = torch.zeros(4, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        graph.capture_begin(capture_error_mode="thread_local")
+        with pytest.raises(pfm.PfError):
+            g.graph_run(2)
+        x.add_(1.0)
+        graph.capture_end()
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(x.cpu(), torch.ones(4))
+    f.advance(T - 2)
+    g.graph_run(T - 2)
+    for a, b in zip(_outputs(f), _outputs(g)):
+        np.testing.assert_array_equal(a, b)
+    f.close()
+    g.close()

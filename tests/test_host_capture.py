@@ -1,0 +1,31 @@
+"""pf_graph_run inside a caller's stream capture, on the CPU stand-in runtime
+(tests/hostcheck): a refused call leaves the handle as it was."""
+import os
+import subprocess
+
+import pytest
+from test_host_runtime import CSRC, CXX, HERE, ROOT, launcher_stubs
+
+
+def test_refused_capture_leaves_the_pending_ancestors(tmp_path):
+    if not os.path.exists(CXX):
+        pytest.skip("ROCm clang++ not found")
+    stubs, names = launcher_stubs()
+    for name in names:  # every stub also tells the driver its name
+        stubs = stubs.replace(f"hipError_t {name}(", f"hipError_t {name} (")
+        head, tail = stubs.split(f"hipError_t {name} (", 1)
+        stubs = (head + f"hipError_t {name}(" +
+                 tail.replace("{ fake_kernel(", f'{{ note_kernel("{name}"); fake_kernel(', 1))
+    (tmp_path / "stubs.cpp").write_text('extern "C" void note_kernel(const char* name);\n' + stubs)
+    exe = str(tmp_path / "driver")
+    cmd = [CXX, "-std=c++17", "-g", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-w", "-fsanitize=address,undefined",
+           "-fno-omit-frame-pointer", "-o", exe, os.path.join(CSRC, "pf_api.cpp"),
+           os.path.join(HERE, "fake_hip.cpp"), os.path.join(HERE, "driver_capture.cpp"),
+           str(tmp_path / "stubs.cpp")]
+    r = subprocess.run(cmd, capture_output=True, text=True, cwd=str(tmp_path))
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1",
+               UBSAN_OPTIONS="halt_on_error=1")
+    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120)
+    assert r.returncode == 0 and "done" in r.stdout, (r.stdout + r.stderr)[-4000:]
