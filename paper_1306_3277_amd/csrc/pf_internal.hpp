@@ -147,6 +147,30 @@ constexpr int K4_NT = 256;  // tile-gather threads
 constexpr int K4_PER = 1;   // outputs per tile-gather lane
 constexpr int K4_TILE = K4_NT * K4_PER;  // outputs per tile (one owner each)
 static_assert(K4_TILE == K1_NT, "a propagation block names the ancestors of one tile");
+// The multinomial search of N cumulative weights (1 <= N < 2^31, so no sum of N
+// and a block size fits 32 bits): the level it starts at (0: the weights, 1: the
+// last of every 16, 2: of every 256), the entries of that level and of the
+// 16s, and the samples of the level that a block holds, one per `per` entries.
+constexpr int MULTI_NB = 1024;
+struct MultiLevels {
+  int32_t n16, level, nt, per, ns;
+};
+__host__ __device__ __forceinline__ int32_t blocks_of(int32_t n, int32_t size) {
+  return (n - 1) / size + 1;  // n >= 1
+}
+__host__ __device__ __forceinline__ MultiLevels multi_levels(int32_t N) {
+  MultiLevels m;
+  m.n16 = blocks_of(N, 16);
+  m.level = N <= MULTI_NB ? 0 : m.n16 <= MULTI_NB ? 1 : 2;
+  m.nt = m.level == 0 ? N : m.level == 1 ? m.n16 : blocks_of(N, 256);
+  m.per = blocks_of(m.nt, MULTI_NB);
+  m.ns = blocks_of(m.nt, m.per);
+  return m;
+}
+// A scan lane's last particle, of the K3_PER from j0 on (j0 < N).
+__host__ __device__ __forceinline__ int32_t lane_last(int32_t j0, int32_t N) {
+  return j0 + (N - j0 < K3_PER ? N - j0 : K3_PER) - 1;
+}
 // particles a single workgroup steps or resamples on its own
 constexpr int SMALL_MAXN = 4096;
 constexpr int SMALL_MAXK = 253;  // substeps per interval such a run takes

@@ -934,7 +934,7 @@ __global__ __launch_bounds__(K3_NT) void k_scan_mark(const double* __restrict__ 
     for (int e = 0; e < K3_PER; ++e)
       if (j0 + e < N) A.wcum[j0 + e] = W[e + 1];
     // the ends of every 16 and every 256 of them
-    const int32_t jl = min(j0 + K3_PER, N) - 1;  // the lane's last particle
+    const int32_t jl = j0 < N ? lane_last(j0, N) : 0;  // the lane's last particle
     double wl = W[1];
 #pragma unroll
     for (int e = 1; e < K3_PER; ++e) wl = jl == j0 + e ? W[e + 1] : wl;
@@ -1186,8 +1186,6 @@ __global__ __launch_bounds__(K1_NT) void k_rejection(const double* __restrict__ 
 // 1,000 / 65,536 / 10^6 particles: 12.6 / 18.7 / 109 us where the search of the
 // weights took 14.0 / 20.7 / 137; seven values a round in the weights alone gave
 // 12.3 / 19.1 / 186.
-constexpr int MULTI_NB = 1024;
-
 // The first of the n non-decreasing values at W + lo that is above thr (lo + n:
 // none).
 __device__ __forceinline__ int32_t first_above(const double* W, int32_t lo, int32_t n,
@@ -1219,12 +1217,9 @@ __global__ __launch_bounds__(K1_NT) void k_multinomial(const int32_t* __restrict
   __shared__ double ends[MULTI_NB];
   const int32_t N = (int32_t)A.N;
   const int32_t k = (int32_t)(blockIdx.x * K1_NT + threadIdx.x);
-  const int32_t n16 = (N + 15) / 16;
-  const int level = N <= MULTI_NB ? 0 : n16 <= MULTI_NB ? 1 : 2;
+  const auto [n16, level, nt, per, ns] = multi_levels(N);
   const double* top = level == 0 ? A.wcum : level == 1 ? A.w16 : A.w256;
-  const int32_t nt = level == 0 ? N : level == 1 ? n16 : (N + 255) / 256;
   // sample i: the end of the level's entries [i per, (i + 1) per)
-  const int32_t per = (nt + MULTI_NB - 1) / MULTI_NB, ns = (nt + per - 1) / per;
   double e[MULTI_NB / K1_NT];
 #pragma unroll
   for (int q = 0; q < MULTI_NB / K1_NT; ++q)
@@ -1247,7 +1242,7 @@ __global__ __launch_bounds__(K1_NT) void k_multinomial(const int32_t* __restrict
       a = j;
     } else {
       int32_t js = -1;
-      for (int i = (N + K3_SPAN - 1) / K3_SPAN - 1; i >= 0 && js < 0; --i) js = jc_all[A.own0 + i];
+      for (int i = (N - 1) / K3_SPAN; i >= 0 && js < 0; --i) js = jc_all[A.own0 + i];
       a = js >= 0 ? js : 0;
     }
   }
