@@ -724,6 +724,34 @@ pf_status enqueue_resample(pf_handle* H, hipStream_t s, const double* u) {
   return PF_OK;
 }
 
+// Whether a run of the small windkessel filters goes one workgroup per filter
+// (pf_small.hip).  With systematic, stratified and multinomial resampling it
+// always does (1,024 particles, K = 10: 6.3, 10.0 and 9.4 us an interval against
+// 12.2, 15.5 and 14.6 of the multi-kernel path's graphs).  A Metropolis move or a
+// rejection attempt takes a lane's particles one after the other there, and up
+// to four waves of a SIMD, where the multi-kernel path spreads them over the
+// device but takes the filters in turn: 0.13 us a move for 64 particles, 0.26
+// for 128, 0.53 from 193 to 1,024, 0.69, 0.89 and 1.10 for 2,048, 3,000 and
+// 4,096, against 0.17 to 0.23 a filter; besides the moves 5 to 13 us an interval
+// against 11 to 12 a filter.  So one filter of 1,024 takes 8 moves in 9.7 us
+// against 14.2, 32 in 22.9 against 18.8, 508 in 283 against 104; four of 2,048
+// take 128 in 96 against 143.  Rejection is bound by its attempts, about N an
+// output on collapsed weights: 3.8 ms an interval against 1.4 for one filter of
+// 1,024 (spread weights: 14.0 us against 16.7), 0.97 against 1.28 for three of
+// 300 (12.7 us against 43), 6.7 against 8.2 for three of 2,048, 15.6 against 19.0
+// for four of 4,096, 15.0 against 9.6 for two; where collapsed weights lose up to
+// a third, spread ones halve (128 particles: 203 us against 150, 8.5 against 13.4;
+// two filters of 300: 0.95 ms against 0.85, 12.7 us against 29).
+bool small_pays(const pf_handle* H) {
+  if (H->rs.scheme != pfk::RS_METROPOLIS && H->rs.scheme != pfk::RS_REJECTION) return true;
+  const int64_t n = *std::max_element(H->np.begin(), H->np.end());
+  const double move = n <= 192 ? 0.13 * (double)((n + 63) / 64)
+                               : 0.33 + 0.19 * (double)((n + 1023) / 1024);
+  if (H->rs.scheme == pfk::RS_REJECTION) return move <= 0.28 * H->cfg.B;
+  const double rest = n <= 1024 ? 5.0 : n <= 2048 ? 7.0 : 13.0;
+  return rest + move * H->rs.steps <= H->cfg.B * (12.0 + 0.2 * H->rs.steps);
+}
+
 // n intervals of the plain layout's small windkessel filters, each filter in
 // one workgroup.
 pf_status enqueue_small(pf_handle* H, hipStream_t s, int n) {
@@ -740,8 +768,10 @@ pf_status enqueue_small(pf_handle* H, hipStream_t s, int n) {
   H->marks_pending = false;
   const PlainArgs a = plain_args(H, 0);
   const int max_n = (int)*std::max_element(H->np.begin(), H->np.end());
+  // (an interval of rejection resampling can take 20 ms: short launches)
+  const int most = H->rs.scheme == pfk::RS_REJECTION ? 16 : n;
   for (int left = n; left > 0;) {
-    const int m = std::min(left, (int)H->L.small_n);
+    const int m = std::min({left, most, (int)H->L.small_n});
     HIP_TRY(pfk::launch_small_run(c.precision, c.B, max_n, H->ws + H->L.x_cur,
                                   H->ws + H->L.x_tmp, H->at<double>(H->L.lw),
                                   H->at<int32_t>(H->L.anc), a, H->at<int64_t>(H->L.b_off),
@@ -1253,7 +1283,7 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
   if (H->t + n_steps > H->cfg.T)
     return fail(PF_E_STATE, "%d steps from t = %d exceed T = %d", n_steps, H->t, H->cfg.T);
   if (n_steps == 0) return PF_OK;
-  if (H->L.small_n > 0 && !H->hist) {
+  if (H->L.small_n > 0 && !H->hist && small_pays(H)) {
     if ((st = enqueue_small(H, H->stream, n_steps))) return st;
     H->t += n_steps;
     return PF_OK;

@@ -134,3 +134,39 @@ def test_small_run_refused_on_a_capturing_stream(env):  # noqa: F811
         np.testing.assert_array_equal(a, b)
     f.close()
     g.close()
+
+
+@pytest.mark.parametrize("sizes,scheme,steps,frac", [
+    ((64,), 4, 0, float("inf")), ((64,), 4, 0, 0.5), ((700,), 4, 0, float("inf")),
+    ((300, 200, 257), 4, 0, float("inf")), ((300, 200, 257), 4, 0, 0.5),
+    ((4096, 1, 3000, 2049, 65), 4, 0, float("inf")), ((193, 65), 4, 0, 0.5),
+    ((1024,), 2, 21, float("inf")), ((1024,), 2, 22, float("inf")), ((193,), 2, 40, 0.5),
+    ((64,), 2, 508, float("inf")), ((2048, 1500), 2, 33, float("inf")),
+    ((4096, 4096), 2, 0, float("inf"))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_rejection_and_many_moves_equal_eager_steps(env, sizes, scheme, steps, frac,  # noqa: F811
+                                                    precision):
+    """Rejection and long Metropolis runs go one workgroup per filter or the
+    multi-kernel path's graphs by sizes, filters and moves: the eager steps'
+    bits either way, over more intervals than a launch of rejection takes and
+    with eager steps between."""
+    _, pfm = env
+    import dataclasses
+
+    import workloads as W
+    T = 24
+    base = dataclasses.replace(W.windkessel(N=1, T=T, K=3, B=len(sizes), seed=steps), obs_sd=8.0)
+    pb = dataclasses.replace(
+        base.with_obs(90.0 + 5.0 * np.random.default_rng(steps).standard_normal((T, 1))),
+        n_particles=np.array(sizes, dtype=np.int64))
+    f, g = (pfm.Filter(pb, precision=precision) for _ in range(2))
+    for h in (f, g):
+        h.set_resampler(scheme, steps, frac)
+    f.advance(T)
+    g.graph_run(18)
+    g.advance(2)
+    g.graph_run(4)
+    for a, b in zip(_outputs(f), _outputs(g)):
+        np.testing.assert_array_equal(a, b)
+    f.close()
+    g.close()
