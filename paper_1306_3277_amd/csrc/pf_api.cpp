@@ -273,6 +273,8 @@ struct pf_handle {
   std::vector<hipStream_t> side;
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_join;
+  // what a null-stream handle's graphs are captured on, until all of them are
+  hipStream_t cap_stream = nullptr;
   // timing
   bool timing = false;
   struct Ev {
@@ -957,8 +959,17 @@ pf_status drain(pf_handle* H) {
   return PF_OK;
 }
 
+// (nothing is ever issued on it, only captured)
+void drop_cap_stream(pf_handle* H) {
+  if (!H->cap_stream) return;
+  (void)hipStreamSynchronize(H->cap_stream);
+  (void)hipStreamDestroy(H->cap_stream);
+  H->cap_stream = nullptr;
+}
+
 void destroy_streams(pf_handle* H) {
   destroy_graphs(H);
+  drop_cap_stream(H);
   for (auto s : H->side) (void)hipStreamDestroy(s);
   for (auto e : H->ev_join) (void)hipEventDestroy(e);
   if (H->ev_fork) (void)hipEventDestroy(H->ev_fork);
@@ -999,17 +1010,17 @@ pf_status capture_graph(pf_handle* H, hipStream_t cs, int g, int v) {
   return PF_OK;
 }
 
-// Captures the graphs that a run of n intervals replays and that are not
-// there yet.  Every capture is on one stream and holds kernel launches only
-// (no event, copy or memset), so a graph never refers to an event or another
-// stream: 2^v intervals for a step v of the ladder, of every filter (plain
+// Captures the graphs that a run of n intervals replays, or the whole ladder,
+// where they are not there yet.  Every capture is on one stream and holds
+// kernel launches only (no event, copy or memset), so a graph never refers to
+// an event or another stream: 2^v intervals for a step v of the ladder, of every filter (plain
 // layout) or of each filter group (batched layout).  The groups' graphs are
 // launched on their own streams between an eager fork and join.  The null
 // stream cannot be captured: a caller that uses it has its graphs captured on
 // another stream, and launched on the null stream all the same (on another,
 // every run would wait for the null stream's work and make it wait in turn,
 // about 15 us each way).
-pf_status ensure_graphs(pf_handle* H, int n) {
+pf_status ensure_graphs(pf_handle* H, int n, bool whole) {
   const int ng = H->cfg.layout == PF_LAYOUT_BATCHED ? H->groups : 1;
   const int nv = graph_ladder(H);
   if (H->gexecs.empty()) {
@@ -1017,27 +1028,63 @@ pf_status ensure_graphs(pf_handle* H, int n) {
     H->graphs.assign((size_t)ng * nv, nullptr);
     H->gexecs.assign((size_t)ng * nv, nullptr);
   }
-  hipStream_t cs = H->stream, own = nullptr;
   const bool tm = H->timing;
   H->timing = false;
-  pf_status st = for_graphs(nv, n, [&](int v) -> pf_status {
+  auto capture = [&](int v) -> pf_status {
     for (int g = 0; g < ng; ++g) {
       if (H->gexecs[(size_t)g * nv + v]) continue;
-      if (!cs) {
-        HIP_TRY(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
-        cs = own;
-      }
-      if (pf_status e = capture_graph(H, cs, g, v)) return e;
+      if (!H->stream && !H->cap_stream)
+        HIP_TRY(hipStreamCreateWithFlags(&H->cap_stream, hipStreamNonBlocking));
+      if (pf_status e = capture_graph(H, H->stream ? H->stream : H->cap_stream, g, v)) return e;
     }
     return PF_OK;
-  });
-  if (own) {  // (nothing was issued on it, only captured)
-    (void)hipStreamSynchronize(own);
-    (void)hipStreamDestroy(own);
-  }
+  };
+  pf_status st = PF_OK;
+  if (whole)
+    for (int v = 0; v < nv && !st; ++v) st = capture(v);
+  else
+    st = for_graphs(nv, n, capture);
   H->timing = tm;
   // (graphs of an earlier run may still be replaying: wait before they go)
   if (st && drain(H) == PF_OK) destroy_graphs(H);
+  return st;
+}
+
+// What a first run's lengths left of the ladder, so that a later run of another
+// length does not wait for its capture (0.4 to 1.5 ms in all).  It is captured
+// once the run is issued, while the device works on it.  A failure is not this
+// run's: the run that needs the graph meets it.
+void finish_graphs(pf_handle* H) {
+  if (std::find(H->gexecs.begin(), H->gexecs.end(), nullptr) == H->gexecs.end()) return;
+  (void)ensure_graphs(H, 0, true);
+  drop_cap_stream(H);
+  err_clear();
+}
+
+// n intervals from the handle's graphs (those captured that are missing).
+pf_status run_graphs(pf_handle* H, int n) {
+  const hipStream_t ls = H->stream;
+  pf_status st;
+  if ((st = ensure_graphs(H, n, false))) return st;
+  const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
+  if (!batched) H->marks_pending = true;
+  const int G = batched ? H->groups : 1;
+  if (G > 1 && (st = fork_groups(H, ls))) return st;
+  st = for_graphs(H->gnv, n, [&](int v) -> pf_status {
+    for (int g = 0; g < G; ++g)
+      HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * H->gnv + v], group_stream(H, g, ls)));
+    return PF_OK;
+  });
+  if (st) return st;
+  if (G > 1 && (st = join_groups(H, ls))) return st;
+  return PF_OK;
+}
+
+// n intervals issued from the handle's graphs, or eagerly where it is set to.
+pf_status run_intervals(pf_handle* H, int n) {
+  const bool eager = H->eager_replay && H->cfg.layout == PF_LAYOUT_BATCHED;
+  const pf_status st = eager ? enqueue_batched(H, H->stream, n) : run_graphs(H, n);
+  if (!st) H->t += n;
   return st;
 }
 
@@ -1288,25 +1335,8 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
     H->t += n_steps;
     return PF_OK;
   }
-  const hipStream_t ls = H->stream;
-  if (H->eager_replay && H->cfg.layout == PF_LAYOUT_BATCHED) {
-    if ((st = enqueue_batched(H, ls, n_steps))) return st;
-    H->t += n_steps;
-    return PF_OK;
-  }
-  if ((st = ensure_graphs(H, n_steps))) return st;
-  if (H->cfg.layout == PF_LAYOUT_PLAIN) H->marks_pending = true;
-  const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
-  const int G = batched ? H->groups : 1;
-  if (G > 1 && (st = fork_groups(H, ls))) return st;
-  st = for_graphs(H->gnv, n_steps, [&](int v) -> pf_status {
-    for (int g = 0; g < G; ++g)
-      HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * H->gnv + v], group_stream(H, g, ls)));
-    return PF_OK;
-  });
-  if (st) return st;
-  if (G > 1 && (st = join_groups(H, ls))) return st;
-  H->t += n_steps;
+  if ((st = run_intervals(H, n_steps))) return st;
+  finish_graphs(H);
   return PF_OK;
 }
 
@@ -1757,9 +1787,9 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
   }
   // capture the graphs before the loop
   if (!kalman) {
-    if ((st = ensure_graphs(H, 1))) return st;
+    if ((st = ensure_graphs(H, 1, false))) return st;
     for (int32_t i = 1; i < T; i <<= 1)
-      if ((st = ensure_graphs(P, std::min(i, 1 << (graph_ladder(P) - 1))))) return st;
+      if ((st = ensure_graphs(P, std::min(i, 1 << (graph_ladder(P) - 1)), false))) return st;
   }
 
   pfk::Smc2Args S{};
@@ -1852,7 +1882,7 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
     P->t = 0;
     P->phase = 0;
     P->marks_pending = false;
-    if (i > 1 && (st = pf_graph_run(P, i - 1))) return st;
+    if (i > 1 && (st = run_intervals(P, i - 1))) return st;
     prop.x = P->ws + state_buf(P, i - 1);
     HIP_TRY(pfk::launch_smc2_finish(c.model == PF_MODEL_WK ? 1 : c.d, c.precision, H->ws + cur,
                                     H->at<int32_t>(H->L.anc), la_d + (size_t)(i - 1) * B,
@@ -1860,9 +1890,13 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
                                     (double*)(ws + L.theta_tr) + (size_t)(i - 1) * B * nth, prop,
                                     A, S, s));
     // 4. every attached filter advances one interval
-    if ((st = pf_graph_run(H, 1))) return st;
+    if ((st = run_intervals(H, 1))) return st;
   }
   HIP_TRY(pfk::launch_theta_resample(S, T - 1, 0.5, 0, nullptr, ess_d + (T - 1), s));
+  if (!kalman) {
+    finish_graphs(H);
+    finish_graphs(P);
+  }
 
   // outputs
   std::vector<double> ell((size_t)B * c.T);
@@ -2090,7 +2124,7 @@ pf_status time_graph_replay(pf_handle* H, int n, double* ms_out) {
   pf_status st = do_init(H, H->stream);
   if (st) return st;
   H->eager_replay = false;
-  if ((st = ensure_graphs(H, n)) || (st = pf_graph_run(H, 1))) return st;
+  if ((st = pf_graph_run(H, 1))) return st;  // captures the graphs
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);

@@ -2,7 +2,9 @@
 // capturing, over the CPU stand-in runtime (fake_hip.cpp): refused, with
 // nothing recorded into the capture, and the ancestors that were pending
 // before are still written out by the next run.  The kernel stubs count their
-// calls by name.
+// calls by name.  And which calls capture graphs: a handle's first run of each
+// tuning, whatever its length, and no later one.
+//   driver_capture refused | ladder
 #include <hip/hip_runtime_api.h>
 
 #include <cmath>
@@ -16,6 +18,7 @@
 
 static std::map<std::string, int> g_calls;
 extern "C" void note_kernel(const char* name) { ++g_calls[name]; }
+extern "C" int fake_captures(void);
 
 #define CHECK_(c)                                          \
   do {                                                     \
@@ -25,7 +28,7 @@ extern "C" void note_kernel(const char* name) { ++g_calls[name]; }
     }                                                      \
   } while (0)
 
-int main() {
+static void refused() {
   const int B = 2, T = 8, K = 3;
   const std::vector<int64_t> np = {300, 70};
   const std::vector<int32_t> idx = {0};
@@ -77,6 +80,54 @@ int main() {
   CHECK_(pf_destroy(h) == PF_OK);
   CHECK_(hipStreamDestroy(s) == hipSuccess);
   free(ws);
+}
+
+static void ladder() {
+  for (int layout : {PF_LAYOUT_PLAIN, PF_LAYOUT_BATCHED}) {
+    const int B = 3, T = 300, d = 4;
+    const std::vector<int64_t> np = {300, 70, 1000};
+    const std::vector<int32_t> idx = {0, 1, 2, 3};
+    const std::vector<double> obs((size_t)T * d, 0.5), theta = {8.0, 0.1, 7.0, 0.2, 9.0, 0.1};
+    pf_config c{};
+    c.model = PF_MODEL_L96;
+    c.precision = PF_FP32_MIXED;
+    c.layout = layout;
+    c.d = d;
+    c.K = 2;
+    c.T = T;
+    c.h = 0.05;
+    c.n_obs = d;
+    c.obs_idx = idx.data();
+    c.obs_sd = 0.5;
+    c.obs = obs.data();
+    c.B = B;
+    c.n_theta = 2;
+    c.n_particles = np.data();
+    c.theta = theta.data();
+    const size_t n = pf_workspace_bytes(&c);
+    CHECK_(n > 0);
+    void* ws = aligned_alloc(256, (n + 255) / 256 * 256);
+    pf_handle* h = nullptr;
+    CHECK_(pf_init(&c, ws, n, nullptr, &h) == PF_OK);
+    for (int groups : {1, 2}) {
+      CHECK_(pf_set_tuning(h, 512, groups) == PF_OK);
+      CHECK_(pf_reset(h, 0) == PF_OK);
+      CHECK_(pf_graph_run(h, 10) == PF_OK);
+      const int first = fake_captures();
+      CHECK_(first > 0);
+      for (int len : {1, 3, 20, 255, 4}) {
+        CHECK_(pf_graph_run(h, len) == PF_OK);
+        CHECK_(fake_captures() == first);
+      }
+    }
+    CHECK_(pf_destroy(h) == PF_OK);
+    free(ws);
+  }
+}
+
+int main(int, char** argv) {
+  if (std::string(argv[1]) == "refused") refused();
+  else ladder();
   printf("done\n");
   return 0;
 }

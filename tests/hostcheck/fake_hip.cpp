@@ -74,6 +74,7 @@ struct FExec {
 // objects are never freed, so a use after destruction is caught
 std::set<void*> g_streams, g_events, g_graphs, g_execs;
 FStream g_null;
+int g_captures = 0;
 double g_clock = 0;
 
 FStream* S(hipStream_t s) {
@@ -123,6 +124,8 @@ void op(hipStream_t s, std::function<void()> fn) {
 extern "C" void fake_kernel(hipStream_t s) {
   op(s, [] {});
 }
+// captures begun so far
+extern "C" int fake_captures(void) { return g_captures; }
 
 extern "C" {
 
@@ -254,6 +257,7 @@ hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   FStream* f = S(s);
   CHECK(!f->cap, "begin capture on a stream already capturing");
   FGraph* g = new FGraph();
+  ++g_captures;
   g_graphs.insert(g);
   f->cap = g;
   f->origin = true;

@@ -1,5 +1,6 @@
-"""pf_graph_run inside a caller's stream capture, on the CPU stand-in runtime
-(tests/hostcheck): a refused call leaves the handle as it was."""
+"""pf_graph_run and stream capture, on the CPU stand-in runtime
+(tests/hostcheck): a call inside a caller's capture that is refused leaves the
+handle as it was, and a handle's graphs are all captured by its first run."""
 import os
 import subprocess
 
@@ -7,7 +8,9 @@ import pytest
 from test_host_runtime import CSRC, CXX, HERE, ROOT, launcher_stubs
 
 
-def test_refused_capture_leaves_the_pending_ancestors(tmp_path):
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    tmp_path = tmp_path_factory.mktemp("capture")
     if not os.path.exists(CXX):
         pytest.skip("ROCm clang++ not found")
     stubs, names = launcher_stubs()
@@ -25,7 +28,19 @@ def test_refused_capture_leaves_the_pending_ancestors(tmp_path):
            str(tmp_path / "stubs.cpp")]
     r = subprocess.run(cmd, capture_output=True, text=True, cwd=str(tmp_path))
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    return exe
+
+
+def _run(exe, scenario):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1",
                UBSAN_OPTIONS="halt_on_error=1")
-    r = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=120)
+    r = subprocess.run([exe, scenario], capture_output=True, text=True, env=env, timeout=120)
     assert r.returncode == 0 and "done" in r.stdout, (r.stdout + r.stderr)[-4000:]
+
+
+def test_refused_capture_leaves_the_pending_ancestors(driver):
+    _run(driver, "refused")
+
+
+def test_only_a_first_run_captures(driver):
+    _run(driver, "ladder")
