@@ -54,14 +54,20 @@ __device__ __forceinline__ double kf_interval(const double* th, const KfArgs& A,
 //     and each squaring perturbs the map by an ulp of its entries);
 //   - given the gains the mean's maps m' = alpha m + beta compose by a wave
 //     scan.
+//   - the composed maps round a stationary gain the same way at every interval,
+//     which adds up over a long series; so each lane steps its intervals from
+//     the mean that the scan gave it, and a second scan of what that differs by
+//     corrects the lanes' first means.
 // The logarithms and divisions then run in all lanes at once.  512 chains
-// over T = 100, K = 10: 4.5 us an iteration against 74 (two waves per SIMD,
-// still latency: two intervals per lane interleave); 512 likelihoods: 57 us a
-// call, most of it the copies of the results, against 147.  Against 80-bit
-// arithmetic, over 40 draws of T to 300 and K to 20, its likelihoods are off
-// by 1.8e-15 (relative, in the norm over the filters; the mean of the draws)
-// where the chain's are by 3.1e-15, its increments by 3.7e-15 and 6.1e-15; at
-// K = 1 alone the two change places (9.3e-15 and 7.8e-15 at the most).  Which
+// over T = 100, K = 10: 5.7 us an iteration with the launch and the outputs'
+// allocation (5.6 without the correction) against 74 a lane each (two waves per
+// SIMD, still latency: two intervals per lane interleave); 512 likelihoods: 60
+// us a call, most of it the copies of the results, against 150.  Both forms'
+// arithmetic against 113-bit arithmetic, 500 parameter sets, the likelihood's
+// mean relative error, this form / the chain / this form without the
+// correction: T = 100, K = 10: 1.2e-15 / 3.6e-15 / 1.3e-15; T = 300: 7.7e-16 /
+// 2.1e-15 / 5.1e-15; T = 2,000: 4.4e-16 / 1.6e-15 / 1.0e-14; K = 1: 4.3e-15 /
+// 4.5e-15 / 6.0e-15 at T = 100, 1.3e-15 / 1.7e-15 / 3.2e-14 at T = 2,000.  Which
 // form runs: kf_wave_form.
 constexpr int KF_L = 2;
 
@@ -148,12 +154,13 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
   double tot = 0.0;
   for (int t0 = 0; t0 < T; t0 += WAVE * KF_L) {
     const int tl = t0 + lane * KF_L;  // this lane's first interval
-    double g[KF_L], b[KF_L];
+    double g[KF_L], y[KF_L], qe[KF_L];
 #pragma unroll
     for (int e = 0; e < KF_L; ++e) {
       const int t = min(tl + e, T - 1);
       g[e] = 0.0;
-      b[e] = Q.y(t) - Z * Q.q_end(t);
+      y[e] = Q.y(t);
+      qe[e] = Q.q_end(t);
     }
 #pragma unroll 4
     for (int s = 0; s < K; ++s)
@@ -193,19 +200,39 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
       const double rest = R * iS[e];  // 1 - Kg
       Vl = in ? R * Kg[e] : Vl;
       g[e] = c * g[e];
-      const double ae = __builtin_fma(aK, rest, aKl * rest), bb = __builtin_fma(rest, g[e], Kg[e] * b[e]);
+      const double ae = __builtin_fma(aK, rest, aKl * rest);
+      const double bb = __builtin_fma(rest, g[e], Kg[e] * __builtin_fma(-Z, qe[e], y[e]));
       be = in ? __builtin_fma(ae, be, bb) : be;
       al = in ? ae * al : al;
     }
+    double da = al;
     wave_affine_scan(al, be);
     const double mi = __builtin_fma(al, m, be);  // the mean after the lane's intervals
     double ml = wave_prev(mi, m);
+    // what the lane's intervals, stepped from that mean, make of it, less the
+    // scan's: carried on by the same maps, it corrects the lanes' first means
+    auto innovation = [&](int e, double mean, double& mp) -> double {
+      mp = __builtin_fma(aK, mean, __builtin_fma(aKl, mean, g[e]));
+      return __builtin_fma(-Z, qe[e], y[e] - mp);
+    };
+    double db;
+    {
+      double x = ml, mp;
+#pragma unroll
+      for (int e = 0; e < KF_L; ++e) {
+        const double v = innovation(e, x, mp);
+        x = tl + e < T ? __builtin_fma(Kg[e], v, mp) : x;
+      }
+      db = x - mi;
+    }
+    wave_affine_scan(da, db);
+    ml += wave_prev(db, 0.0);
     double part = 0.0;
 #pragma unroll
     for (int e = 0; e < KF_L; ++e) {
       const bool in = tl + e < T;
-      const double mp = __builtin_fma(aK, ml, __builtin_fma(aKl, ml, g[e]));
-      const double v = b[e] - mp;
+      double mp;
+      const double v = innovation(e, ml, mp);
       const double le = -0.5 * (log(2.0 * 3.14159265358979323846 * S[e]) + v * v * iS[e]);
       ml = in ? __builtin_fma(Kg[e], v, mp) : ml;
       part += in ? le : 0.0;
