@@ -585,11 +585,14 @@ static inline unsigned kf_blocks(int n) { return (unsigned)((n + 255) / 256); }
 // chain and iteration about 2.4 ns, plus 1.5 + 0.08 K ns per pass of 128
 // intervals (T = 100, K = 10: 6.1 us at 512 chains, 41 at 8,192, 78 at
 // 16,384, 152 at 32,768; T = 300: 250 at 32,768).  A plain likelihood run has
-// no proposals, in either form.  The cheaper estimate wins: at T = 100 and
-// K = 10 the wave form up to 16,500 chains.
+// no proposals, in either form, and a wave's own latency shows in the shortest
+// ones: 3.2 us against the lane form's 2.1 at T = 1 (one filter, K = 10), 3.0
+// against 3.1 at T = 2.  The cheaper estimate wins: at T = 100 and K = 10 the
+// wave form up to 16,500 chains.
 static inline bool kf_wave_form(int B, int T, int K, bool chains) {
   const double passes = (double)((T + WAVE * KF_L - 1) / (WAVE * KF_L));
-  const double wave_ns = B * ((chains ? 2.4 : 0.6) + passes * (1.5 + 0.08 * K));
+  const double wave_ns =
+      (chains ? 0.0 : 700.0) + B * ((chains ? 2.4 : 0.6) + passes * (1.5 + 0.08 * K));
   const double lane_ns = (chains ? 11e3 : 0.0) + T * (320.0 + 33.0 * K);
   return wave_ns <= lane_ns;
 }
