@@ -194,8 +194,7 @@ Layout make_layout(const pf_config* c) {
   L.w16 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * 16 * n256 : 8);
   L.w256 = take(c->layout == PF_LAYOUT_PLAIN ? 8 * n256 : 8);
   // Runs of small windkessel filters draw their random numbers ahead (K values
-  // per particle and interval, whole 256-particle blocks of the largest
-  // filter's number for each): as many intervals at a time as 64 MiB hold, at
+  // per particle and interval, for each filter as many as the largest's): as many intervals at a time as 64 MiB hold, at
   // least one, in at most 256 MiB.  Small is up to SMALL_MAXN / 2 particles, and
   // SMALL_MAXN where several filters run side by side that the multi-kernel path
   // takes in turn.  Measured against that path's graphs, us per interval, FP64
@@ -208,8 +207,9 @@ Layout make_layout(const pf_config* c) {
       c->B <= 65535 &&
       *std::max_element(c->n_particles, c->n_particles + c->B) <=
           (c->B > 1 ? pfk::SMALL_MAXN : pfk::SMALL_MAXN / 2)) {
-    const int64_t nb = *std::max_element(L.nblk.begin(), L.nblk.end());
-    const size_t one = sx * (size_t)c->K * (size_t)(nb * pfk::K1_NT) * (size_t)c->B;
+    const int max_n = (int)*std::max_element(c->n_particles, c->n_particles + c->B);
+    const size_t one =
+        sx * (size_t)c->K * (size_t)pfk::small_width(max_n) * (size_t)c->B;
     if (one <= ((size_t)256 << 20)) {
       const size_t most = std::max<size_t>(1, ((size_t)64 << 20) / one);
       L.small_n = (int32_t)std::min<size_t>({most, (size_t)c->T, (size_t)1024});

@@ -219,6 +219,9 @@ hipError_t launch_multinomial_anc(const int32_t* jc, int32_t* anc,
 hipError_t launch_simulate(int model, int d, double* out, const PlainArgs& a, double obs_sd,
                            hipStream_t s);
 // ---- small filters, one workgroup each (pf_small.hip) ----
+// Random numbers of one substep that a run keeps for each filter: four (a
+// lane's rows) for each of a wave's lanes, or of a smaller filter's particles.
+inline int small_width(int max_n) { return max_n <= 64 ? 4 * max_n : (max_n + 255) / 256 * 256; }
 // The stateless resampler for n <= SMALL_MAXN weights in one launch; the
 // plain kernels' bits.
 hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* anc, double* stats,
@@ -226,7 +229,7 @@ hipError_t launch_small_systematic(const double* lw, int n, double u, int32_t* a
 // n intervals of B windkessel filters of at most max_n <= SMALL_MAXN
 // particles (a: the first filter's arguments; off: [B + 1] first particles),
 // a workgroup each, after a launch that draws their random numbers into nz
-// (n K B ceil(max_n / 256) 256 values in the state's precision) and rec (B n (K + 3)
+// (n K B small_width(max_n) values in the state's precision) and rec (B n (K + 3)
 // doubles).  The ancestors pending must not be marks (flagged in the filter's
 // scalars if they are); they are the array afterwards.
 hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, double* lw,

@@ -339,16 +339,17 @@ constexpr int REC_HEAD = 3;
 
 // The random numbers of n intervals from every filter's counter on: sigma_p z
 // (FP64; the FP32 forms keep z, which enters a fused multiply-add), and the
-// intervals' records.  Every filter has fb whole 256-particle blocks of
-// numbers; within a block a lane's four rows lie together:
-// nz[(((i K + s) B + b) fb + block) 256 + 4 lane + row].  One lane per
-// particle and interval; bound by the normals' FP64 instructions (1,024
-// particles, 100 intervals of K = 10: 13.4 us for all of them).
+// intervals' records.  Every filter has W = small_width(max_n) numbers, whole
+// 256-particle blocks but in a filter of a single row; within a block a lane's
+// four rows lie together: nz[((i K + s) B + b) W + 256 block + 4 lane + row].
+// One lane per particle and interval (numbers past a filter's end are not
+// drawn); bound by the normals' FP64 instructions (1,024 particles, 100
+// intervals of K = 10: 13.4 us for all of them).
 template <typename Real>
 __global__ __launch_bounds__(K1_NT) void k_small_noise(PlainArgs A,
                                                        const int64_t* __restrict__ offs,
                                                        Real* __restrict__ nz,
-                                                       double* __restrict__ rec, int n) {
+                                                       double* __restrict__ rec, int n, int W) {
   const int i = blockIdx.y, b = blockIdx.z;
   const int N = (int)(offs[b + 1] - offs[b]);
   const FilterState* fs = A.fs + b;
@@ -374,12 +375,11 @@ __global__ __launch_bounds__(K1_NT) void k_small_noise(PlainArgs A,
       o[s] = v;
     }
   }
-  if ((int)blockIdx.x * K1_NT >= N) return;
   // thread 4 lane + row of the block
   const int j = blockIdx.x * K1_NT + (threadIdx.x & 3) * WAVE + (threadIdx.x >> 2);
-  const int64_t step = (int64_t)gridDim.z * gridDim.x * K1_NT;
-  Real* o = nz + (int64_t)i * A.K * step + ((int64_t)b * gridDim.x + blockIdx.x) * K1_NT +
-            threadIdx.x;
+  if (j >= N) return;
+  const int64_t step = (int64_t)gridDim.z * W;
+  Real* o = nz + (int64_t)i * A.K * step + (int64_t)b * W + blockIdx.x * K1_NT + threadIdx.x;
   for (int s = 1; s <= A.K; ++s, o += step) {
     const uint4 w = draw(key, TAG_NOISE, 0, iter, (uint32_t)j, (uint32_t)(n0 + s), (uint32_t)b);
     if constexpr (sizeof(Real) == 8) {
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
                                                          const int64_t* __restrict__ offs,
                                                          const Real* __restrict__ nz,
                                                          const double* __restrict__ rec, int n,
-                                                         int fb) {
+                                                         int W) {
   constexpr int NT = K3_NT * NQ;
   // substeps loaded ahead, as many as the registers leave room for
   constexpr int AHEAD = NQ == 4 ? 4 : 12;
@@ -437,9 +437,10 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
   const Key key{A.key.lo, A.key.hi};
   const double a64 = th[0];
   const float am1 = (float)(th[0] - 1.0), sp = (float)th[3];
-  // this wave's block of numbers (a wave past the filter's blocks reads the last)
-  const int64_t step = (int64_t)gridDim.x * fb * K1_NT;
-  nz += ((int64_t)b * fb + min(wave, fb - 1)) * K1_NT;
+  // this wave's block of numbers, from the lane's on (a wave or a lane past the
+  // filter's reads the last)
+  const int64_t step = (int64_t)gridDim.x * W;
+  nz += (int64_t)b * W + min(wave, (W - 1) / K1_NT) * K1_NT + ROWS * min(lane, W / ROWS - 1);
   rec += (int64_t)b * n * (K + REC_HEAD);
   double* ell_tr = A.ell_tr + (int64_t)b * A.T;
   double* ess_tr = A.ess_tr + (int64_t)b * A.T;
@@ -462,7 +463,7 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
     const Real* zi = nz + (int64_t)i * K * step;
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s)
-      if (s < K) zn[s] = *(const Row4*)(zi + s * step + ROWS * lane);
+      if (s < K) zn[s] = *(const Row4*)(zi + s * step);
   };
   load_ahead(0);
   if (tid < K + REC_HEAD) recL[0][tid] = rec[tid];
@@ -496,7 +497,7 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
 #pragma unroll
       for (int s = 0; s < AHEAD; ++s)
         if (s < K) substep(lane_value(head, s), zn[s]);
-      const Real* zi = nz + (int64_t)i * K * step + ROWS * lane;
+      const Real* zi = nz + (int64_t)i * K * step;
       for (int s0 = AHEAD; s0 < K; s0 += 4) {
         Row4 z[4];
 #pragma unroll
@@ -590,12 +591,12 @@ __global__ __launch_bounds__(K3_NT* NQ) void k_small_run(Real* __restrict__ xa,
 }
 
 template <typename Real, bool ACC>
-static void small_run(int nq, int fb, int B, void* xa, void* xb, double* lw, int32_t* anc,
+static void small_run(int nq, int W, int B, void* xa, void* xb, double* lw, int32_t* anc,
                       const PlainArgs& a, const int64_t* off, const void* nz, const double* rec,
                       int n, hipStream_t s) {
 #define PF_SMALL(Q, SYS)                                                                       \
   hipLaunchKernelGGL((k_small_run<Real, ACC, Q, SYS>), (unsigned)B, K3_NT* Q, 0, s, (Real*)xa, \
-                     (Real*)xb, lw, anc, a, off, (const Real*)nz, rec, n, fb)
+                     (Real*)xb, lw, anc, a, off, (const Real*)nz, rec, n, W)
   const bool sys = a.rs.scheme == RS_SYSTEMATIC;
   if (nq == 1) {
     if (sys) PF_SMALL(1, true);
@@ -616,15 +617,16 @@ hipError_t launch_small_run(int prec, int B, int max_n, void* xa, void* xb, doub
   if (max_n < 1 || max_n > SMALL_MAXN || a.K > SMALL_MAXK || n < 1 || B < 1 || B > 65535 ||
       n > 65535)
     return hipErrorInvalidValue;
+  const int W = small_width(max_n);
   const dim3 g((unsigned)((max_n + K1_NT - 1) / K1_NT), (unsigned)n, (unsigned)B);
   if (prec == 0)
-    hipLaunchKernelGGL(k_small_noise<double>, g, K1_NT, 0, s, a, off, (double*)nz, rec, n);
+    hipLaunchKernelGGL(k_small_noise<double>, g, K1_NT, 0, s, a, off, (double*)nz, rec, n, W);
   else
-    hipLaunchKernelGGL(k_small_noise<float>, g, K1_NT, 0, s, a, off, (float*)nz, rec, n);
+    hipLaunchKernelGGL(k_small_noise<float>, g, K1_NT, 0, s, a, off, (float*)nz, rec, n, W);
   const int nq = max_n <= K3_SPAN ? 1 : max_n <= 2 * K3_SPAN ? 2 : 4;
-  if (prec == 0) small_run<double, false>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
-  else if (prec == 1) small_run<float, false>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
-  else small_run<float, true>(nq, g.x, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
+  if (prec == 0) small_run<double, false>(nq, W, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
+  else if (prec == 1) small_run<float, false>(nq, W, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
+  else small_run<float, true>(nq, W, B, xa, xb, lw, anc, a, off, nz, rec, n, s);
   return hipGetLastError();
 }
 

@@ -168,3 +168,14 @@ def test_tuning_calls_need_a_handle():
     assert L.pf_set_replay(None, 1) == binding.PF_E_INVAL
     t = C.c_int32()
     assert L.pf_get_tuning(None, C.byref(t), None, None) == binding.PF_E_INVAL
+
+
+def test_kalman_handle_reserves_little_for_particles_it_never_steps():
+    """512 windkessel parameter sets of one particle each (a handle that only
+    runs Kalman filters): the numbers drawn ahead for its particles take 4 of
+    each substep a filter, not a block of 256."""
+    pb = W.windkessel(N=1, T=100, K=10, B=512).with_obs(np.zeros((100, 1)))
+    _, n = _size(pb)
+    ahead = 100 * (10 * 4 * 8 + 13 * 8) * 512  # numbers and records of 100 intervals
+    traces = 3 * 8 * 100 * 512
+    assert n < ahead + traces + (1 << 20)

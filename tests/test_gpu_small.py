@@ -170,3 +170,29 @@ def test_rejection_and_many_moves_equal_eager_steps(env, sizes, scheme, steps, f
         np.testing.assert_array_equal(a, b)
     f.close()
     g.close()
+
+
+@pytest.mark.parametrize("sizes", [(1,), (3,), (63,), (64, 1, 33), (65, 64, 2), (17,) * 40])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_small_run_of_single_row_filters(env, sizes, precision):  # noqa: F811
+    """Filters of up to 64 particles keep numbers for those alone."""
+    _, pfm = env
+    import dataclasses
+
+    import workloads as W
+    T = 7
+    base = W.windkessel(N=1, T=T, K=14, B=len(sizes))
+    pb = dataclasses.replace(
+        base.with_obs(90.0 + 5.0 * np.random.default_rng(3).standard_normal((T, 1))),
+        n_particles=np.array(sizes, dtype=np.int64))
+    for name, (scheme, steps, frac) in SCHEMES.items():
+        f, g = (pfm.Filter(pb, precision=precision) for _ in range(2))
+        for h in (f, g):
+            h.set_resampler(scheme, steps, frac)
+        f.advance(T)
+        g.graph_run(5)
+        g.graph_run(2)
+        for a, b in zip(_outputs(f), _outputs(g)):
+            np.testing.assert_array_equal(a, b, err_msg=name)
+        f.close()
+        g.close()
