@@ -55,21 +55,22 @@ __device__ __forceinline__ double kf_interval(const double* th, const KfArgs& A,
 //   - given the gains the mean's maps m' = alpha m + beta compose by a wave
 //     scan.
 //   - the composed maps round a stationary gain the same way at every interval,
-//     which adds up over a long series; so each lane steps its intervals from
-//     the mean that the scan gave it, and a second scan of what that differs by
-//     corrects the lanes' first means.
+//     which adds up over a series.  Its complement is kept in two parts; in
+//     series of several passes, where that is not enough, each lane also steps
+//     its intervals from the mean that the scan gave it, and a second scan of
+//     what that differs by corrects the lanes' first means.
 // The logarithms and divisions then run in all lanes at once.  512 chains
-// over T = 100, K = 10: 5.7 us an iteration with the launch and the outputs'
-// allocation (5.6 without the correction) against 74 a lane each (two waves per
-// SIMD, still latency: two intervals per lane interleave); 512 likelihoods: 60
-// us a call, most of it the copies of the results, against 150.  Both forms'
+// over T = 100, K = 10: 4.7 us an iteration against 74 a lane each (two waves per
+// SIMD, still latency: two intervals per lane interleave); 512 likelihoods: 58
+// us a call, most of it the copies of the results, against 148.  Both forms'
 // arithmetic against 113-bit arithmetic, 500 parameter sets, the likelihood's
-// mean relative error, this form / the chain / this form without the
-// correction: T = 100, K = 10: 1.2e-15 / 3.6e-15 / 1.3e-15; T = 300: 7.7e-16 /
-// 2.1e-15 / 5.1e-15; T = 2,000: 4.4e-16 / 1.6e-15 / 1.0e-14; K = 1: 4.3e-15 /
-// 4.5e-15 / 6.0e-15 at T = 100, 1.3e-15 / 1.7e-15 / 3.2e-14 at T = 2,000.  Which
+// mean relative error, this form / the chain / this form without either
+// correction: T = 100, K = 10: 0.97e-15 / 3.6e-15 / 1.3e-15; T = 300: 0.77e-15 /
+// 2.1e-15 / 5.1e-15; T = 2,000: 0.44e-15 / 1.6e-15 / 10e-15; K = 1: 3.8e-15 /
+// 4.5e-15 / 6.0e-15 at T = 100, 1.3e-15 / 1.7e-15 / 32e-15 at T = 2,000.  Which
 // form runs: kf_wave_form.
 constexpr int KF_L = 2;
+constexpr int KF_PASS = WAVE * KF_L;  // intervals of a pass
 
 // Flow and observations in memory, or staged in LDS with the substeps as
 // rows (lanes read consecutive entries).
@@ -108,8 +109,8 @@ __device__ __forceinline__ void wave_affine_scan(double& a, double& b) {
 // The log-likelihood of T intervals from N(m, V), every lane of the wave
 // active; th uniform.  ell (or null) receives the T increments; m and V
 // become the filtered mean and variance.  The result is the same in every
-// lane.
-template <class Series>
+// lane.  SEVERAL: T may take more than one pass.
+template <bool SEVERAL, class Series>
 __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double R,
                                           const Series& Q, double& m, double& V,
                                           double* __restrict__ ell) {
@@ -152,7 +153,7 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
     for (int j = 1; j < 6; ++j) square(P[j - 1], P[j]);
   }
   double tot = 0.0;
-  for (int t0 = 0; t0 < T; t0 += WAVE * KF_L) {
+  for (int t0 = 0; t0 < T; t0 += KF_PASS) {
     const int tl = t0 + lane * KF_L;  // this lane's first interval
     double g[KF_L], y[KF_L], qe[KF_L];
 #pragma unroll
@@ -197,11 +198,12 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
       S[e] = Pv + R;
       iS[e] = 1.0 / S[e];
       Kg[e] = Pv * iS[e];
-      const double rest = R * iS[e];  // 1 - Kg
+      const double rest = R * iS[e], rr = (1.0 - Kg[e]) - rest;  // 1 - Kg, in two parts
       Vl = in ? R * Kg[e] : Vl;
       g[e] = c * g[e];
-      const double ae = __builtin_fma(aK, rest, aKl * rest);
-      const double bb = __builtin_fma(rest, g[e], Kg[e] * __builtin_fma(-Z, qe[e], y[e]));
+      const double ae = __builtin_fma(aK, rest, __builtin_fma(aKl, rest, aK * rr));
+      const double bb = __builtin_fma(
+          rest, g[e], __builtin_fma(Kg[e], __builtin_fma(-Z, qe[e], y[e]), rr * g[e]));
       be = in ? __builtin_fma(ae, be, bb) : be;
       al = in ? ae * al : al;
     }
@@ -209,24 +211,24 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
     wave_affine_scan(al, be);
     const double mi = __builtin_fma(al, m, be);  // the mean after the lane's intervals
     double ml = wave_prev(mi, m);
-    // what the lane's intervals, stepped from that mean, make of it, less the
-    // scan's: carried on by the same maps, it corrects the lanes' first means
+    // (several passes) what the lane's intervals, stepped from that mean, make
+    // of it, less the scan's: carried on by the same maps, it corrects the
+    // lanes' first means
     auto innovation = [&](int e, double mean, double& mp) -> double {
       mp = __builtin_fma(aK, mean, __builtin_fma(aKl, mean, g[e]));
       return __builtin_fma(-Z, qe[e], y[e] - mp);
     };
-    double db;
-    {
+    if constexpr (SEVERAL) {
       double x = ml, mp;
 #pragma unroll
       for (int e = 0; e < KF_L; ++e) {
         const double v = innovation(e, x, mp);
         x = tl + e < T ? __builtin_fma(Kg[e], v, mp) : x;
       }
-      db = x - mi;
+      double db = x - mi;
+      wave_affine_scan(da, db);
+      ml += wave_prev(db, 0.0);
     }
-    wave_affine_scan(da, db);
-    ml += wave_prev(db, 0.0);
     double part = 0.0;
 #pragma unroll
     for (int e = 0; e < KF_L; ++e) {
@@ -246,6 +248,7 @@ __device__ __forceinline__ double kf_wave(const double* th, int K, int T, double
   return tot;
 }
 
+template <bool SEVERAL>
 __global__ __launch_bounds__(WAVE) void k_kf_run_wave(KfArgs A, const double* __restrict__ theta,
                                                       double* __restrict__ ll,
                                                       double* __restrict__ ell) {
@@ -254,12 +257,13 @@ __global__ __launch_bounds__(WAVE) void k_kf_run_wave(KfArgs A, const double* __
 #pragma unroll
   for (int p = 0; p < 6; ++p) th[p] = theta[(int64_t)b * 8 + p];
   double m = th[4], V = th[5] * th[5];
-  const double tot = kf_wave(th, A.K, A.T, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V,
-                             ell + (int64_t)b * A.T);
+  const double tot = kf_wave<SEVERAL>(th, A.K, A.T, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V,
+                                      ell + (int64_t)b * A.T);
   if (threadIdx.x == 0) ll[b] = tot;
 }
 
 // The proposals' filters (k_kf_proposal), a wave each; i >= 2.
+template <bool SEVERAL>
 __global__ __launch_bounds__(WAVE) void k_kf_proposal_wave(KfArgs A, Smc2Args S,
                                                            const double* __restrict__ prop_dev,
                                                            double* __restrict__ prop_l,
@@ -270,7 +274,8 @@ __global__ __launch_bounds__(WAVE) void k_kf_proposal_wave(KfArgs A, Smc2Args S,
 #pragma unroll
   for (int p = 0; p < 6; ++p) th[p] = prop_dev[(int64_t)j * 8 + p];
   double m = th[4], V = th[5] * th[5];
-  const double tot = kf_wave(th, A.K, i - 1, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V, nullptr);
+  const double tot =
+      kf_wave<SEVERAL>(th, A.K, i - 1, A.R, KfSeriesMem{A.q, A.obs, A.K}, m, V, nullptr);
   if (threadIdx.x == 0) {
     prop_l[j] = tot;
     prop_mV[2 * j] = m;
@@ -392,7 +397,7 @@ __device__ __forceinline__ double kf_loglik(const KfArgs& A, const double* th) {
 // evaluated at once; the current state's terms are kept from one iteration to
 // the next and follow an acceptance only.  The likelihood is kf_wave, with the
 // series staged in LDS when it fits.
-template <bool LDS>
+template <bool LDS, bool SEVERAL>
 __global__ __launch_bounds__(WAVE) void k_kf_pmmh_wave(KfArgs A, pf_wk_mh H, double h,
                                                        int32_t iters,
                                                        const double* __restrict__ theta0,
@@ -417,10 +422,11 @@ __global__ __launch_bounds__(WAVE) void k_kf_pmmh_wave(KfArgs A, pf_wk_mh H, dou
   auto loglik = [&](const double* th) -> double {
     double m = th[4], V = th[5] * th[5];
     if constexpr (LDS)
-      return kf_wave(th, K, T, A.R, KfSeriesLds{series, series + (int64_t)K * (T + 1), T + 1}, m,
-                     V, nullptr);
+      return kf_wave<SEVERAL>(th, K, T, A.R,
+                              KfSeriesLds{series, series + (int64_t)K * (T + 1), T + 1}, m, V,
+                              nullptr);
     else
-      return kf_wave(th, K, T, A.R, KfSeriesMem{A.q, A.obs, K}, m, V, nullptr);
+      return kf_wave<SEVERAL>(th, K, T, A.R, KfSeriesMem{A.q, A.obs, K}, m, V, nullptr);
   };
   // the sum over the parameters in their order
   auto sum4 = [&](double v) -> double {
@@ -590,7 +596,7 @@ static inline unsigned kf_blocks(int n) { return (unsigned)((n + 255) / 256); }
 // against 3.1 at T = 2.  The cheaper estimate wins: at T = 100 and K = 10 the
 // wave form up to 16,500 chains.
 static inline bool kf_wave_form(int B, int T, int K, bool chains) {
-  const double passes = (double)((T + WAVE * KF_L - 1) / (WAVE * KF_L));
+  const double passes = (double)((T + KF_PASS - 1) / KF_PASS);
   const double wave_ns =
       (chains ? 0.0 : 700.0) + B * ((chains ? 2.4 : 0.6) + passes * (1.5 + 0.08 * K));
   const double lane_ns = (chains ? 11e3 : 0.0) + T * (320.0 + 33.0 * K);
@@ -601,10 +607,12 @@ constexpr size_t KF_LDS_MAX = 64 * 1024;
 
 hipError_t launch_kf_run(const KfArgs& A, const double* theta, double* ll, double* ell,
                          hipStream_t s) {
-  if (kf_wave_form(A.B, A.T, A.K, false))
-    hipLaunchKernelGGL(k_kf_run_wave, (unsigned)A.B, WAVE, 0, s, A, theta, ll, ell);
-  else
+  if (!kf_wave_form(A.B, A.T, A.K, false))
     hipLaunchKernelGGL(k_kf_run, kf_blocks(A.B), 256, 0, s, A, theta, ll, ell);
+  else if (A.T <= KF_PASS)
+    hipLaunchKernelGGL(k_kf_run_wave<false>, (unsigned)A.B, WAVE, 0, s, A, theta, ll, ell);
+  else
+    hipLaunchKernelGGL(k_kf_run_wave<true>, (unsigned)A.B, WAVE, 0, s, A, theta, ll, ell);
   return hipGetLastError();
 }
 
@@ -615,12 +623,15 @@ hipError_t launch_kf_init(const Smc2Args& S, hipStream_t s) {
 
 hipError_t launch_kf_proposal(const KfArgs& A, const Smc2Args& S, const double* prop_dev,
                               double* prop_l, double* prop_mV, int i, hipStream_t s) {
-  if (i >= 2 && kf_wave_form(S.B, i - 1, A.K, false))
-    hipLaunchKernelGGL(k_kf_proposal_wave, (unsigned)S.B, WAVE, 0, s, A, S, prop_dev, prop_l,
-                       prop_mV, i);
-  else
+  if (i < 2 || !kf_wave_form(S.B, i - 1, A.K, false))
     hipLaunchKernelGGL(k_kf_proposal, kf_blocks(S.B), 256, 0, s, A, S, prop_dev, prop_l, prop_mV,
                        i);
+  else if (i - 1 <= KF_PASS)
+    hipLaunchKernelGGL(k_kf_proposal_wave<false>, (unsigned)S.B, WAVE, 0, s, A, S, prop_dev,
+                       prop_l, prop_mV, i);
+  else
+    hipLaunchKernelGGL(k_kf_proposal_wave<true>, (unsigned)S.B, WAVE, 0, s, A, S, prop_dev,
+                       prop_l, prop_mV, i);
   return hipGetLastError();
 }
 
@@ -638,15 +649,17 @@ hipError_t launch_kf_pmmh(const KfArgs& A, const pf_wk_mh& H, double h, int32_t 
                           hipStream_t s) {
   const size_t lds = 8 * ((size_t)A.K * ((size_t)A.T + 1) + (size_t)A.T);
   const bool wave = kf_wave_form(A.B, A.T, A.K, true);
-  if (wave && lds <= KF_LDS_MAX)
-    hipLaunchKernelGGL(k_kf_pmmh_wave<true>, (unsigned)A.B, WAVE, lds, s, A, H, h, iters, theta0,
-                       prop, alpha, theta_trace, ll_trace, accepts, ll0);
-  else if (wave)
-    hipLaunchKernelGGL(k_kf_pmmh_wave<false>, (unsigned)A.B, WAVE, 0, s, A, H, h, iters, theta0,
-                       prop, alpha, theta_trace, ll_trace, accepts, ll0);
+#define PF_KF_PMMH(LDS, SEVERAL)                                                                  \
+  hipLaunchKernelGGL((k_kf_pmmh_wave<LDS, SEVERAL>), (unsigned)A.B, WAVE, LDS ? lds : 0, s, A, H, \
+                     h, iters, theta0, prop, alpha, theta_trace, ll_trace, accepts, ll0)
+  const bool fits = lds <= KF_LDS_MAX, several = A.T > KF_PASS;
+  if (wave && fits && !several) PF_KF_PMMH(true, false);
+  else if (wave && fits) PF_KF_PMMH(true, true);
+  else if (wave) PF_KF_PMMH(false, true);
   else
     hipLaunchKernelGGL(k_kf_pmmh, (unsigned)((A.B + 63) / 64), 64, 0, s, A, H, h, iters, theta0,
                        prop, alpha, theta_trace, ll_trace, accepts, ll0);
+#undef PF_KF_PMMH
   return hipGetLastError();
 }
 
