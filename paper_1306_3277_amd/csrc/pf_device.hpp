@@ -209,11 +209,6 @@ __device__ __forceinline__ void bm_pair_f32(uint32_t wa, uint32_t wb, float& z0,
   z1 = r * __builtin_amdgcn_sinf(ub);
 }
 
-__device__ __forceinline__ void normals4_f32(uint4 w, float z[4]) {
-  bm_pair_f32(w.x, w.y, z[0], z[1]);
-  bm_pair_f32(w.z, w.w, z[2], z[3]);
-}
-
 // ---------------------------------------------------------------- models
 // Per-filter constants, derived on the host in FP64.
 struct ModelConsts {
@@ -789,82 +784,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
 // lane - 1's value (wave_shr 1); lane 0 takes `old`
 __device__ __forceinline__ double wave_prev(double v, double old) {
   return dpp_move<0x138, 0xf>(v, old);
-}
-__device__ __forceinline__ int64_t wave_prev_i64(int64_t v, int64_t old) {
-  const int lo = dpp_move_i<0x138, 0xf>((int)(uint32_t)v, (int)(uint32_t)old);
-  const int hi = dpp_move_i<0x138, 0xf>((int)(v >> 32), (int)(old >> 32));
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-// Block-wide reductions for a block of NT threads (NT/64 waves); `red` is
-// LDS scratch of NT/64 doubles; ends with a barrier so `red` can be reused.
-template <int NT>
-__device__ __forceinline__ double block_max(double v, double* red) {
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  v = wave_max(v);
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  double r = red[0];
-#pragma unroll
-  for (int i = 1; i < NT / WAVE; ++i) r = fmax(r, red[i]);
-  __syncthreads();
-  return r;
-}
-template <int NT>
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  v = wave_sum(v);
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  double r = 0.0;
-#pragma unroll
-  for (int i = 0; i < NT / WAVE; ++i) r += red[i];
-  __syncthreads();
-  return r;
-}
-template <int NT>
-__device__ __forceinline__ int block_max_i(int v, int* red) {
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  v = wave_max_i(v);
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  int r = red[0];
-#pragma unroll
-  for (int i = 1; i < NT / WAVE; ++i) r = max(r, red[i]);
-  __syncthreads();
-  return r;
-}
-// inclusive block scan; returns the thread's inclusive prefix and the total
-template <int NT>
-__device__ __forceinline__ double block_incl_scan(double v, double* red, double& total) {
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  v = wave_incl_scan(v, lane);
-  if (lane == WAVE - 1) red[w] = v;
-  __syncthreads();
-  double pre = 0.0, tot = 0.0;
-#pragma unroll
-  for (int i = 0; i < NT / WAVE; ++i) {
-    if (i < w) pre += red[i];
-    tot += red[i];
-  }
-  __syncthreads();
-  total = tot;
-  return pre + v;
-}
-
-// inclusive running maximum across a block (exact)
-template <int NT>
-__device__ __forceinline__ double block_incl_max_scan(double v, double* red) {
-  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
-  v = wave_incl_max_scan(v, lane);
-  if (lane == WAVE - 1) red[w] = v;
-  __syncthreads();
-  double pre = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NT / WAVE; ++i)
-    if (i < w) pre = fmax(pre, red[i]);
-  __syncthreads();
-  return fmax(pre, v);
 }
 
 // Number of strata k in [0, N) with (u + k) S < N W, i.e. the particles up
