@@ -80,9 +80,10 @@ __device__ __forceinline__ double u01_f64(uint32_t w) {
   return __builtin_fma((double)w, 0x1p-32, 0x1p-33);  // exact
 }
 
-// a / b, correctly rounded, for 2^-500 < |b| < 2^500 and a quotient (or a
-// zero a) as far from the ends of the range: the reciprocal by two Newton
-// steps, then the quotient corrected by its remainder.
+// a / b, correctly rounded for the quotients that ln_f64 forms (b in (1.7, 2.5),
+// |a| < 0.5; compared at every word): the reciprocal by two Newton steps, then
+// the quotient corrected by its remainder.  Nothing near the ends of the
+// exponent range may come in.
 __device__ __forceinline__ double div_mid(double a, double b) {
   double y = __builtin_amdgcn_rcp(b);
   y = __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
@@ -91,17 +92,17 @@ __device__ __forceinline__ double div_mid(double a, double b) {
   return __builtin_fma(__builtin_fma(-b, q, a), y, q);
 }
 
-// a / b from the correctly rounded reciprocal y of b, in the same range: the
-// remainder's correction then gives the correctly rounded quotient (Markstein,
-// IBM J. Res. Dev. 34, 1990).
+// a / b from the correctly rounded reciprocal y of b, all far from the ends of
+// the exponent range: the remainder's correction then gives the correctly
+// rounded quotient (Markstein, IBM J. Res. Dev. 34, 1990).
 __device__ __forceinline__ double div_by(double a, double b, double y) {
   const double q = a * y;
   return __builtin_fma(__builtin_fma(-b, q, a), y, q);
 }
 
-// sqrt(x), correctly rounded, for 2^-500 < x < 2^500: Goldschmidt's coupled
-// iteration for root and half reciprocal root, then two corrections by the
-// remainder.
+// sqrt(x), correctly rounded for the radii's squares (2^-32 <= x < 46; compared
+// at every word): Goldschmidt's coupled iteration for root and half reciprocal
+// root, then two corrections by the remainder.
 __device__ __forceinline__ double sqrt_mid(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
