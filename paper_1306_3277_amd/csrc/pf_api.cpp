@@ -507,22 +507,42 @@ void set_history(const pf_handle* H, BatchArgs& a) {
 // Whether filter group g's runs of several intervals are fused (pf_fused.hip).
 // A fused interval saves a launch boundary and the ancestors' way through
 // memory, and pays for every workgroup scanning its whole filter: about 2.3 us
-// per million particles scanned in all.  Measured, us per interval, fused
-// against two launches (Lorenz '96 d = 8, K = 8, fast FP32, one group, 256
-// threads): 64 filters of 256: 10.9 / 12.8, of 2,048 (1.05 million scanned):
-// 16.8 / 18.9; 256 of 512: 15.0 / 17.5, of 1,024 (1.05 million): 24.8 / 25.9, of
-// 2,048 (4.2 million): 46 / 41.  Workgroups of 512 gain less, as their
-// propagation has two waves on a SIMD where two launches would spread them
-// (4 filters of 1,024: 12.9 / 12.7): they fuse only filters of more than 2,048
-// in groups that overlap (64 of 4,096, 2.1 million scanned, two groups: 24.7 /
-// 25.2; one group: 27.7 / 28.7; 128 in two groups: 41.9 / 37.9).
+// per million particles scanned in all.  Measured, us per interval, fused / two
+// launches (Lorenz '96 d = 8, K = 8, fast, accurate and FP64 form):
+// workgroups of 256, one group: 64 filters of 300: 10.8 / 13.1, 11.6 / 14.1,
+// 19.2 / 22.3; 64 of 2,048 (1.05 million scanned): 16.0 / 18.1, 16.9 / 19.6,
+// 32.2 / 35.4; 72 of 2,048 (1.18): 20.3 / 20.5, 22.6 / 23.3, 44.1 / 46.2; 150
+// of 1,500 (1.35): 23.9 / 24.2, 27.6 / 27.8, 57.1 / 57.6; 384 of 1,024 (1.57):
+// 31.7 / 31.4, 37.0 / 36.9, 80.3 / 80.5.  With many workgroups the propagation
+// hides a boundary by itself: 640 filters of 512 (1,280 workgroups): 26.4 /
+// 28.7, 31.5 / 33.2, 67.7 / 69.8; 500 of 700 (1,500): 31.1 / 30.9, 36.4 / 36.2,
+// 79.2 / 79.6; 1,000 of 300 (2,000): 38.0 / 37.6, 45.7 / 44.5, 102 / 103; and
+// sooner where most of their waves are idle, whose places two launches give to
+// others: 700 of 100: 14.4 / 17.1, 16.8 / 19.2, 33.0 / 34.1; 1,000 of 100: 18.7 /
+// 18.7, 21.4 / 20.4, 44 / 36.
+// Workgroups of 512 put two waves of the propagation on a SIMD where two
+// launches spread them, so they fuse only filters of more than 2,048 in two
+// groups that overlap, where a group's workgroups fit an XCD's 32 CUs (a filter
+// stays on one XCD) and, but for the fast form, take more than half of them: 16
+// of 4,096: 18.7 / 19.4, 20.9 / 20.6, 40.6 / 31.8; 40 of 4,096: 20.7 / 22.2, 24.6
+// / 25.0, 50.1 / 50.9; 56 of 4,096: 22.2 / 22.4, 25.6 / 25.6, 55.0 / 51.5; 64 of
+// 4,096 (2.1 million): 21.8 / 22.9, 25.5 / 26.5, 55.4 / 57.7; past 32 rows 72 of
+// 4,096: 27.3 / 26.7, 32.3 / 31.0, 68.6 / 65.3, 100 of 2,500: 25.4 / 22.8, 30.1 /
+// 26.3, 62 / 58; in four groups 64 of 4,096: 23.8 / 23.5, 27.3 / 26.2, 56.3 / 54.4.
 bool group_fused(const pf_handle* H, int g) {
   const pf_config& c = H->cfg;
   if (H->timing || H->rs.scheme != pfk::RS_SYSTEMATIC ||
       !pfk::fused_supported(c.model, c.d, H->batch_nt, H->grp_maxn[g]))
     return false;
-  if (H->batch_nt == 256) return H->scanned[0] <= (1 << 20) + (1 << 17);
-  return H->groups > 1 && H->grp_maxn[g] > 2048 && H->scanned[1] <= (1 << 21) + (1 << 18);
+  if (H->batch_nt == 256) {
+    const int64_t wg = H->L.n_chunks;
+    return H->scanned[0] <= (1 << 20) + (1 << 17) &&
+           (wg <= 768 || (wg <= 1280 && H->L.n_total >= 128 * wg));
+  }
+  const int rows = H->grp_nfused[1][g] / 8;
+  return c.precision != PF_FP64 && H->groups == 2 && H->grp_maxn[g] > 2048 &&
+         H->scanned[1] <= (1 << 21) && rows <= 32 &&
+         (rows > 16 || c.precision == PF_FP32_MIXED);
 }
 
 // A run of n intervals of filter group g is a sequence of launches on one

@@ -116,7 +116,7 @@ static void launch_fused(int nt, unsigned g, hipStream_t s, void* xa, void* xb,
   if (nt == 256)
     hipLaunchKernelGGL((k_batch_fused<MODEL, D, Real, ACC, 256>), g, 256, 0, s, (Real*)xa,
                        (Real*)xb, lw_in, lw, a);
-  else
+  else if constexpr (sizeof(Real) == 4)  // (an FP64 propagation is never better off so)
     hipLaunchKernelGGL((k_batch_fused<MODEL, D, Real, ACC, 512>), g, 512, 0, s, (Real*)xa,
                        (Real*)xb, lw_in, lw, a);
 }
@@ -125,7 +125,8 @@ hipError_t launch_batched_fused(int model, int d, int prec, int nt, void* xa, vo
                                 const double* lw_in, double* lw, const BatchArgs& a,
                                 int nentries, hipStream_t s) {
   if (nentries <= 0) return hipSuccess;
-  if (lw_in == lw || a.step < 1 || (nt != 256 && nt != 512)) return hipErrorInvalidValue;
+  if (lw_in == lw || a.step < 1 || (nt != 256 && (nt != 512 || prec == 0)))
+    return hipErrorInvalidValue;
   const unsigned g = (unsigned)nentries;
 #define PF_FUSED(M, DD)                                                              \
   do {                                                                               \

@@ -93,3 +93,25 @@ def test_fused_run_with_lost_weights(pfm):
     assert np.all(np.isneginf(g.loglik(allow_numeric=True)[0]))
     f.close()
     g.close()
+
+
+@pytest.mark.parametrize("threads,groups,n,precision", [
+    (512, 2, [2049] * 52, 1), (512, 2, [2049] * 52, 2),      # 20 rows of workgroups
+    (512, 2, [4096] * 16, 1), (512, 2, [4096] * 16, 2),      # 8: the fast form alone
+    (512, 2, [4096] * 64, 2), (512, 2, [4096] * 66, 2),      # 32 and 40
+    (512, 2, [4096] * 34, 0), (512, 4, [4096] * 80, 1),      # neither
+    (256, 1, [7] * 768, 1), (256, 1, [7] * 769, 1),          # workgroups nearly empty
+    (256, 1, [128] * 1280, 0), (256, 1, [129] * 1281, 0), (256, 2, [2048] * 73, 2)])
+def test_both_sides_of_the_rule(pfm, threads, groups, n, precision):
+    T = 6
+    pb = _problem(pfm, 2, 4, n, T)
+    f, g = (pfm.Filter(pb, precision=precision, layout=1) for _ in range(2))
+    for h in (f, g):
+        h.set_tuning(threads, groups)
+    f.advance(T)
+    g.graph_run(5)
+    g.graph_run(1)
+    for a, b in zip(_outputs(f), _outputs(g)):
+        np.testing.assert_array_equal(a, b)
+    f.close()
+    g.close()
