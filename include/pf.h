@@ -171,9 +171,9 @@ pf_status pf_get_trace(pf_handle* h, double* ell_out, double* ess_out);
 pf_status pf_destroy(pf_handle* h);
 
 /* Run n_steps observation intervals (pf_step + pf_resample each) by replaying
- * HIP graphs captured by the first call (and again after a change of tuning
- * or resampler): those the call needs before it issues them, the others of
- * the ladder while the device runs.  Each graph is captured on
+ * HIP graphs, captured by the first call (and again after a change of tuning
+ * or resampler) for its length; a later call of another length is issued from
+ * the graphs there are and captures its own behind it.  Each graph is captured on
  * one stream and holds kernel launches only: graphs of 1, 2, 4, ... 128
  * intervals (up to 8 for the plain layout with more than four filters), of
  * every filter (plain layout) or of one filter group (batched layout; several

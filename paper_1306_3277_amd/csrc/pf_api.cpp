@@ -273,7 +273,7 @@ struct pf_handle {
   std::vector<hipStream_t> side;
   hipEvent_t ev_fork = nullptr;
   std::vector<hipEvent_t> ev_join;
-  // what a null-stream handle's graphs are captured on, until all of them are
+  // what a null-stream handle's graphs are captured on, while a run needs it
   hipStream_t cap_stream = nullptr;
   // timing
   bool timing = false;
@@ -1030,8 +1030,8 @@ pf_status capture_graph(pf_handle* H, hipStream_t cs, int g, int v) {
   return PF_OK;
 }
 
-// Captures the graphs that a run of n intervals replays, or the whole ladder,
-// where they are not there yet.  Every capture is on one stream and holds
+// Captures the graphs that a run of n intervals replays best and that are not
+// there yet.  Every capture is on one stream and holds
 // kernel launches only (no event, copy or memset), so a graph never refers to
 // an event or another stream: 2^v intervals for a step v of the ladder, of every filter (plain
 // layout) or of each filter group (batched layout).  The groups' graphs are
@@ -1040,7 +1040,7 @@ pf_status capture_graph(pf_handle* H, hipStream_t cs, int g, int v) {
 // another stream, and launched on the null stream all the same (on another,
 // every run would wait for the null stream's work and make it wait in turn,
 // about 15 us each way).
-pf_status ensure_graphs(pf_handle* H, int n, bool whole) {
+pf_status ensure_graphs(pf_handle* H, int n) {
   const int ng = H->cfg.layout == PF_LAYOUT_BATCHED ? H->groups : 1;
   const int nv = graph_ladder(H);
   if (H->gexecs.empty()) {
@@ -1050,7 +1050,7 @@ pf_status ensure_graphs(pf_handle* H, int n, bool whole) {
   }
   const bool tm = H->timing;
   H->timing = false;
-  auto capture = [&](int v) -> pf_status {
+  pf_status st = for_graphs(nv, n, [&](int v) -> pf_status {
     for (int g = 0; g < ng; ++g) {
       if (H->gexecs[(size_t)g * nv + v]) continue;
       if (!H->stream && !H->cap_stream)
@@ -1058,45 +1058,39 @@ pf_status ensure_graphs(pf_handle* H, int n, bool whole) {
       if (pf_status e = capture_graph(H, H->stream ? H->stream : H->cap_stream, g, v)) return e;
     }
     return PF_OK;
-  };
-  pf_status st = PF_OK;
-  if (whole)
-    for (int v = 0; v < nv && !st; ++v) st = capture(v);
-  else
-    st = for_graphs(nv, n, capture);
+  });
   H->timing = tm;
   // (graphs of an earlier run may still be replaying: wait before they go)
   if (st && drain(H) == PF_OK) destroy_graphs(H);
   return st;
 }
 
-// What a first run's lengths left of the ladder, so that a later run of another
-// length does not wait for its capture (0.4 to 1.5 ms in all).  It is captured
-// once the run is issued, while the device works on it.  A failure is not this
-// run's: the run that needs the graph meets it.
-void finish_graphs(pf_handle* H) {
-  if (std::find(H->gexecs.begin(), H->gexecs.end(), nullptr) == H->gexecs.end()) return;
-  (void)ensure_graphs(H, 0, true);
-  drop_cap_stream(H);
-  err_clear();
-}
-
-// n intervals from the handle's graphs (those captured that are missing).
+// n intervals from the handle's graphs.  A run on a handle that has some goes
+// from those, the longest first, and what it would have liked is captured once
+// it is issued, while the device works on it: only a first run, and one whose
+// remainder no graph is short enough for, waits for a capture.
 pf_status run_graphs(pf_handle* H, int n) {
   const hipStream_t ls = H->stream;
-  pf_status st;
-  if ((st = ensure_graphs(H, n, false))) return st;
   const bool batched = H->cfg.layout == PF_LAYOUT_BATCHED;
-  if (!batched) H->marks_pending = true;
-  const int G = batched ? H->groups : 1;
-  if (G > 1 && (st = fork_groups(H, ls))) return st;
-  st = for_graphs(H->gnv, n, [&](int v) -> pf_status {
-    for (int g = 0; g < G; ++g)
-      HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * H->gnv + v], group_stream(H, g, ls)));
-    return PF_OK;
-  });
+  const int G = batched ? H->groups : 1, nv = graph_ladder(H);
+  // (a capture makes every group's graph of a length, or none stays)
+  auto have = [&](int v) { return !H->gexecs.empty() && H->gexecs[v] != nullptr; };
+  int rest = n;
+  for (int v = nv - 1; v >= 0; --v)
+    if (have(v)) rest &= (1 << v) - 1;
+  pf_status st = ensure_graphs(H, rest);
   if (st) return st;
+  if (!batched) H->marks_pending = true;
+  if (G > 1 && (st = fork_groups(H, ls))) return st;
+  int left = n;
+  for (int v = nv - 1; v >= 0; --v)
+    for (; have(v) && left >= (1 << v); left -= 1 << v)
+      for (int g = 0; g < G; ++g)
+        HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * nv + v], group_stream(H, g, ls)));
   if (G > 1 && (st = join_groups(H, ls))) return st;
+  // (a failure is not this run's: the run that needs the graph meets it)
+  if (ensure_graphs(H, n) != PF_OK) err_clear();
+  drop_cap_stream(H);
   return PF_OK;
 }
 
@@ -1355,9 +1349,7 @@ pf_status pf_graph_run(pf_handle* H, int32_t n_steps) {
     H->t += n_steps;
     return PF_OK;
   }
-  if ((st = run_intervals(H, n_steps))) return st;
-  finish_graphs(H);
-  return PF_OK;
+  return run_intervals(H, n_steps);
 }
 
 pf_status pf_set_theta(pf_handle* H, const double* theta, uint32_t iteration) {
@@ -1807,9 +1799,9 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
   }
   // capture the graphs before the loop
   if (!kalman) {
-    if ((st = ensure_graphs(H, 1, false))) return st;
+    if ((st = ensure_graphs(H, 1))) return st;
     for (int32_t i = 1; i < T; i <<= 1)
-      if ((st = ensure_graphs(P, std::min(i, 1 << (graph_ladder(P) - 1)), false))) return st;
+      if ((st = ensure_graphs(P, std::min(i, 1 << (graph_ladder(P) - 1))))) return st;
   }
 
   pfk::Smc2Args S{};
@@ -1913,10 +1905,6 @@ pf_status pf_smc2(pf_handle* H, pf_handle* P, void* d_ws, size_t ws_bytes, const
     if ((st = run_intervals(H, 1))) return st;
   }
   HIP_TRY(pfk::launch_theta_resample(S, T - 1, 0.5, 0, nullptr, ess_d + (T - 1), s));
-  if (!kalman) {
-    finish_graphs(H);
-    finish_graphs(P);
-  }
 
   // outputs
   std::vector<double> ell((size_t)B * c.T);
@@ -2144,7 +2132,7 @@ pf_status time_graph_replay(pf_handle* H, int n, double* ms_out) {
   pf_status st = do_init(H, H->stream);
   if (st) return st;
   H->eager_replay = false;
-  if ((st = pf_graph_run(H, 1))) return st;  // captures the graphs
+  if ((st = ensure_graphs(H, n)) || (st = pf_graph_run(H, 1))) return st;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);

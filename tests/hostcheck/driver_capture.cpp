@@ -2,11 +2,13 @@
 // capturing, over the CPU stand-in runtime (fake_hip.cpp): refused, with
 // nothing recorded into the capture, and the ancestors that were pending
 // before are still written out by the next run.  The kernel stubs count their
-// calls by name.  And which calls capture graphs: a handle's first run of each
-// tuning, whatever its length, and no later one.
+// calls by name.  And which calls wait for the capture of a graph: a handle's
+// first run of each tuning; a later one only where its remainder is shorter
+// than every graph there is.
 //   driver_capture refused | ladder
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -18,7 +20,7 @@
 
 static std::map<std::string, int> g_calls;
 extern "C" void note_kernel(const char* name) { ++g_calls[name]; }
-extern "C" int fake_captures(void);
+extern "C" void fake_trace(std::string* out);
 
 #define CHECK_(c)                                          \
   do {                                                     \
@@ -109,16 +111,28 @@ static void ladder() {
     void* ws = aligned_alloc(256, (n + 255) / 256 * 256);
     pf_handle* h = nullptr;
     CHECK_(pf_init(&c, ws, n, nullptr, &h) == PF_OK);
-    for (int groups : {1, 2}) {
+    // (the plain layout has no groups to tune)
+    for (int groups = 1; groups <= (layout == PF_LAYOUT_BATCHED ? 2 : 1); ++groups) {
       CHECK_(pf_set_tuning(h, 512, groups) == PF_OK);
       CHECK_(pf_reset(h, 0) == PF_OK);
-      CHECK_(pf_graph_run(h, 10) == PF_OK);
-      const int first = fake_captures();
-      CHECK_(first > 0);
-      for (int len : {1, 3, 20, 255, 4}) {
+      const int G = groups;  // graphs of each length
+      auto run = [&](int len) {
+        std::string tr;
+        fake_trace(&tr);
         CHECK_(pf_graph_run(h, len) == PF_OK);
-        CHECK_(fake_captures() == first);
-      }
+        fake_trace(&tr);
+        return tr;
+      };
+      auto waits = [](const std::string& tr) { return tr.find('L'); };
+      auto launches = [](const std::string& tr) { return std::count(tr.begin(), tr.end(), 'L'); };
+      std::string tr = run(10);  // graphs of 8 and 2
+      CHECK_(waits(tr) == (size_t)(2 * G) && launches(tr) == 2 * G);
+      tr = run(100);  // 12 of 8 and 2 of 2; 64, 32 and 4 captured behind them
+      CHECK_(waits(tr) == 0 && launches(tr) == 14 * G && tr.size() == (size_t)(17 * G));
+      tr = run(101);  // the graph of 1 is waited for
+      CHECK_(waits(tr) == (size_t)G && launches(tr) == 4 * G && tr.size() == (size_t)(5 * G));
+      tr = run(89);  // 64, 8, 8, 8, 1; 16 captured behind them
+      CHECK_(waits(tr) == 0 && launches(tr) == 5 * G && tr.size() == (size_t)(6 * G));
     }
     CHECK_(pf_destroy(h) == PF_OK);
     free(ws);

@@ -20,6 +20,7 @@
 #include <cstring>
 #include <functional>
 #include <set>
+#include <string>
 #include <vector>
 
 #define CHECK(c, ...)                                 \
@@ -74,7 +75,7 @@ struct FExec {
 // objects are never freed, so a use after destruction is caught
 std::set<void*> g_streams, g_events, g_graphs, g_execs;
 FStream g_null;
-int g_captures = 0;
+std::string g_trace;  // C for every capture begun, L for every graph launch
 double g_clock = 0;
 
 FStream* S(hipStream_t s) {
@@ -124,8 +125,11 @@ void op(hipStream_t s, std::function<void()> fn) {
 extern "C" void fake_kernel(hipStream_t s) {
   op(s, [] {});
 }
-// captures begun so far
-extern "C" int fake_captures(void) { return g_captures; }
+// captures begun (C) and graphs launched (L) since the last call
+extern "C" void fake_trace(std::string* out) {
+  out->swap(g_trace);
+  g_trace.clear();
+}
 
 extern "C" {
 
@@ -257,7 +261,7 @@ hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   FStream* f = S(s);
   CHECK(!f->cap, "begin capture on a stream already capturing");
   FGraph* g = new FGraph();
-  ++g_captures;
+  g_trace += 'C';
   g_graphs.insert(g);
   f->cap = g;
   f->origin = true;
@@ -301,6 +305,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t ex, hipStream_t s) {
   FStream* f = S(s);
   CHECK(!f->cap, "graph launch inside a capture");
   if (!s) CHECK(!capture_open(), "graph launch on the null stream while a capture is open");
+  g_trace += 'L';
   for (auto& n : x->nodes) n();
   x->launches.push_back({f, f->ops});
   f->ops++;

@@ -1,6 +1,6 @@
 """pf_graph_run and stream capture, on the CPU stand-in runtime
 (tests/hostcheck): a call inside a caller's capture that is refused leaves the
-handle as it was, and a handle's graphs are all captured by its first run."""
+handle as it was, and a run waits for a capture only where it has to."""
 import os
 import subprocess
 
@@ -42,5 +42,5 @@ def test_refused_capture_leaves_the_pending_ancestors(driver):
     _run(driver, "refused")
 
 
-def test_only_a_first_run_captures(driver):
+def test_a_later_run_goes_from_the_graphs_there_are(driver):
     _run(driver, "ladder")
