@@ -180,7 +180,12 @@ pf_status pf_destroy(pf_handle* h);
  * groups' are launched on streams of their own between a fork from and a join
  * into the handle's stream); a run replays the longest that fit first (200 =
  * 128 + 64 + 8).  Plain windkessel filters of up to 2,048 particles (several:
- * 4,096) take one launch per chunk of intervals instead.  A batched handle set
+ * 4,096) with K <= 253 and no history attached take two launches per chunk of
+ * intervals instead, the random numbers and then the intervals of every
+ * filter, after two per filter that write out the ancestors of eager steps
+ * (under Metropolis and rejection resampling where that is the cheaper, and
+ * while an interval's numbers take at most 256 MiB); on a stream that is being
+ * captured they are refused (PF_E_DEVICE).  A batched handle set
  * to eager replay (pf_set_replay, or pf_autotune when it measured eager
  * launches faster on this host) issues the same kernels as eager launches
  * instead.  Same results as the eager calls either way. */
