@@ -746,6 +746,12 @@ pf_status enqueue_resample(pf_handle* H, hipStream_t s, const double* u) {
   return PF_OK;
 }
 
+// Whether s is being captured (or cannot be asked).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
 // Whether a run of the small windkessel filters goes one workgroup per filter
 // (pf_small.hip).  With systematic, stratified and multinomial resampling it
 // always does (1,024 particles, K = 10: 6.3, 10.0 and 9.4 us an interval against
@@ -780,10 +786,7 @@ pf_status enqueue_small(pf_handle* H, hipStream_t s, int n) {
   const pf_config& c = H->cfg;
   // a caller's capture is refused before anything is recorded into it: its
   // replays would run past T, and the write-out below would not have run
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIP_TRY(hipStreamIsCapturing(s, &cap));
-  if (cap != hipStreamCaptureStatusNone)
-    return fail(PF_E_DEVICE, "pf_graph_run on a capturing stream");
+  if (capturing(s)) return fail(PF_E_DEVICE, "pf_graph_run on a capturing stream");
   if (H->marks_pending)
     for (int b = 0; b < c.B; ++b)
       if (pf_status st = plain_anc_out(H, b, s)) return st;
@@ -1088,8 +1091,9 @@ pf_status run_graphs(pf_handle* H, int n) {
       for (int g = 0; g < G; ++g)
         HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * nv + v], group_stream(H, g, ls)));
   if (G > 1 && (st = join_groups(H, ls))) return st;
-  // (a failure is not this run's: the run that needs the graph meets it)
-  if (ensure_graphs(H, n) != PF_OK) err_clear();
+  // (a failure is not this run's: the run that needs the graph meets it; nor is
+  // a caller's capture, which ours would end)
+  if (!capturing(ls) && ensure_graphs(H, n) != PF_OK) err_clear();
   drop_cap_stream(H);
   return PF_OK;
 }

@@ -338,3 +338,42 @@ def test_filter_groups_do_not_change_results(pfm):
     for o in outs[1:]:
         for a, b in zip(o, outs[0]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+def test_run_of_a_new_length_leaves_a_callers_capture(pfm, layout):
+    """pf_graph_run on a stream that its caller is capturing, of a length that
+    the handle's graphs make up but have no graph for: whether the runtime
+    takes the launches or refuses them, the capture stays valid (no capture of
+    ours is begun or waited for inside it) and the run's outputs are the eager
+    steps'."""
+    import torch
+    T = 16
+    pb = W.lorenz96(d=8, N=500, T=T, K=2)
+    pb = pb.with_obs(np.random.default_rng(4).standard_normal((T, 8)))
+    s = torch.cuda.Stream()
+    f, g = (pfm.Filter(pb, precision=0, layout=layout, stream=s) for _ in range(2))
+    f.advance(T)
+    g.graph_run(2)
+    x = torch.zeros(4, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    taken = True
+    with torch.cuda.stream(s):
+        graph.capture_begin(capture_error_mode="thread_local")
+        x.add_(1.0)
+        try:
+            g.graph_run(4)
+        except pfm.PfError:
+            taken = False
+        graph.capture_end()
+        graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(x.cpu(), torch.ones(4))
+    if not taken:
+        g.graph_run(4)
+    g.graph_run(T - 6)
+    for a, b in zip((f.get_state(), *f.trace()), (g.get_state(), *g.trace())):
+        np.testing.assert_array_equal(a, b)
+    f.close()
+    g.close()
