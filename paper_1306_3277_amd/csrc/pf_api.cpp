@@ -1056,6 +1056,8 @@ pf_status ensure_graphs(pf_handle* H, int n) {
   pf_status st = for_graphs(nv, n, [&](int v) -> pf_status {
     for (int g = 0; g < ng; ++g) {
       if (H->gexecs[(size_t)g * nv + v]) continue;
+      if (capturing(H->stream))
+        return fail(PF_E_DEVICE, "pf_graph_run's graphs captured on a capturing stream");
       if (!H->stream && !H->cap_stream)
         HIP_TRY(hipStreamCreateWithFlags(&H->cap_stream, hipStreamNonBlocking));
       if (pf_status e = capture_graph(H, H->stream ? H->stream : H->cap_stream, g, v)) return e;
@@ -1063,8 +1065,9 @@ pf_status ensure_graphs(pf_handle* H, int n) {
     return PF_OK;
   });
   H->timing = tm;
-  // (graphs of an earlier run may still be replaying: wait before they go)
-  if (st && drain(H) == PF_OK) destroy_graphs(H);
+  // (graphs of an earlier run may still be replaying: wait before they go; a
+  // caller's capture stopped ours before it began, and waiting would end it)
+  if (st && !capturing(H->stream) && drain(H) == PF_OK) destroy_graphs(H);
   return st;
 }
 
@@ -1091,9 +1094,8 @@ pf_status run_graphs(pf_handle* H, int n) {
       for (int g = 0; g < G; ++g)
         HIP_TRY(hipGraphLaunch(H->gexecs[(size_t)g * nv + v], group_stream(H, g, ls)));
   if (G > 1 && (st = join_groups(H, ls))) return st;
-  // (a failure is not this run's: the run that needs the graph meets it; nor is
-  // a caller's capture, which ours would end)
-  if (!capturing(ls) && ensure_graphs(H, n) != PF_OK) err_clear();
+  // (a failure is not this run's: the run that needs the graph meets it)
+  if (ensure_graphs(H, n) != PF_OK) err_clear();
   drop_cap_stream(H);
   return PF_OK;
 }

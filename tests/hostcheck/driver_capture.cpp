@@ -5,7 +5,7 @@
 // calls by name.  And which calls wait for the capture of a graph: a handle's
 // first run of each tuning; a later one only where its remainder is shorter
 // than every graph there is.
-//   driver_capture refused | ladder
+//   driver_capture refused | first | ladder
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -139,8 +139,53 @@ static void ladder() {
   }
 }
 
+// A first run on a stream that its caller is capturing: refused before a
+// capture of the handle's own is begun or anything is waited for (the stand-in
+// stops at either), and the caller's capture goes on.
+static void first() {
+  for (int layout : {PF_LAYOUT_PLAIN, PF_LAYOUT_BATCHED}) {
+    const int B = 3, T = 9, d = 4;
+    const std::vector<int64_t> np = {300, 70, 1000};
+    const std::vector<int32_t> idx = {0, 1, 2, 3};
+    const std::vector<double> obs((size_t)T * d, 0.5), theta = {8.0, 0.1, 7.0, 0.2, 9.0, 0.1};
+    pf_config c{};
+    c.model = PF_MODEL_L96;
+    c.precision = PF_FP64;
+    c.layout = layout;
+    c.d = d;
+    c.K = 2;
+    c.T = T;
+    c.h = 0.05;
+    c.n_obs = d;
+    c.obs_idx = idx.data();
+    c.obs_sd = 0.5;
+    c.obs = obs.data();
+    c.B = B;
+    c.n_theta = 2;
+    c.n_particles = np.data();
+    c.theta = theta.data();
+    const size_t n = pf_workspace_bytes(&c);
+    CHECK_(n > 0);
+    void* ws = aligned_alloc(256, (n + 255) / 256 * 256);
+    hipStream_t s;
+    CHECK_(hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess);
+    pf_handle* h = nullptr;
+    CHECK_(pf_init(&c, ws, n, s, &h) == PF_OK);
+    CHECK_(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess);
+    CHECK_(pf_graph_run(h, 3) == PF_E_DEVICE);
+    hipGraph_t g;
+    CHECK_(hipStreamEndCapture(s, &g) == hipSuccess);
+    CHECK_(hipGraphDestroy(g) == hipSuccess);
+    CHECK_(pf_graph_run(h, 9) == PF_OK);
+    CHECK_(pf_destroy(h) == PF_OK);
+    CHECK_(hipStreamDestroy(s) == hipSuccess);
+    free(ws);
+  }
+}
+
 int main(int, char** argv) {
   if (std::string(argv[1]) == "refused") refused();
+  else if (std::string(argv[1]) == "first") first();
   else ladder();
   printf("done\n");
   return 0;

@@ -44,3 +44,7 @@ def test_refused_capture_leaves_the_pending_ancestors(driver):
 
 def test_a_later_run_goes_from_the_graphs_there_are(driver):
     _run(driver, "ladder")
+
+
+def test_first_run_refused_inside_a_capture(driver):
+    _run(driver, "first")
