@@ -203,8 +203,9 @@ pf_status pf_reset(pf_handle* h, uint32_t iteration);
 /* Exact marginal likelihood of every filter's parameters under the
  * windkessel model by the Kalman filter (Sec. 3.1.1, Alg. 1 with one state
  * and one observation, where each Cholesky factor is a square root), a wave
- * per filter (a lane for very many), FP64: from N(m0, s0^2), per substep m <- a m + c q_{n-1},
- * V <- a^2 V + sigma_p^2; per observation v = y - (m + Z q), S = V + obs_sd^2,
+ * per filter (a lane for very many, or a single interval), FP64: from
+ * N(m0, s0^2), per substep m <- a m + c q_{n-1}, V <- a^2 V + sigma_p^2; per
+ * observation v = y - (m + Z q), S = V + obs_sd^2,
  * ell = -(ln(2 pi S) + v^2/S)/2, then m += (V/S) v, V <- (1 - V/S) V.
  * loglik_out [B] and, if not NULL, ell_out [B][T] are host arrays; the
  * handle's particles are untouched.  Synchronous. */
